@@ -71,8 +71,10 @@ typedef enum { TS3_ACCUM_FP32 = 0, TS3_ACCUM_FP64 = 1 } ts3_accum;
  *                matrix cores throughout.  The runtime-shape kernels read
  *                either storage type and compute in float32 on vector units.
  *  group_span  : Q, points per accumulation span (1 <= Q <= 2^30).  Pass 1
- *                reduces each span to one partial and sums spans in index
- *                order, so results do not depend on how the mesh is tiled.
+ *                reduces each span to partials of its consecutive parts and sums
+ *                them in index order, so results do not depend on how the mesh
+ *                is tiled.  How many parts (one, unless the mesh has too few
+ *                spans to fill the GPU) follows from this struct alone.
  *  accum       : ts3_accum, the precision of the fold of span partials (the
  *                sum over tiles of Eq. (4); Appendix A.4 on accumulating over
  *                very large meshes).  TS3_ACCUM_FP32 adds the float32 span
@@ -80,7 +82,8 @@ typedef enum { TS3_ACCUM_FP32 = 0, TS3_ACCUM_FP64 = 1 } ts3_accum;
  *                rounds once to float32.  Each span's own partial is float32
  *                either way.  Any other value is TS3_ERR_INVALID_ARG.
  *  max_points  : largest point index + 1 the state will accumulate; sizes the
- *                span partials (ceil(max_points / Q) * H * M * (C+1) floats). */
+ *                span partials (ceil(max_points / Q) * H * M * (C+1) floats, or
+ *                up to 128 MiB where spans are cut into parts). */
 typedef struct {
     int32_t C, H, M, dh;
     float temperature;
@@ -183,7 +186,9 @@ ts3_status ts3_deslice(const ts3_state *st, const ts3_weights *w, const void *x_
 /* Whole layer on a resident mesh (Algorithm 1): reset, accumulate tiles of
  * `tile` points, finalize, attention, deslice chunks of `chunk` points.
  * tile must be a multiple of group_span; N <= max_points.  Allocates nothing.
- * Consecutive tiles (and chunks) are enqueued alternately on `stream` and on
+ * A launch covers several tiles (or chunks), up to about 4M points, which
+ * changes no result.
+ * Consecutive launches are enqueued alternately on `stream` and on
  * a second stream that the state owns, forked from `stream` by an event and
  * joined back into it before the call returns: work enqueued on `stream`
  * afterwards sees the whole layer.  Leaves the state ATTENDED. */
@@ -195,12 +200,12 @@ ts3_status ts3_layer_forward(ts3_state *st, const ts3_weights *w, const void *x,
  * allocation.  Same arguments and results as ts3_layer_forward (bitwise equal
  * outputs for the same desc, weights, x, N and tile), but there is no state
  * object: every buffer beyond x, out and the weights lives in one fixed
- * 64 MiB device array inside the library.  Each GPU the library runs on holds
+ * 80 MiB device array inside the library.  Each GPU the library runs on holds
  * its own copy of that array from the first call on that device until the
  * process ends.  The call allocates and frees nothing (no hipMalloc, no
  * stream or event creation).  All its work runs on `stream`; tiles run one
  * after another (no second stream).
- *  - Scratch needed: the span partials of one tile, ceil(tile / group_span) *
+ *  - Scratch counted: the span partials of one tile, ceil(tile / group_span) *
  *    H*M*(C+1) floats, plus the run sums of the mesh, ceil(ceil(N /
  *    group_span) / 64) * H*M*(C+1) floats (doubles with TS3_ACCUM_FP64), plus
  *    under 1 MiB of token-side buffers.  At C=128, H*M=512, group_span 15,625
@@ -209,7 +214,8 @@ ts3_status ts3_layer_forward(ts3_state *st, const ts3_weights *w, const void *x,
  *  - Calls that overlap on one GPU (from several threads or streams) share the
  *    array and race: serialise them.  The array keeps the last call's
  *    contents; every region a call reads is written by that call first.
- *  - desc is validated as for ts3_state_create (max_points is not used).
+ *  - desc is validated as for ts3_state_create; max_points (N, if larger) only
+ *    decides how spans are cut into parts.
  *  - N = 0 is valid: only the token-side work of an empty mesh runs and out
  *    is not touched.
  * The cached state is not retained after the call returns. */
@@ -243,7 +249,8 @@ ts3_status ts3_state_get(const ts3_state *st, int32_t which, float *host_dst, in
                          void *stream);
 
 /* Copy the span partials of spans [span0, span0 + nspan) to host memory, after
- * synchronising `stream`: [nspan][H][M][C+1] floats, where columns 0..C-1 hold
+ * synchronising `stream` (a span summed in parts is the float32 sum of their
+ * partials in order): [nspan][H][M][C+1] floats, where columns 0..C-1 hold
  * the sum over the span's points of w_i x_i and column C the sum of w_i.  These
  * are the per-span terms of Eq. (4) before the ordered fold (finalize sums them
  * in span order).  Every requested span must have been accumulated since the

@@ -5,7 +5,9 @@
 
 #include <algorithm>
 #include <atomic>
+#include <memory>
 #include <mutex>
+#include <new>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -65,21 +67,21 @@ enum Phase { PH_RESET = 0, PH_ACCUM = 1, PH_FINAL = 2, PH_ATTEND = 3 };
 // runtime-shape kernels (rt) for the other multiples of 16.  The pass entry
 // points take C and M, which only the runtime-shape ones read.
 struct Kernels {
-    void (*pass1)(const void *, int64_t, int64_t, int32_t, int32_t, int32_t, int32_t, int32_t, const void *,
+    void (*pass1)(const void *, int64_t, int64_t, SpanGeo, int32_t, int32_t, int32_t, int32_t, const void *,
                   const float *, float *, hipStream_t);
     hipError_t (*pass2)(const void *, int64_t, int32_t, int32_t, int32_t, const void *, const float *, const void *,
                         void *, hipStream_t);
     // Backward (float32 storage only; NULL for bfloat16).
-    void (*bw_head)(const float *, const float *, int64_t, int64_t, int32_t, int32_t, int32_t, const float *,
+    void (*bw_head)(const float *, const float *, int64_t, int64_t, SpanGeo, int32_t, int32_t, const float *,
                     const float *, float *, hipStream_t);
     void (*bw_dx)(const float *, const float *, int64_t, int32_t, const float *, const float *, const float *,
                   const float *, const float *, const float *, const float *, float, float *, float *,
                   hipStream_t);
-    void (*bw_dw2)(const float *, const float *, int64_t, int64_t, int32_t, int32_t, int32_t, float *,
+    void (*bw_dw2)(const float *, const float *, int64_t, int64_t, SpanGeo, int32_t, int32_t, float *,
                    hipStream_t);
     // Pass 1 in the projected form (bfloat16, C = 128, head width 16): x, n,
-    // span0, Q, nspan, H, W2', b2', W1 fragments, partials [span][H][M][17].
-    void (*pass1p)(const void *, int64_t, int64_t, int32_t, int32_t, int32_t, const void *, const float *,
+    // span0, geo, nspan, H, W2', b2', W1 fragments, partials [span][H][M][17].
+    void (*pass1p)(const void *, int64_t, int64_t, SpanGeo, int32_t, int32_t, const void *, const float *,
                    const void *, float *, hipStream_t) = nullptr;
     // Pass 2 in the slice-state form (bfloat16, head width 16): x, n, W2', b2',
     // s'^T fragments, W3^T fragments, b3, out.  NULL where it does not apply.
@@ -89,26 +91,26 @@ struct Kernels {
 };
 
 template <typename T, int C, int M>
-void launch_pass1(const void *x, int64_t n, int64_t span0, int32_t Q, int32_t nspan, int32_t H, int32_t, int32_t,
+void launch_pass1(const void *x, int64_t n, int64_t span0, SpanGeo geo, int32_t nspan, int32_t H, int32_t, int32_t,
                   const void *w2p, const float *b2s, float *partials, hipStream_t st) {
     if constexpr (sizeof(T) == 2 && C == 256) {
         // Wide rows: two heads per workgroup, two producer and two consumer
         // waves per head (H is even for every wide shape check_desc accepts).
         hipLaunchKernelGGL((k_slice_accumulate_pcw<C, M>), dim3(nspan * (H / 2)), dim3(512), 0, st,
-                           (const bf16_t *)x, n, span0, Q, nspan, H, (const bf16_t *)w2p, b2s, partials);
+                           (const bf16_t *)x, n, span0, geo, nspan, H, (const bf16_t *)w2p, b2s, partials);
     } else if constexpr (sizeof(T) == 2 && M >= 32 && C == 128) {
         // Two heads per workgroup whenever H is even (independently of the
         // span count, so that every tiling sums a span the same way); the one
         // odd case, H = 1, takes the generic kernel.
         if (H % 2 == 0)
             hipLaunchKernelGGL((k_slice_accumulate_pc<C, M>), dim3(nspan * (H / 2)), dim3(512), 0, st,
-                               (const bf16_t *)x, n, span0, Q, nspan, H, (const bf16_t *)w2p, b2s, partials);
+                               (const bf16_t *)x, n, span0, geo, nspan, H, (const bf16_t *)w2p, b2s, partials);
         else
             hipLaunchKernelGGL((k_slice_accumulate<T, C, M>), dim3(nspan * H), dim3(256), 0, st,
-                               (const T *)x, n, span0, Q, nspan, H, (const T *)w2p, b2s, partials);
+                               (const T *)x, n, span0, geo, nspan, H, (const T *)w2p, b2s, partials);
     } else {
         hipLaunchKernelGGL((k_slice_accumulate<T, C, M>), dim3(nspan * H), dim3(256), 0, st,
-                           (const T *)x, n, span0, Q, nspan, H, (const T *)w2p, b2s, partials);
+                           (const T *)x, n, span0, geo, nspan, H, (const T *)w2p, b2s, partials);
     }
 }
 
@@ -188,18 +190,18 @@ hipError_t launch_pass2(const void *x, int64_t n, int32_t H, int32_t, int32_t, c
 }
 
 template <int C, int M>
-void launch_bw_head(const float *x, const float *g, int64_t n, int64_t span0, int32_t Q, int32_t nspan,
+void launch_bw_head(const float *x, const float *g, int64_t n, int64_t span0, SpanGeo geo, int32_t nspan,
                     int32_t H, const float *w2p, const float *b2s, float *partials, hipStream_t st) {
     const int64_t places = (int64_t)BW_XCDS * ((nspan + BW_XCDS - 1) / BW_XCDS) * H;
-    hipLaunchKernelGGL((k_bw_head<C, M>), dim3((unsigned)places), dim3(512), 0, st, x, g, n, span0, Q, nspan, H,
+    hipLaunchKernelGGL((k_bw_head<C, M>), dim3((unsigned)places), dim3(512), 0, st, x, g, n, span0, geo, nspan, H,
                        w2p, b2s, partials);
 }
 
 template <int C, int M>
-void launch_bw_dw2(const float *x, const float *dzs, int64_t n, int64_t span0, int32_t Q, int32_t nspan, int32_t H,
+void launch_bw_dw2(const float *x, const float *dzs, int64_t n, int64_t span0, SpanGeo geo, int32_t nspan, int32_t H,
                    float *partials, hipStream_t st) {
     const int64_t places = (int64_t)BW_XCDS * ((nspan + BW_XCDS - 1) / BW_XCDS) * H;
-    hipLaunchKernelGGL((k_bw_dw2<C, M>), dim3((unsigned)places), dim3(512), 0, st, x, dzs, n, span0, Q, nspan, H,
+    hipLaunchKernelGGL((k_bw_dw2<C, M>), dim3((unsigned)places), dim3(512), 0, st, x, dzs, n, span0, geo, nspan, H,
                        partials);
 }
 
@@ -215,10 +217,10 @@ void launch_bw_dx(const float *x, const float *g, int64_t n, int32_t H, const fl
 }
 
 template <int C, int M>
-void launch_pass1p(const void *x, int64_t n, int64_t span0, int32_t Q, int32_t nspan, int32_t H, const void *w2p,
+void launch_pass1p(const void *x, int64_t n, int64_t span0, SpanGeo geo, int32_t nspan, int32_t H, const void *w2p,
                    const float *b2s, const void *w1p, float *partials, hipStream_t st) {
     hipLaunchKernelGGL((k_slice_accumulate_pcp<C, M>), dim3(nspan * (H / 2)), dim3(PCP_THREADS), 0, st, (const bf16_t *)x,
-                       n, span0, Q, nspan, H, (const bf16_t *)w2p, b2s, (const bf16_t *)w1p, partials);
+                       n, span0, geo, nspan, H, (const bf16_t *)w2p, b2s, (const bf16_t *)w1p, partials);
 }
 
 template <int C, int M>
@@ -262,16 +264,17 @@ template <typename T, int C, int M> Kernels make_kernels() {
 constexpr int64_t RT_MAX_WGS = 1 << 22;
 
 template <typename T>
-void launch_pass1_rt(const void *x, int64_t n, int64_t span0, int32_t Q, int32_t nspan, int32_t H, int32_t C,
+void launch_pass1_rt(const void *x, int64_t n, int64_t span0, SpanGeo geo, int32_t nspan, int32_t H, int32_t C,
                      int32_t M, const void *w2r, const float *b2s, float *partials, hipStream_t st) {
     const size_t lds = (size_t)RT_PTS * (C + M) * 4;
     const int64_t per_span = (int64_t)H * ((C + 63) / 64);
     const int64_t batch = std::max<int64_t>(1, RT_MAX_WGS / per_span);
     for (int64_t s0 = 0; s0 < nspan; s0 += batch) {
         const int64_t ns = std::min<int64_t>(batch, nspan - s0);
+        SpanGeo part = geo;
+        part.first += (int32_t)s0;
         hipLaunchKernelGGL(k_slice_accumulate_rt<T>, dim3((unsigned)(ns * per_span)), dim3(256), lds, st,
-                           (const T *)x + s0 * Q * C, n - s0 * Q, span0 + s0, Q, H, C, M, (const T *)w2r, b2s,
-                           partials);
+                           (const T *)x, n, span0 + s0, part, H, C, M, (const T *)w2r, b2s, partials);
     }
 }
 template <typename T>
@@ -328,8 +331,10 @@ struct ts3_state {
     ts3_desc desc;
     Kernels k;
     int esize;          // bytes per io element
-    int64_t nspan_max;  // spans the partial buffer holds
-    int64_t E;          // floats per (span, head-block) partial row group: H*M*(C+1)
+    int64_t nspan_max;  // spans of max_points
+    SpanGeo geo;        // how a span is cut into the parts that pass 1 sums apart
+    int64_t npart_max;  // parts the partial buffer holds
+    int64_t E;          // floats per part: H*M*(rowc+1)
     int64_t nrun_max;
     // device buffers
     float *partials = nullptr, *runs = nullptr, *s_raw = nullptr, *dsum = nullptr, *s = nullptr,
@@ -349,6 +354,7 @@ struct ts3_state {
     // host bookkeeping
     std::vector<uint8_t> span_written;
     int64_t span_hi = 0;
+    int64_t part_hi = 0;  // parts up to the last one accumulated
     int phase = PH_RESET;
     bool w2_ready = false;
     bool partials_fwd = false;  // the partial buffer holds pass-1 span sums (not a backward's)
@@ -398,6 +404,37 @@ ts3_status check_desc(const ts3_desc *d) {
     if (nspan * (int64_t)d->H > (int64_t)INT32_MAX)
         return fail(TS3_ERR_UNSUPPORTED, "too many spans: raise group_span");
     return TS3_OK;
+}
+
+// The parts of a span (SpanGeo) for a state of max_points points.  A workgroup
+// sums one part for one head or head pair, so a mesh of few spans would leave
+// most compute units idle: at 100,003 points and spans of 32,768 (bf16, C =
+// 128, H = 8, M = 64) pass 1 ran 16 workgroups and took 343 us, with parts of
+// 1,632 points 248 workgroups.  The part length gives one workgroup per compute
+// unit for the whole mesh (a second round would pay a workgroup's start and end
+// again, about 3 us against 1.3 us per 96 points), but at most PART_POINTS, so that
+// a mesh that arrives in tiles still spreads each tile, unless the mesh fills
+// PART_ROUNDS rounds with longer ones: at 16M points parts of 5,216 instead of
+// whole spans of 15,625 made the layer 1.8% slower.  Never more than PART_BYTES of
+// partials through the split, and a multiple of the points that a workgroup's
+// waves take per step.  Only desc enters the rule, so a state's sums do not depend
+// on the tiling.
+constexpr int64_t PART_POINTS = 4096, PART_WGS = 256, PART_ROUNDS = 4, PART_BYTES = int64_t(128) << 20;
+
+SpanGeo span_geo(const ts3_desc &d, const Kernels &k, bool proj, int64_t E) {
+    const bool pairs = d.H % 2 == 0 && d.io_dtype == TS3_BF16 && !k.rt && (d.C == 256 || (d.C == 128 && d.M >= 32));
+    const int64_t unit = proj ? 96 : !pairs ? 128 : d.C == 256 ? 32 : 64;
+    const int64_t wgs = k.rt ? (int64_t)d.H * ((d.C + 63) / 64) : pairs ? d.H / 2 : d.H;  // per part
+    const int64_t N = std::max<int64_t>(d.max_points, 1), Q = d.group_span;
+    const int64_t one_round = (N * wgs + PART_WGS - 1) / PART_WGS;
+    const int64_t want = std::min(one_round, std::max(PART_POINTS, one_round / PART_ROUNDS));
+    const int64_t nspan = (N + Q - 1) / Q;
+    int64_t S = (Q + want - 1) / want;
+    S = std::max<int64_t>(1, std::min<int64_t>(S, PART_BYTES / (nspan * E * 4)));
+    if (S <= 1) return SpanGeo{(int32_t)Q, (int32_t)Q, 1, 0};
+    const int64_t L = ((Q + S - 1) / S + unit - 1) / unit * unit;
+    if (L >= Q) return SpanGeo{(int32_t)Q, (int32_t)Q, 1, 0};
+    return SpanGeo{(int32_t)Q, (int32_t)L, (int32_t)((Q + L - 1) / L), 0};
 }
 
 ts3_status check_weights_w2(const ts3_weights *w) {
@@ -520,13 +557,15 @@ ts3_status ts3_state_create(const ts3_desc *desc, ts3_state **out) {
     st->proj = st->k.pass1p && d.H * 16 == d.C;
     st->rowc = st->proj ? 16 : d.C;
     st->E = (int64_t)d.H * d.M * (st->rowc + 1);
-    st->nrun_max = (st->nspan_max + FOLD - 1) / FOLD;
+    st->geo = span_geo(d, st->k, st->proj, st->E);
+    st->npart_max = std::max<int64_t>(1, st->geo.parts(d.max_points));
+    st->nrun_max = (st->npart_max + FOLD - 1) / FOLD;
     const int64_t HM = (int64_t)d.H * d.M;
     struct Req {
         void **p;
         int64_t bytes;
     } reqs[] = {
-        {(void **)&st->partials, st->nspan_max * st->E * 4},
+        {(void **)&st->partials, st->npart_max * st->E * 4},
         {(void **)&st->runs, st->nrun_max * st->E * 8},  // float or double run sums
         {(void **)&st->s_raw, HM * d.C * 4},
         {(void **)&st->dsum, HM * 4},
@@ -580,6 +619,7 @@ ts3_status ts3_state_reset(ts3_state *st, void *stream) {
     if (!st) return fail(TS3_ERR_INVALID_ARG, "state is NULL");
     std::fill(st->span_written.begin(), st->span_written.end(), 0);
     st->span_hi = 0;
+    st->part_hi = 0;
     st->phase = PH_RESET;
     st->w2_ready = false;
     st->partials_fwd = false;
@@ -613,6 +653,8 @@ ts3_status ts3_slice_accumulate(ts3_state *st, const ts3_weights *w, const void 
         return fail(TS3_ERR_INVALID_ARG, "W1 differs from the one recorded at the first accumulate");
     const int64_t span0 = point_offset / Q;
     const int64_t nspan = (n_tile + Q - 1) / Q;
+    const int64_t part0 = span0 * st->geo.S;
+    const int32_t nparts = (int32_t)st->geo.parts(n_tile);
     const bool ragged = n_tile % Q != 0;
     for (int64_t i = span0; i < span0 + nspan; ++i)
         if (st->span_written[(size_t)i])
@@ -629,15 +671,14 @@ ts3_status ts3_slice_accumulate(ts3_state *st, const ts3_weights *w, const void 
         if (s != TS3_OK) return s;
     }
     if (st->proj)
-        st->k.pass1p(x_tile, n_tile, span0, (int32_t)Q, (int32_t)nspan, d.H, st->w2p, st->b2s, st->w1p, st->partials,
-                     hs);
+        st->k.pass1p(x_tile, n_tile, part0, st->geo, nparts, d.H, st->w2p, st->b2s, st->w1p, st->partials, hs);
     else
-        st->k.pass1(x_tile, n_tile, span0, (int32_t)Q, (int32_t)nspan, d.H, d.C, d.M, st->w2p, st->b2s, st->partials,
-                hs);
+        st->k.pass1(x_tile, n_tile, part0, st->geo, nparts, d.H, d.C, d.M, st->w2p, st->b2s, st->partials, hs);
     LAUNCH_CHECK("slice_accumulate");
     for (int64_t i = span0; i < span0 + nspan; ++i) st->span_written[(size_t)i] = 1;
     if (ragged) st->span_written[(size_t)(span0 + nspan - 1)] = 2;
     st->span_hi = std::max(st->span_hi, span0 + nspan);
+    st->part_hi = std::max(st->part_hi, part0 + nparts);
     st->phase = PH_ACCUM;
     st->partials_fwd = true;
     return TS3_OK;
@@ -647,7 +688,7 @@ ts3_status ts3_slice_accumulate(ts3_state *st, const ts3_weights *w, const void 
 
 namespace {
 
-// Ordered fold of the first nspan span partials into main [H*M*C] and the
+// Ordered fold of the first nspan part sums into main [H*M*C] and the
 // column C entries into col [H*M] (the forward's fold kernels).
 template <typename T>
 ts3_status fold_partials_t(ts3_state *st, int64_t nspan, int rowc, float *main, float *col, hipStream_t hs) {
@@ -680,19 +721,21 @@ ts3_status ts3_slice_finalize(ts3_state *st, const ts3_weights *w, void *stream)
     const ts3_desc &d = st->desc;
     hipStream_t hs = (hipStream_t)stream;
     const int64_t E = st->E;
-    const int64_t nspan = std::max<int64_t>(st->span_hi, 1);
-    // Spans below span_hi that no tile wrote contribute zero.
+    // Parts of spans below span_hi that no tile wrote contribute zero (an
+    // empty mesh folds one zero part).
+    const int64_t S = st->geo.S, nspan = std::max<int64_t>(st->span_hi, 1);
+    const int64_t nparts = std::max<int64_t>(st->part_hi, 1);
     for (int64_t i = 0; i < nspan; ++i) {
         if (st->span_written[(size_t)i]) continue;
         int64_t j = i;
         while (j < nspan && !st->span_written[(size_t)j]) ++j;
-        const int64_t cnt = (j - i) * E;
+        const int64_t cnt = (std::min(j * S, nparts) - i * S) * E;
         hipLaunchKernelGGL(k_zero, dim3((unsigned)std::min<int64_t>((cnt + 255) / 256, 65535)), dim3(256), 0,
-                           hs, st->partials + i * E, cnt);
+                           hs, st->partials + i * S * E, cnt);
         LAUNCH_CHECK("zero spans");
         i = j;
     }
-    const ts3_status s = fold_partials(st, nspan, st->rowc, st->s_raw, st->dsum, hs);
+    const ts3_status s = fold_partials(st, nparts, st->rowc, st->s_raw, st->dsum, hs);
     if (s != TS3_OK) return s;
     if (st->proj)
         hipLaunchKernelGGL(k_finalize_proj, dim3(d.H), dim3(256), 0, hs, st->s_raw, st->dsum, w->b1, d.H, d.M, d.eps,
@@ -769,6 +812,13 @@ ts3_status ts3_deslice(const ts3_state *st, const ts3_weights *w, const void *x_
 
 namespace {
 
+// Points per launch over a resident mesh: as many whole tiles (or chunks) as
+// make up LAUNCH_POINTS.  Each launch ends with a partly filled last round of
+// workgroups; 16 chunks of 65,536 points (256 blocks each) take 16 rounds and 16
+// launches, one launch of 1M points the rounds alone.
+constexpr int64_t LAUNCH_POINTS = int64_t(1) << 22;
+int64_t launch_points(int64_t tile) { return tile >= LAUNCH_POINTS ? tile : LAUNCH_POINTS / tile * tile; }
+
 // The second stream starts after everything enqueued on `main` so far.
 ts3_status fork_aux(ts3_state *st, hipStream_t main, bool *forked) {
     HIP_TRY(hipEventRecord(st->ev_fork, main));
@@ -807,17 +857,20 @@ ts3_status ts3_layer_forward(ts3_state *st, const ts3_weights *w, const void *x,
     // Pass-1 tiles write disjoint group partials and pass-2 chunks disjoint
     // output rows, so each loop runs its launches alternately on the caller's
     // stream and the second one, forked from and joined back into the caller's.
+    // The mesh is resident and neither result depends on the split, so a launch
+    // takes several tiles or chunks.
+    const int64_t tstep = launch_points(tile), cstep = launch_points(chunk);
     bool forked = false;
-    if (s == TS3_OK && N > tile) s = fork_aux(st, main, &forked);
-    for (int64_t t0 = 0, i = 0; s == TS3_OK && t0 < N; t0 += tile, ++i)
-        s = ts3_slice_accumulate(st, w, xb + t0 * row, std::min(tile, N - t0), t0, (i & 1) ? st->aux : main);
+    if (s == TS3_OK && N > tstep) s = fork_aux(st, main, &forked);
+    for (int64_t t0 = 0, i = 0; s == TS3_OK && t0 < N; t0 += tstep, ++i)
+        s = ts3_slice_accumulate(st, w, xb + t0 * row, std::min(tstep, N - t0), t0, (i & 1) ? st->aux : main);
     if (forked) s = join_aux(st, main, s);
     if (s == TS3_OK) s = ts3_slice_finalize(st, w, stream);
     if (s == TS3_OK) s = ts3_token_attention(st, w, stream);
     forked = false;
-    if (s == TS3_OK && N > chunk) s = fork_aux(st, main, &forked);
-    for (int64_t c0 = 0, i = 0; s == TS3_OK && c0 < N; c0 += chunk, ++i)
-        s = ts3_deslice(st, w, xb + c0 * row, std::min(chunk, N - c0), ob + c0 * row, (i & 1) ? st->aux : main);
+    if (s == TS3_OK && N > cstep) s = fork_aux(st, main, &forked);
+    for (int64_t c0 = 0, i = 0; s == TS3_OK && c0 < N; c0 += cstep, ++i)
+        s = ts3_deslice(st, w, xb + c0 * row, std::min(cstep, N - c0), ob + c0 * row, (i & 1) ? st->aux : main);
     if (forked) s = join_aux(st, main, s);
     return s;
 }
@@ -879,11 +932,11 @@ ts3_status ts3_layer_backward(ts3_state *st, const ts3_weights *w, const void *x
     st->partials_fwd = false;  // the backward passes reuse the span partial buffer
     for (int64_t t0 = 0; t0 < N; t0 += tile) {
         const int64_t nt = std::min(tile, N - t0);
-        st->k.bw_head(xf + t0 * d.C, gf + t0 * d.C, nt, t0 / Q, (int32_t)Q, (int32_t)((nt + Q - 1) / Q), d.H, w2p,
-                      st->b2s, st->partials, hs);
+        st->k.bw_head(xf + t0 * d.C, gf + t0 * d.C, nt, t0 / Q * st->geo.S, st->geo, (int32_t)st->geo.parts(nt), d.H,
+                      w2p, st->b2s, st->partials, hs);
         LAUNCH_CHECK("backward dZ pass");
     }
-    ts3_status s = fold_partials(st, nspan_all, d.C, st->bdZ, st->bdd, hs);
+    ts3_status s = fold_partials(st, st->geo.parts(N), d.C, st->bdZ, st->bdd, hs);
     if (s != TS3_OK) return s;
     // token side: ds_raw, dd and the Linear1 / attention / Linear3 gradients
     const size_t lds = (size_t)(2 * d.M * d.C + 10 * d.M * d.dh + 2 * d.M * d.M) * 4;
@@ -900,11 +953,11 @@ ts3_status ts3_layer_backward(ts3_state *st, const ts3_weights *w, const void *x
         st->k.bw_dx(xf + t0 * d.C, gf + t0 * d.C, nt, d.H, w2p, st->b2s, w->W2, st->Z, st->bdsr, st->bdsT, st->bdd,
                     inv_tau, (float *)dx + t0 * d.C, st->bdz, hs);
         LAUNCH_CHECK("backward dx pass");
-        st->k.bw_dw2(xf + t0 * d.C, st->bdz, nt, t0 / Q, (int32_t)Q, (int32_t)((nt + Q - 1) / Q), d.H,
+        st->k.bw_dw2(xf + t0 * d.C, st->bdz, nt, t0 / Q * st->geo.S, st->geo, (int32_t)st->geo.parts(nt), d.H,
                      st->partials, hs);
         LAUNCH_CHECK("backward dW2 pass");
     }
-    s = fold_partials(st, nspan_all, d.C, st->bdW2T, gr->db2, hs);
+    s = fold_partials(st, st->geo.parts(N), d.C, st->bdW2T, gr->db2, hs);
     if (s != TS3_OK) return s;
     hipLaunchKernelGGL(k_bw_transpose_w2, dim3((unsigned)std::min<int64_t>((d.C * HM + 255) / 256, 4096)), dim3(256),
                        0, hs, st->bdW2T, d.C, (int)HM, gr->dW2);
@@ -965,8 +1018,24 @@ ts3_status ts3_state_get_spans(const ts3_state *st, int64_t span0, int64_t nspan
         if (!st->span_written[(size_t)i])
             return fail(TS3_ERR_BAD_STATE, "span %lld has not been accumulated", (long long)i);
     hipStream_t hs = (hipStream_t)stream;
-    HIP_TRY(hipMemcpyAsync(host_dst, st->partials + span0 * st->E, (size_t)n * 4, hipMemcpyDeviceToHost, hs));
-    HIP_TRY(hipStreamSynchronize(hs));
+    const int64_t S = st->geo.S, E = st->E;
+    if (S == 1) {
+        HIP_TRY(hipMemcpyAsync(host_dst, st->partials + span0 * E, (size_t)n * 4, hipMemcpyDeviceToHost, hs));
+        HIP_TRY(hipStreamSynchronize(hs));
+        return TS3_OK;
+    }
+    // a span is the sum of its parts, in order
+    const std::unique_ptr<float[]> part(new (std::nothrow) float[(size_t)(S * E)]);
+    if (!part) return fail(TS3_ERR_OUT_OF_MEMORY, "host allocation failed");
+    for (int64_t i = 0; i < nspan; ++i) {
+        const int64_t p0 = (span0 + i) * S, np = std::min<int64_t>(S, st->part_hi - p0);
+        HIP_TRY(hipMemcpyAsync(part.get(), st->partials + p0 * E, (size_t)(np * E) * 4, hipMemcpyDeviceToHost, hs));
+        HIP_TRY(hipStreamSynchronize(hs));
+        float *dst = host_dst + i * E;
+        std::memcpy(dst, part.get(), (size_t)E * 4);
+        for (int64_t p = 1; p < np; ++p)
+            for (int64_t e = 0; e < E; ++e) dst[e] += part[(size_t)(p * E + e)];
+    }
     return TS3_OK;
 }
 
@@ -1003,9 +1072,12 @@ ts3_status ts3_state_set(ts3_state *st, const ts3_weights *w, int32_t which, con
 // not a device pointer.
 namespace {
 
-constexpr size_t SCRATCH_BYTES = size_t(64) << 20;
+// A call is accepted by the bytes that scratch_layout counts (one partial per
+// span); the array holds SCRATCH_SLACK more, for the runs of a span's parts (at
+// most PART_BYTES / FOLD as doubles, and one run of the shape's partial is counted).
+constexpr size_t SCRATCH_BYTES = size_t(64) << 20, SCRATCH_SLACK = size_t(16) << 20;
 constexpr int SCRATCH_MAX_DEVICES = 64;
-static __device__ __align__(256) unsigned char scratch[SCRATCH_BYTES];
+static __device__ __align__(256) unsigned char scratch[SCRATCH_BYTES + SCRATCH_SLACK];
 
 std::once_flag g_scratch_once[SCRATCH_MAX_DEVICES];
 void *g_scratch_ptr[SCRATCH_MAX_DEVICES];
@@ -1030,9 +1102,11 @@ ts3_status scratch_base(void **out) {
 
 // Byte layout of the scratch array for one call (each region 256-aligned).
 struct ScratchLayout {
-    size_t partials, runs, s_raw, dsum, s, s1, Z, b2s, b3, w2p, zp, sfp, w3p, w1p, total;
+    size_t s_raw, dsum, s, s1, Z, b2s, b3, w2p, zp, sfp, w3p, w1p, tail, total;
 };
 
+// The bytes that a call is refused or accepted by: a tile's spans, one partial
+// each.
 ScratchLayout scratch_layout(const ts3_desc &d, int64_t N, int64_t tile) {
     auto up = [](size_t b) { return (b + 255) & ~size_t(255); };
     const int64_t HM = (int64_t)d.H * d.M;
@@ -1048,8 +1122,6 @@ ScratchLayout scratch_layout(const ts3_desc &d, int64_t N, int64_t tile) {
     ScratchLayout L{};
     size_t at = 0;
     auto take = [&](size_t &field, size_t bytes) { field = at; at += up(bytes); };
-    take(L.partials, (size_t)(tile_spans * E) * 4);
-    take(L.runs, (size_t)(nrun * E) * (d.accum == TS3_ACCUM_FP64 ? 8 : 4));
     take(L.s_raw, (size_t)(HM * d.C) * 4);
     take(L.dsum, (size_t)HM * 4);
     take(L.s, (size_t)(HM * d.dh) * 4);
@@ -1063,7 +1135,8 @@ ScratchLayout scratch_layout(const ts3_desc &d, int64_t N, int64_t tile) {
     take(L.sfp, sf ? (size_t)HM * 16 * 2 : 0);
     take(L.w3p, sf ? (size_t)d.C * d.C * 2 : 0);
     take(L.w1p, proj ? (size_t)d.C * d.C * 4 : 0);
-    L.total = at;
+    L.tail = at;
+    L.total = at + up((size_t)(tile_spans * E) * 4) + up((size_t)(nrun * E) * (d.accum == TS3_ACCUM_FP64 ? 8 : 4));
     return L;
 }
 
@@ -1107,6 +1180,14 @@ ts3_status ts3_layer_forward_noalloc(const ts3_desc *desc, const ts3_weights *w,
     s = scratch_base(&base);
     if (s != TS3_OK) return s;
     unsigned char *b = (unsigned char *)base;
+    // The parts of the spans, as a state of the same desc cuts them (max_points
+    // 0 stands for the N points of this call).
+    ts3_desc cut = d;
+    cut.max_points = std::max(d.max_points, N);
+    Kernels ck;
+    find_any_kernels(d.io_dtype, d.C, d.M, &ck);
+    const bool cproj = ck.pass1p && d.H * 16 == d.C;
+    const SpanGeo geo = span_geo(cut, ck, cproj, (int64_t)d.H * d.M * ((cproj ? 16 : d.C) + 1));
     // A state on the host stack whose device buffers are regions of the array;
     // it owns nothing and is never freed.
     ts3_state st;
@@ -1117,8 +1198,16 @@ ts3_status ts3_layer_forward_noalloc(const ts3_desc *desc, const ts3_weights *w,
     st.rowc = st.proj ? 16 : d.C;
     st.E = (int64_t)d.H * d.M * (st.rowc + 1);
     st.w1p = st.proj ? b + lay.w1p : nullptr;
-    st.partials = (float *)(b + lay.partials);
-    st.runs = (float *)(b + lay.runs);
+    const int64_t nparts = std::max<int64_t>(geo.parts(N), 1);
+    const int64_t nrun = (nparts + FOLD - 1) / FOLD;
+    const size_t run_bytes = (size_t)(nrun * st.E) * (d.accum == TS3_ACCUM_FP64 ? 8 : 4);
+    // partials and runs come last: the partials take what the runs leave
+    st.runs = (float *)(b + lay.tail);
+    const size_t part_at = (lay.tail + run_bytes + 255) & ~size_t(255);
+    const int64_t batch = part_at < sizeof(scratch) ? (int64_t)((sizeof(scratch) - part_at) / ((size_t)st.E * 4)) : 0;
+    if (batch < 1) return fail(TS3_ERR_INVALID_ARG, "no scratch is left for a partial");  // excluded by the slack
+    st.partials = (float *)(b + part_at);
+    st.geo = geo;
     st.s_raw = (float *)(b + lay.s_raw);
     st.dsum = (float *)(b + lay.dsum);
     st.s = (float *)(b + lay.s);
@@ -1135,33 +1224,32 @@ ts3_status ts3_layer_forward_noalloc(const ts3_desc *desc, const ts3_weights *w,
         st.k.pass2sf = nullptr;
     }
     hipStream_t hs = (hipStream_t)stream;
-    const int64_t Q = d.group_span;
     const int64_t E = st.E;
-    const int64_t nspan = std::max<int64_t>((N + Q - 1) / Q, 1);
-    const int64_t nrun = (nspan + FOLD - 1) / FOLD;
     s = prep_w2(&st, w, hs);
     if (s != TS3_OK) return s;
-    if (N == 0) {  // an empty mesh: the one span is zero
+    if (N == 0) {  // an empty mesh: the one part is zero
         hipLaunchKernelGGL(k_zero, dim3((unsigned)((E + 255) / 256)), dim3(256), 0, hs, st.partials, E);
-        LAUNCH_CHECK("zero span");
+        LAUNCH_CHECK("zero part");
         if (d.accum == TS3_ACCUM_FP64) fold_tile<double>(st.partials, E, 0, 1, st.runs, hs);
         else fold_tile<float>(st.partials, E, 0, 1, st.runs, hs);
         LAUNCH_CHECK("fold");
     }
-    // Pass 1 tile by tile on the caller's stream: the tile's spans go to the
-    // start of the partial region, then into their runs.
-    for (int64_t t0 = 0; t0 < N; t0 += tile) {
-        const int64_t nt = std::min(tile, N - t0);
-        const int64_t ns = (nt + Q - 1) / Q;
+    // Pass 1 on the caller's stream, as many parts at a time as the partial
+    // region holds; each batch's partials go into their runs.
+    for (int64_t p0 = 0; N > 0 && p0 < nparts; p0 += batch) {
+        const int64_t np = std::min(batch, nparts - p0);
+        // the batch starts in span p0 / S of the mesh
+        const int64_t t0 = p0 / geo.S * geo.Q;
+        SpanGeo part = geo;
+        part.first = (int32_t)(p0 % geo.S);
+        const char *xt = (const char *)x + t0 * d.C * st.esize;
         if (st.proj)
-            st.k.pass1p((const char *)x + t0 * d.C * st.esize, nt, 0, (int32_t)Q, (int32_t)ns, d.H, st.w2p, st.b2s,
-                        st.w1p, st.partials, hs);
+            st.k.pass1p(xt, N - t0, 0, part, (int32_t)np, d.H, st.w2p, st.b2s, st.w1p, st.partials, hs);
         else
-            st.k.pass1((const char *)x + t0 * d.C * st.esize, nt, 0, (int32_t)Q, (int32_t)ns, d.H, d.C, d.M,
-                       st.w2p, st.b2s, st.partials, hs);
+            st.k.pass1(xt, N - t0, 0, part, (int32_t)np, d.H, d.C, d.M, st.w2p, st.b2s, st.partials, hs);
         LAUNCH_CHECK("slice_accumulate");
-        if (d.accum == TS3_ACCUM_FP64) fold_tile<double>(st.partials, E, t0 / Q, ns, st.runs, hs);
-        else fold_tile<float>(st.partials, E, t0 / Q, ns, st.runs, hs);
+        if (d.accum == TS3_ACCUM_FP64) fold_tile<double>(st.partials, E, p0, np, st.runs, hs);
+        else fold_tile<float>(st.partials, E, p0, np, st.runs, hs);
         LAUNCH_CHECK("fold");
     }
     const unsigned gx = (unsigned)((E + 255) / 256);
@@ -1182,8 +1270,9 @@ ts3_status ts3_layer_forward_noalloc(const ts3_desc *desc, const ts3_weights *w,
     st.phase = PH_FINAL;
     s = ts3_token_attention(&st, w, stream);
     if (s != TS3_OK) return s;
-    for (int64_t c0 = 0; s == TS3_OK && c0 < N; c0 += chunk)
-        s = ts3_deslice(&st, w, (const char *)x + c0 * d.C * st.esize, std::min(chunk, N - c0),
+    const int64_t cstep = launch_points(chunk);
+    for (int64_t c0 = 0; s == TS3_OK && c0 < N; c0 += cstep)
+        s = ts3_deslice(&st, w, (const char *)x + c0 * d.C * st.esize, std::min(cstep, N - c0),
                         (char *)out + c0 * d.C * st.esize, stream);
     return s;
 }

@@ -193,7 +193,7 @@ constexpr int BW_HEAD_LD = BW_HEAD_PTS + 8;  // floats per transposed LDS row (b
 
 template <int C, int M>
 __global__ __launch_bounds__(512, 1) void k_bw_head(const float *__restrict__ x, const float *__restrict__ gout,
-                                                    int64_t n_tile, int64_t span0, int32_t Q, int32_t nspan,
+                                                    int64_t n_tile, int64_t span0, SpanGeo geo, int32_t nspan,
                                                     int32_t H, const float *__restrict__ w2p,
                                                     const float *__restrict__ b2s, float *__restrict__ partials) {
     constexpr int MT = M / 16, CT = C / 16, NK = BW_HEAD_PTS / 32, LD = BW_HEAD_LD;
@@ -209,8 +209,8 @@ __global__ __launch_bounds__(512, 1) void k_bw_head(const float *__restrict__ x,
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15, g = lane >> 4;
-    const int64_t p_begin = (int64_t)span_local * Q;
-    const int64_t p_end = p_begin + Q < n_tile ? p_begin + Q : n_tile;
+    const int64_t p_begin = geo.begin(span_local);
+    const int64_t p_end = geo.end(span_local, n_tile);
     const int nblk = (int)((p_end - p_begin + BW_HEAD_PTS - 1) / BW_HEAD_PTS);
     const bool has_ct = wave < CT;
     const int dmt = wave - 4;  // this wave's column-sum tile, if 0 <= dmt < MT
@@ -413,7 +413,7 @@ template <int C, int M> struct BwDw2Cfg {
 
 template <int C, int M>
 __global__ __launch_bounds__(512, 1) void k_bw_dw2(const float *__restrict__ x, const float *__restrict__ dzs,
-                                                   int64_t n_tile, int64_t span0, int32_t Q, int32_t nspan,
+                                                   int64_t n_tile, int64_t span0, SpanGeo geo, int32_t nspan,
                                                    int32_t H, float *__restrict__ partials) {
     using Cfg = BwDw2Cfg<C, M>;
     constexpr int MT = M / 16, CT = C / 16, NK = BW_DW2_PTS / 32, LD = BW_DW2_LD;
@@ -424,8 +424,8 @@ __global__ __launch_bounds__(512, 1) void k_bw_dw2(const float *__restrict__ x, 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15, g = lane >> 4;
-    const int64_t p_begin = (int64_t)span_local * Q;
-    const int64_t p_end = p_begin + Q < n_tile ? p_begin + Q : n_tile;
+    const int64_t p_begin = geo.begin(span_local);
+    const int64_t p_end = geo.end(span_local, n_tile);
     const int nblk = (int)((p_end - p_begin + BW_DW2_PTS - 1) / BW_DW2_PTS);
     const float *dzh = dzs + (size_t)h * n_tile * M;
     const bool has_ct = wave < CT;

@@ -225,6 +225,28 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
 }
 
+// Sub-spans: a span of Q points is summed in S consecutive parts of L points (a
+// multiple of the block size; the last part is shorter), each to its own
+// partial, so that a mesh of few spans still fills the chip.  Of a tile that
+// starts on a span boundary, a launch's part i covers points [begin(i), end(i));
+// `first` is the tile's part that the launch starts with.
+struct SpanGeo {
+    int32_t Q, L, S, first;
+    __host__ __device__ __forceinline__ int64_t begin(int i) const {
+        i += first;
+        return (int64_t)(i / S) * Q + (int64_t)(i % S) * L;
+    }
+    __host__ __device__ __forceinline__ int64_t end(int i, int64_t n) const {
+        const int64_t s = (int64_t)((i + first) / S) * Q + Q, e = begin(i) + L;
+        const int64_t m = e < s ? e : s;
+        return m < n ? m : n;
+    }
+    // Parts that hold the first n points of a mesh (or of a tile).
+    __host__ __device__ __forceinline__ int64_t parts(int64_t n) const {
+        return n / Q * S + (n % Q + L - 1) / L;
+    }
+};
+
 // XCD-aware block index: consecutive logical indices land on the same XCD
 // (workgroups are dispatched round-robin over the 8 XCDs of an MI355X).
 __device__ __forceinline__ int xcd_remap(int i, int n) {

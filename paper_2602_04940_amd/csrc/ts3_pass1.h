@@ -137,7 +137,7 @@ template <int V> using ic = std::integral_constant<int, V>;
 // partials: [span][H][M][C+1] float32
 template <typename T, int C, int M>
 __global__ __launch_bounds__(256, 1) void k_slice_accumulate(
-    const T *__restrict__ x, int64_t n_tile, int64_t span0, int32_t Q, int32_t nspan, int32_t H,
+    const T *__restrict__ x, int64_t n_tile, int64_t span0, SpanGeo geo, int32_t nspan, int32_t H,
     const T *__restrict__ w2p, const float *__restrict__ b2s, float *__restrict__ partials) {
     using Cfg = Pass1Cfg<T, C, M>;
     constexpr int CT = Cfg::CT, MT = Cfg::MT, CK = Cfg::CK;
@@ -154,8 +154,8 @@ __global__ __launch_bounds__(256, 1) void k_slice_accumulate(
     const int li = lane & 15;
     const int g = lane >> 4;
 
-    const int64_t p_begin = (int64_t)span_local * Q;
-    const int64_t p_end = p_begin + Q < n_tile ? p_begin + Q : n_tile;
+    const int64_t p_begin = geo.begin(span_local);
+    const int64_t p_end = geo.end(span_local, n_tile);
     const int nblk = (int)((p_end - p_begin + 31) >> 5);
     const int nmine = nblk > wave ? (nblk - wave + Cfg::WAVES - 1) / Cfg::WAVES : 0;
 

@@ -93,7 +93,7 @@ __global__ void k_prep_w1(const float *__restrict__ W1, int C, int H, bf16_t *__
 // [span][H][M][17] (t then d).  Grid nspan * H / 2, PCP_THREADS threads.
 template <int C, int M>
 __global__ __launch_bounds__(PCP_THREADS, 1) void k_slice_accumulate_pcp(
-    const bf16_t *__restrict__ x, int64_t n_tile, int64_t span0, int32_t Q, int32_t nspan, int32_t H,
+    const bf16_t *__restrict__ x, int64_t n_tile, int64_t span0, SpanGeo geo, int32_t nspan, int32_t H,
     const bf16_t *__restrict__ w2p, const float *__restrict__ b2s, const bf16_t *__restrict__ w1p,
     float *__restrict__ partials) {
     using Cfg = Pass1PCPCfg<C, M>;
@@ -116,8 +116,8 @@ __global__ __launch_bounds__(PCP_THREADS, 1) void k_slice_accumulate_pcp(
     const int h = 2 * hp + hsel;
     const int li = lane & 15, g = lane >> 4;
 
-    const int64_t p_begin = (int64_t)span_local * Q;
-    const int64_t p_end = p_begin + Q < n_tile ? p_begin + Q : n_tile;
+    const int64_t p_begin = geo.begin(span_local);
+    const int64_t p_end = geo.end(span_local, n_tile);
     const int nrows = (int)(p_end - p_begin);  // <= Q <= 2^30
     const int nblk = (nrows + 31) >> 5;
     const int nit = (nblk + NST - 1) / NST;  // block steps, the same for every wave

@@ -54,7 +54,7 @@ template <int C, int M> struct Pass1PCWCfg {
 // Arguments as k_slice_accumulate (H even); grid nspan * H / 2, 512 threads.
 template <int C, int M>
 __global__ __launch_bounds__(512, 1) void k_slice_accumulate_pcw(
-    const bf16_t *__restrict__ x, int64_t n_tile, int64_t span0, int32_t Q, int32_t nspan, int32_t H,
+    const bf16_t *__restrict__ x, int64_t n_tile, int64_t span0, SpanGeo geo, int32_t nspan, int32_t H,
     const bf16_t *__restrict__ w2p, const float *__restrict__ b2s, float *__restrict__ partials) {
     using Cfg = Pass1PCWCfg<C, M>;
     using T = bf16_t;
@@ -75,8 +75,8 @@ __global__ __launch_bounds__(512, 1) void k_slice_accumulate_pcw(
     const int h = 2 * hp + hsel;
     const int li = lane & 15, g = lane >> 4;
 
-    const int64_t p_begin = (int64_t)span_local * Q;
-    const int64_t p_end = p_begin + Q < n_tile ? p_begin + Q : n_tile;
+    const int64_t p_begin = geo.begin(span_local);
+    const int64_t p_end = geo.end(span_local, n_tile);
     const int nrows = (int)(p_end - p_begin);  // <= Q <= 2^30
     const int nit = (nrows + 31) >> 5;        // blocks, the same for every wave
 

@@ -90,7 +90,7 @@ __device__ void rt_weights(const float *xs, float *ws, int np, int h, int C, int
 // RT_PTS * (C + M) floats.  Each sum runs over the span's points in order.
 template <typename T>
 __global__ __launch_bounds__(256) void k_slice_accumulate_rt(const T *__restrict__ x, int64_t n_tile, int64_t span0,
-                                                             int32_t Q, int32_t H, int C, int M,
+                                                             SpanGeo geo, int32_t H, int C, int M,
                                                              const T *__restrict__ w2r, const float *__restrict__ b2s,
                                                              float *__restrict__ partials) {
     extern __shared__ float sm[];
@@ -102,8 +102,8 @@ __global__ __launch_bounds__(256) void k_slice_accumulate_rt(const T *__restrict
     bid /= nchunk;
     const int h = bid % H, span_local = bid / H;
     const int tid = threadIdx.x;
-    const int64_t p_begin = (int64_t)span_local * Q;
-    const int64_t p_end = p_begin + Q < n_tile ? p_begin + Q : n_tile;
+    const int64_t p_begin = geo.begin(span_local);
+    const int64_t p_end = geo.end(span_local, n_tile);
     const int c0 = chunk * 64, cw = C - c0 < 64 ? C - c0 : 64;
     const int ne = M * cw;  // accumulated elements (m, c) of this workgroup, <= 64 per thread
     float acc[64];

@@ -1,0 +1,83 @@
+"""Spans cut into parts (a mesh of few spans): every pass-1 kernel against the
+oracle, and the guarantees that must not depend on the cut.
+
+9,001 points in spans of 4,096 give parts of 64 to 192 points, the last span
+and its last part ragged.  A part's sum and the fold are float32 sums as before, so
+the bars are those of the other parity tests.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_helpers import (assert_bf16_close, assert_state_close, banner, match_sums, normwise, state_of, sums_key,
+                         to_device, to_host)
+from ts3_synth import make_weights, round_bf16
+
+pytestmark = pytest.mark.gpu
+
+N, Q = 9_001, 4_096
+SHAPES = [(128, 8, 64, "bf16"),   # projected sums, three block streams
+          (128, 2, 64, "bf16"),   # two heads per workgroup, raw sums
+          (256, 8, 64, "bf16"),   # wide rows
+          (64, 4, 16, "bf16"),    # one head per workgroup
+          (128, 8, 64, "fp32"),
+          (48, 1, 80, "fp32")]    # runtime shape
+
+
+@pytest.mark.parametrize("C,H,M,dtype", SHAPES)
+def test_parts_match_the_oracle_and_do_not_depend_on_the_tiling(C, H, M, dtype):
+    import torch
+    from paper_2602_04940_amd import LayerWeights, PhysicsAttention
+    from paper_2602_04940_amd.layer import layer_forward_noalloc
+    banner(f"parts: C={C} H={H} M={M} {dtype}, {N} points in spans of {Q}")
+    x64 = np.random.default_rng(8).standard_normal((N, C))
+    x64 = round_bf16(x64) if dtype == "bf16" else x64.astype(np.float32).astype(np.float64)
+    W = make_weights(C, H, M, C // H, seed=3, bias_seed=4)
+    lw = LayerWeights(W)
+    x = to_device(x64, dtype)
+    ref = oracle.build_state(x64, W, H, M, 2.0)
+    ref_out = oracle.deslice(x64, W["W2"], W["b2"], ref["Z"], W["b3"], H, M, 2.0)
+    with PhysicsAttention(C, H, M, C // H, 0.5, dtype, group_span=Q, max_points=N) as layer:
+        out = layer.forward(lw, x, tile=2 * Q, chunk=1000).clone()
+        st = state_of(layer)
+        spans = layer.get_spans(0, 3)
+        # tile by tile, last tile first
+        layer.reset()
+        for t0 in (2 * Q, Q, 0):
+            layer.accumulate(lw, x[t0:t0 + Q], t0)
+        layer.finalize(lw)
+        layer.attention(lw)
+        assert torch.equal(layer.deslice(lw, x), out)
+        # a mesh whose first span never arrives: its parts count as zero
+        layer.reset()
+        layer.accumulate(lw, x[Q:2 * Q], Q)
+        layer.accumulate(lw, x[2 * Q:], 2 * Q)
+        layer.finalize(lw)
+        layer.attention(lw)
+        late = state_of(layer)
+        # fewer points than max_points
+        few = layer.forward(lw, x[:Q + 77].contiguous(), tile=Q, chunk=4096).clone()
+    noalloc = torch.empty_like(x)
+    layer_forward_noalloc(C, H, M, lw, x, Q, 4096, noalloc, dtype=dtype, group_span=Q)
+    torch.cuda.synchronize()
+    assert torch.equal(noalloc, out)
+
+    late_ref = match_sums(late, oracle.build_state(x64[Q:], W, H, M, 2.0), x64[Q:], W, H, M, 2.0)
+    few_ref = oracle.layer_forward_fast(x64[:Q + 77], W, H, M, 2.0)
+    match_sums(st, ref, x64, W, H, M, 2.0)
+    key = sums_key(st)
+    if dtype == "bf16":
+        assert_bf16_close(to_host(out), ref_out, "out")
+        assert_state_close(st, ref, "state")
+        assert_state_close(late, late_ref, "state without the first span")
+        assert_bf16_close(to_host(few), few_ref, "out of fewer points")
+    else:
+        for what, got, want in (("out", to_host(out), ref_out), (key, st[key], ref[key]), ("d", st["d"], ref["d"]),
+                                ("late sums", late[key], late_ref[key]), ("few", to_host(few), few_ref)):
+            e = normwise(got, want)
+            print(f"{what}: normwise {e:.2e}", flush=True)
+            assert e <= 1e-4, (what, e)
+    # the spans that get_spans reports add up to the state (float32 sums of three terms)
+    total = spans.astype(np.float64).sum(axis=0)
+    assert np.abs(total[..., :-1] - st[key]).max() <= 1e-5 * np.abs(st[key]).max()
+    assert np.abs(total[..., -1] - st["d"]).max() <= 1e-5 * st["d"].max()
