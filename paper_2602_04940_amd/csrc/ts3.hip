@@ -24,6 +24,7 @@
 #include "ts3_backward.h"
 #include "ts3_pass2.h"
 #include "ts3_small.h"
+#include "ts3_token.h"
 #include "ts3_rt.h"
 #include "ts3_pass2sf.h"
 
@@ -449,6 +450,8 @@ ts3_status prep_w2(ts3_state *st, const ts3_weights *w, hipStream_t stream) {
     const int64_t total = w2p_elems(d);
     const int grid = (int)std::min<int64_t>((total + 255) / 256, 4096);
     const int grid2 = std::max(grid, (d.H * d.M + 255) / 256);
+    const float *W1 = st->proj ? w->W1 : nullptr;  // the W1 fragments of the projected pass 1
+    bf16_t *w1p = W1 ? (bf16_t *)st->w1p : nullptr;
     if (st->k.rt && d.io_dtype == TS3_BF16)
         hipLaunchKernelGGL(k_prep_w2_rt<bf16_t>, dim3(grid2), dim3(256), 0, stream, w->W2, w->b2, scale, d.C, d.H,
                            d.M, (bf16_t *)st->w2p, st->b2s);
@@ -457,18 +460,12 @@ ts3_status prep_w2(ts3_state *st, const ts3_weights *w, hipStream_t stream) {
                            d.M, (float *)st->w2p, st->b2s);
     else if (d.io_dtype == TS3_BF16)
         hipLaunchKernelGGL(k_prep_w2<bf16_t>, dim3(grid2), dim3(256), 0, stream, w->W2, w->b2, scale, d.C,
-                           d.H, d.M, (bf16_t *)st->w2p, st->b2s);
+                           d.H, d.M, (bf16_t *)st->w2p, st->b2s, W1, w1p);
     else
         hipLaunchKernelGGL(k_prep_w2<float>, dim3(grid2), dim3(256), 0, stream, w->W2, w->b2, scale, d.C,
-                           d.H, d.M, (float *)st->w2p, st->b2s);
+                           d.H, d.M, (float *)st->w2p, st->b2s, W1, w1p);
     LAUNCH_CHECK("prep_w2");
-    if (st->proj && w->W1) {  // the W1 fragments of the projected pass 1
-        const int64_t nw1 = (int64_t)d.C * d.C;
-        hipLaunchKernelGGL(k_prep_w1, dim3((unsigned)std::min<int64_t>((nw1 + 255) / 256, 1024)), dim3(256), 0,
-                           stream, w->W1, d.C, d.H, (bf16_t *)st->w1p);
-        LAUNCH_CHECK("prep_w1");
-        st->W1 = w->W1;
-    }
+    if (W1) st->W1 = W1;
     st->W2 = w->W2;
     st->b2 = w->b2;
     st->w2_ready = true;
@@ -690,6 +687,39 @@ namespace {
 
 // Ordered fold of the first nspan part sums into main [H*M*C] and the
 // column C entries into col [H*M] (the forward's fold kernels).
+template <typename TS, typename TA>
+void launch_tokens(ts3_state *st, const TS *src, int64_t count, const ts3_weights *w, hipStream_t hs) {
+    const ts3_desc &d = st->desc;
+    hipLaunchKernelGGL((k_slice_tokens<TS, TA>), dim3((unsigned)(d.H * d.M / TOK_ROWS)), dim3(256), 0, hs, src, st->E,
+                       count, st->rowc, st->proj, w->W1, w->b1, d.H, d.M, d.dh, d.eps, st->s_raw, st->dsum, st->s);
+}
+
+// s_raw, d and the slice tokens from the folded runs of part sums.
+ts3_status tokens_from_runs(ts3_state *st, int64_t nrun, const ts3_weights *w, hipStream_t hs) {
+    if (st->desc.accum == TS3_ACCUM_FP64)
+        launch_tokens<double, double>(st, (const double *)(void *)st->runs, nrun, w, hs);
+    else
+        launch_tokens<float, float>(st, st->runs, nrun, w, hs);
+    LAUNCH_CHECK("slice tokens");
+    return TS3_OK;
+}
+
+// The same from the first nparts part sums.  Up to FOLD parts make up one run,
+// which the tokens kernel sums itself (the same order, so the same bits as
+// through a run).
+template <typename T> ts3_status tokens_from_parts(ts3_state *st, int64_t nparts, const ts3_weights *w, hipStream_t hs) {
+    if (nparts <= FOLD) {
+        launch_tokens<float, T>(st, st->partials, nparts, w, hs);
+        LAUNCH_CHECK("slice tokens");
+        return TS3_OK;
+    }
+    const int64_t nrun = (nparts + FOLD - 1) / FOLD;
+    hipLaunchKernelGGL(k_fold_runs<T>, dim3((unsigned)((st->E + 255) / 256), (unsigned)nrun), dim3(256), 0, hs,
+                       st->partials, st->E, nparts, (T *)(void *)st->runs);
+    LAUNCH_CHECK("fold_runs");
+    return tokens_from_runs(st, nrun, w, hs);
+}
+
 template <typename T>
 ts3_status fold_partials_t(ts3_state *st, int64_t nspan, int rowc, float *main, float *col, hipStream_t hs) {
     const int64_t E = (int64_t)st->desc.H * st->desc.M * (rowc + 1);
@@ -707,6 +737,25 @@ ts3_status fold_partials_t(ts3_state *st, int64_t nspan, int rowc, float *main, 
 ts3_status fold_partials(ts3_state *st, int64_t nspan, int rowc, float *main, float *col, hipStream_t hs) {
     return st->desc.accum == TS3_ACCUM_FP64 ? fold_partials_t<double>(st, nspan, rowc, main, col, hs)
                                             : fold_partials_t<float>(st, nspan, rowc, main, col, hs);
+}
+
+}  // namespace
+
+namespace {
+
+template <typename T> ts3_status launch_attend(ts3_state *st, const ts3_weights *w, bool sf, hipStream_t hs) {
+    const ts3_desc &d = st->desc;
+    const size_t lds = attend_lds_bytes(d.M, d.dh);
+    if (lds > 64 * 1024)
+        HIP_TRY(hipFuncSetAttribute((const void *)k_attend<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    ATTN_LDS_MAX));
+    const AttendOut<T> out{st->s1, st->Z, st->b3, (T *)st->zp, st->k.rt, sf ? (bf16_t *)st->sfp : nullptr,
+                           sf ? (bf16_t *)st->w3p : nullptr};
+    const int extra = sf ? 16 : 1;
+    hipLaunchKernelGGL(k_attend<T>, dim3((unsigned)(d.H * (d.M / ATT_ROWS) + extra)), dim3(256), lds, hs, st->s, w->Wq,
+                       w->Wk, w->Wv, w->W3, w->b3, d.C, d.H, d.M, d.dh, extra, out);
+    LAUNCH_CHECK("attention");
+    return TS3_OK;
 }
 
 }  // namespace
@@ -735,15 +784,9 @@ ts3_status ts3_slice_finalize(ts3_state *st, const ts3_weights *w, void *stream)
         LAUNCH_CHECK("zero spans");
         i = j;
     }
-    const ts3_status s = fold_partials(st, nparts, st->rowc, st->s_raw, st->dsum, hs);
+    const ts3_status s = d.accum == TS3_ACCUM_FP64 ? tokens_from_parts<double>(st, nparts, w, hs)
+                                                   : tokens_from_parts<float>(st, nparts, w, hs);
     if (s != TS3_OK) return s;
-    if (st->proj)
-        hipLaunchKernelGGL(k_finalize_proj, dim3(d.H), dim3(256), 0, hs, st->s_raw, st->dsum, w->b1, d.H, d.M, d.eps,
-                           st->s);
-    else
-        hipLaunchKernelGGL(k_finalize, dim3(d.H * d.M), dim3(64), 0, hs, st->s_raw, st->dsum, w->W1, w->b1, d.C,
-                           d.H, d.M, d.dh, d.eps, st->s);
-    LAUNCH_CHECK("finalize");
     st->phase = PH_FINAL;
     return TS3_OK;
 }
@@ -755,33 +798,10 @@ ts3_status ts3_token_attention(ts3_state *st, const ts3_weights *w, void *stream
     if (st->phase != PH_FINAL) return fail(TS3_ERR_BAD_STATE, "token_attention needs a finalized state");
     const ts3_desc &d = st->desc;
     hipStream_t hs = (hipStream_t)stream;
-    const size_t lds = (size_t)(5 * d.M * d.dh + d.M * d.M) * 4;
-    if (lds > 64 * 1024)
-        HIP_TRY(hipFuncSetAttribute((const void *)k_attention, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    ATTN_LDS_MAX));
-    // Z's columns in blocks of 64 over as many workgroups per head
-    const int zb = d.C % 64 == 0 ? d.C / 64 : 1;
-    hipLaunchKernelGGL(k_attention, dim3(d.H, zb), dim3(256), lds, hs, st->s, w->Wq, w->Wk, w->Wv, w->W3, d.C, d.H,
-                       d.M, d.dh, st->s1, st->Z);
-    LAUNCH_CHECK("attention");
-    if (w->b3)
-        HIP_TRY(hipMemcpyAsync(st->b3, w->b3, (size_t)d.C * 4, hipMemcpyDeviceToDevice, hs));
-    else
-        hipLaunchKernelGGL(k_zero, dim3(1), dim3(256), 0, hs, st->b3, (int64_t)d.C);
-    LAUNCH_CHECK("b3");
-    ts3_status s = prep_z(st, hs);  // folds b3 into the prepared Z
+    const bool sf = st->k.pass2sf && st->sfp && st->w3p;  // operands of the slice-state pass 2
+    const ts3_status s = d.io_dtype == TS3_BF16 ? launch_attend<bf16_t>(st, w, sf, hs) : launch_attend<float>(st, w, sf, hs);
     if (s != TS3_OK) return s;
-    st->sf_ready = false;
-    if (st->k.pass2sf && st->sfp && st->w3p) {
-        // operands of the slice-state pass 2: s'^T and W3^T fragments
-        const int64_t nsf = (int64_t)d.H * d.M * 16, nw3 = (int64_t)d.C * d.C;
-        hipLaunchKernelGGL(k_prep_sf<bf16_t>, dim3((unsigned)std::min<int64_t>((nsf + 255) / 256, 1024)), dim3(256),
-                           0, hs, st->s1, d.H, d.M, (bf16_t *)st->sfp);
-        hipLaunchKernelGGL(k_prep_w3f<bf16_t>, dim3((unsigned)std::min<int64_t>((nw3 + 255) / 256, 1024)),
-                           dim3(256), 0, hs, w->W3, d.C, (bf16_t *)st->w3p);
-        LAUNCH_CHECK("prep_sf");
-        st->sf_ready = true;
-    }
+    st->sf_ready = sf;
     st->phase = PH_ATTEND;
     return TS3_OK;
 }
@@ -1252,21 +1272,8 @@ ts3_status ts3_layer_forward_noalloc(const ts3_desc *desc, const ts3_weights *w,
         else fold_tile<float>(st.partials, E, p0, np, st.runs, hs);
         LAUNCH_CHECK("fold");
     }
-    const unsigned gx = (unsigned)((E + 255) / 256);
-    if (d.accum == TS3_ACCUM_FP64)
-        hipLaunchKernelGGL(k_fold_final<double>, dim3(gx), dim3(256), 0, hs, (const double *)st.runs, E, nrun,
-                           st.rowc, st.s_raw, st.dsum);
-    else
-        hipLaunchKernelGGL(k_fold_final<float>, dim3(gx), dim3(256), 0, hs, (const float *)st.runs, E, nrun,
-                           st.rowc, st.s_raw, st.dsum);
-    LAUNCH_CHECK("fold_final");
-    if (st.proj)
-        hipLaunchKernelGGL(k_finalize_proj, dim3(d.H), dim3(256), 0, hs, st.s_raw, st.dsum, w->b1, d.H, d.M, d.eps,
-                           st.s);
-    else
-        hipLaunchKernelGGL(k_finalize, dim3(d.H * d.M), dim3(64), 0, hs, st.s_raw, st.dsum, w->W1, w->b1, d.C, d.H,
-                           d.M, d.dh, d.eps, st.s);
-    LAUNCH_CHECK("finalize");
+    s = tokens_from_runs(&st, nrun, w, hs);
+    if (s != TS3_OK) return s;
     st.phase = PH_FINAL;
     s = ts3_token_attention(&st, w, stream);
     if (s != TS3_OK) return s;

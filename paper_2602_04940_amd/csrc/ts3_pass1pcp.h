@@ -70,25 +70,6 @@ template <int C, int M> struct Pass1PCPCfg {
     static_assert(CK == 4 && CT == 8 && MT <= 4, "the address sets are written for C = 128, M <= 64");
 };
 
-// W1 in the consumer's B-operand order, as two bfloat16 parts whose sum is
-// W1 to about 2^-17 relative: w1p[0][H][CK][64][8] the rounded values,
-// w1p[1][...] the rounded remainders.  Lane l, slot t holds
-// W1[32*kc + 8*(l>>4) + t][h*16 + (l&15)] (head width 16).
-__global__ void k_prep_w1(const float *__restrict__ W1, int C, int H, bf16_t *__restrict__ w1p) {
-    const int CK = C / 32;
-    const int64_t total = (int64_t)H * CK * 64 * 8;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int t = (int)(i & 7), lane = (int)((i >> 3) & 63);
-        const int64_t r = i >> 9;
-        const int kc = (int)(r % CK), h = (int)(r / CK);
-        const float w = W1[(int64_t)(kc * 32 + (lane >> 4) * 8 + t) * C + h * 16 + (lane & 15)];
-        const __bf16 hi = (__bf16)w;
-        reinterpret_cast<__bf16 *>(w1p)[i] = hi;
-        reinterpret_cast<__bf16 *>(w1p)[total + i] = (__bf16)(w - (float)hi);
-    }
-}
-
 // Arguments as k_slice_accumulate (H = C / 16, even) plus w1p; partials are
 // [span][H][M][17] (t then d).  Grid nspan * H / 2, PCP_THREADS threads.
 template <int C, int M>

@@ -65,38 +65,12 @@ template <int C, int M> struct Pass2SFCfg {
     static_assert(LDS_BYTES <= 160 * 1024, "resident operands exceed LDS");
 };
 
-// s'^T in u-product operand order [H][KM][64][8]: lane l, slot t holds
-// s'[h][32*km + 16*(t>>2) + 4*(l>>4) + (t&3)][l & 15] (dh = 16).
-template <typename T>
-__global__ void k_prep_sf(const float *__restrict__ s1, int H, int M, T *__restrict__ sf) {
-    const int KM = M / 32;
-    const int64_t total = (int64_t)H * KM * 64 * 8;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int t = (int)(i & 7), lane = (int)((i >> 3) & 63);
-        const int64_t r = i >> 9;
-        const int km = (int)(r % KM), h = (int)(r / KM);
-        const int m = km * 32 + (t >> 2) * 16 + (lane >> 4) * 4 + (t & 3);
-        store_elem(sf + i, s1[((int64_t)h * M + m) * 16 + (lane & 15)]);
-    }
-}
-
-// W3^T in out-product operand order [CK][CT][64][8]: lane l, slot t of K step
-// kk holds W3[16*(2kk + (t>>2)) + 4*(l>>4) + (t&3)][zchan(ct, l & 15)], the
-// row of head 2kk + (t>>2), head dimension 4*(l>>4) + (t&3) (dh = 16).
-template <typename T>
-__global__ void k_prep_w3f(const float *__restrict__ W3, int C, T *__restrict__ w3f) {
-    const int CT = C / 16, CK = C / 32;
-    const int64_t total = (int64_t)CK * CT * 64 * 8;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int t = (int)(i & 7), lane = (int)((i >> 3) & 63);
-        const int64_t r = i >> 9;
-        const int ct = (int)(r % CT), kk = (int)(r / CT);
-        const int k = 16 * (2 * kk + (t >> 2)) + 4 * (lane >> 4) + (t & 3);
-        store_elem(w3f + i, W3[(int64_t)k * C + zchan(ct, lane & 15)]);
-    }
-}
+// Operands, written by k_attend:
+//   sf  [H][KM][64][8]: lane l, slot t holds
+//       s'[h][32*km + 16*(t>>2) + 4*(l>>4) + (t&3)][l & 15] (dh = 16)
+//   w3f [CK][CT][64][8]: lane l, slot t of K step kk holds
+//       W3[16*(2kk + (t>>2)) + 4*(l>>4) + (t&3)][zchan(ct, l & 15)], the row of
+//       head 2kk + (t>>2), head dimension 4*(l>>4) + (t&3)
 
 // One 16-point tile from global-memory operands with the max-shifted softmax
 // (the fallback for blocks whose exp2 sums left the window).

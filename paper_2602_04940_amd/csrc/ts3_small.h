@@ -1,7 +1,5 @@
-// Small kernels of the layer: operand preparation, the ordered fold of span
-// partials, and the slice-domain work (Linear1, per-head token attention,
-// Linear3) that the paper moves off the points (Eq. (3), Table 2).  These touch
-// O(H*M*C) data and run in microseconds.
+// Small kernels of the layer: operand preparation and the ordered fold of span
+// partials.  These touch O(H*M*C) data and run in microseconds.
 #pragma once
 #include "ts3_device.h"
 
@@ -14,10 +12,15 @@ __device__ __forceinline__ void store_elem(bf16_t *p, float v) {
 
 // W2' = W2 * scale in MFMA fragment order [H][MT][CK][64][8]: lane l, slot t
 // holds W2'[32*kc + 8*(l>>4) + t][h*M + 16*mt + (l&15)].  b2s = b2 * scale.
-// scale = log2(e) / tau, so the softmax can use exp2.
+// scale = log2(e) / tau, so the softmax can use exp2.  With w1p, also W1 in the
+// projected pass 1's operand order (head width 16), as two bfloat16 parts whose
+// sum is W1 to about 2^-17 relative: w1p[0][H][CK][64][8] the rounded values,
+// w1p[1][...] the rounded remainders; lane l, slot t holds
+// W1[32*kc + 8*(l>>4) + t][h*16 + (l&15)].
 template <typename T>
 __global__ void k_prep_w2(const float *__restrict__ W2, const float *__restrict__ b2, float scale,
-                          int C, int H, int M, T *__restrict__ w2p, float *__restrict__ b2s) {
+                          int C, int H, int M, T *__restrict__ w2p, float *__restrict__ b2s,
+                          const float *__restrict__ W1, bf16_t *__restrict__ w1p) {
     const int MT = M / 16, CK = C / 32, HM = H * M;
     const int64_t total = (int64_t)H * MT * CK * 64 * 8;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total;
@@ -33,6 +36,16 @@ __global__ void k_prep_w2(const float *__restrict__ W2, const float *__restrict_
     }
     const int64_t tid = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (tid < HM) b2s[tid] = (b2 ? b2[tid] : 0.f) * scale;
+    const int64_t n1 = w1p ? (int64_t)H * CK * 512 : 0;
+    for (int64_t i = tid; i < n1; i += (int64_t)gridDim.x * blockDim.x) {
+        const int t = (int)(i & 7), lane = (int)((i >> 3) & 63);
+        const int64_t r = i >> 9;
+        const int kc = (int)(r % CK), h = (int)(r / CK);
+        const float w = W1[(int64_t)(kc * 32 + (lane >> 4) * 8 + t) * C + h * 16 + (lane & 15)];
+        const __bf16 hi = (__bf16)w;
+        reinterpret_cast<__bf16 *>(w1p)[i] = hi;
+        reinterpret_cast<__bf16 *>(w1p)[n1 + i] = (__bf16)(w - (float)hi);
+    }
 }
 
 // Z in decoding-operand order [H][CT][KM][64][8]: lane l, slot t holds
@@ -115,117 +128,6 @@ __global__ void k_fold_final(const T *__restrict__ runs, int64_t E, int64_t nrun
         s_raw[hm * C + c] = (float)acc;
     else
         dsum[hm] = (float)acc;
-}
-
-// s[h][m][j] = (d^-1 s_raw)[h][m][:] . W1[:, h*dh + j] + b1[h*dh + j]; one
-// workgroup of one wave per slice token (grid H*M), a lane per output column.
-// The mean is taken before Linear1 (the physical state of Appendix A.4); an
-// empty slice (d + eps <= 0) has mean zero.  The mean is formed where it is
-// used (s_raw rows stay in L2), so no shape needs LDS.  Each output is one
-// sequential sum over c, so the launch shape does not change its rounding.
-__global__ void k_finalize(const float *__restrict__ s_raw, const float *__restrict__ dsum,
-                           const float *__restrict__ W1, const float *__restrict__ b1, int C, int H,
-                           int M, int dh, float eps, float *__restrict__ s) {
-    const int hm = blockIdx.x;  // h * M + m
-    const int h = hm / M;
-    const int HD = H * dh;
-    const float den = dsum[hm] + eps;
-    const float *row = s_raw + (int64_t)hm * C;
-    for (int jj = threadIdx.x; jj < dh; jj += blockDim.x) {
-        const int col = h * dh + jj;
-        float acc = b1 ? b1[col] : 0.f;
-#pragma unroll 8
-        for (int c = 0; c < C; ++c) {
-            const float mean = den > 0.f ? row[c] / den : 0.f;
-            acc = fmaf(mean, W1[(int64_t)c * HD + col], acc);
-        }
-        s[(int64_t)hm * dh + jj] = acc;
-    }
-}
-
-// Projected form (head width 16): t_raw [H][M][16] already holds
-// sum_i w_i (x_i W1_h), so s = t_raw / (d + eps) + b1, zero mean for an
-// empty slice as above.
-__global__ void k_finalize_proj(const float *__restrict__ t_raw, const float *__restrict__ dsum,
-                                const float *__restrict__ b1, int H, int M, float eps, float *__restrict__ s) {
-    const int h = blockIdx.x;
-    for (int i = threadIdx.x; i < M * 16; i += blockDim.x) {
-        const int m = i >> 4, col = h * 16 + (i & 15);
-        const float den = dsum[h * M + m] + eps;
-        const float v = t_raw[((int64_t)h * M + m) * 16 + (i & 15)];
-        s[((int64_t)h * M + m) * 16 + (i & 15)] = (den > 0.f ? v / den : 0.f) + (b1 ? b1[col] : 0.f);
-    }
-}
-
-// Per-head attention among the M slice tokens, then Linear3 without bias:
-// q,k,v = s Wq[h], s Wk[h], s Wv[h]; A = softmax(q k^T / sqrt(dh)); s1 = A v;
-// Z[h][m][c] = s1[m][:] . W3[h*dh .. h*dh+dh-1][c].  Grid (H, ZB): the ZB
-// workgroups of a head each run its attention (the same arithmetic, so the
-// same s1) and write Z for their C / ZB columns; the first also writes s1.
-__global__ void k_attention(const float *__restrict__ s, const float *__restrict__ Wq,
-                            const float *__restrict__ Wk, const float *__restrict__ Wv,
-                            const float *__restrict__ W3, int C, int H, int M, int dh,
-                            float *__restrict__ s1, float *__restrict__ Z) {
-    extern __shared__ float sm[];
-    const int h = blockIdx.x;
-    float *ss = sm;             // [M][dh]
-    float *q = ss + M * dh;     // [M][dh]
-    float *k = q + M * dh;
-    float *v = k + M * dh;
-    float *A = v + M * dh;      // [M][M]
-    float *o = A + M * M;       // [M][dh]
-    const int n = M * dh;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) ss[i] = s[(int64_t)h * n + i];
-    __syncthreads();
-    const float *wq = Wq + (int64_t)h * dh * dh, *wk = Wk + (int64_t)h * dh * dh,
-                *wv = Wv + (int64_t)h * dh * dh;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) {
-        const int m = i / dh, jj = i - m * dh;
-        float aq = 0.f, ak = 0.f, av = 0.f;
-        for (int u = 0; u < dh; ++u) {
-            const float x = ss[m * dh + u];
-            aq = fmaf(x, wq[u * dh + jj], aq);
-            ak = fmaf(x, wk[u * dh + jj], ak);
-            av = fmaf(x, wv[u * dh + jj], av);
-        }
-        q[i] = aq; k[i] = ak; v[i] = av;
-    }
-    __syncthreads();
-    const float scale = 1.0f / sqrtf((float)dh);
-    for (int i = threadIdx.x; i < M * M; i += blockDim.x) {
-        const int a = i / M, b = i - a * M;
-        float acc = 0.f;
-        for (int u = 0; u < dh; ++u) acc = fmaf(q[a * dh + u], k[b * dh + u], acc);
-        A[i] = acc * scale;
-    }
-    __syncthreads();
-    for (int a = threadIdx.x; a < M; a += blockDim.x) {
-        float mx = A[a * M];
-        for (int b = 1; b < M; ++b) mx = fmaxf(mx, A[a * M + b]);
-        float sum = 0.f;
-        for (int b = 0; b < M; ++b) {
-            const float e = expf(A[a * M + b] - mx);
-            A[a * M + b] = e;
-            sum += e;
-        }
-        for (int b = 0; b < M; ++b) A[a * M + b] /= sum;
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < n; i += blockDim.x) {
-        const int a = i / dh, jj = i - a * dh;
-        float acc = 0.f;
-        for (int b = 0; b < M; ++b) acc = fmaf(A[a * M + b], v[b * dh + jj], acc);
-        o[i] = acc;
-        if (blockIdx.y == 0) s1[(int64_t)h * n + i] = acc;
-    }
-    __syncthreads();
-    const int CB = C / (int)gridDim.y, c0 = (int)blockIdx.y * CB;
-    for (int i = threadIdx.x; i < M * CB; i += blockDim.x) {
-        const int m = i / CB, c = c0 + (i - m * CB);
-        float acc = 0.f;
-        for (int u = 0; u < dh; ++u) acc = fmaf(o[m * dh + u], W3[(int64_t)(h * dh + u) * C + c], acc);
-        Z[((int64_t)h * M + m) * C + c] = acc;
-    }
 }
 
 }  // namespace ts3

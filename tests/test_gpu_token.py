@@ -1,0 +1,46 @@
+"""The slice-domain kernels (last fold level, Linear1, token attention, Linear3)
+at the edges of what they accept, against the oracle: head widths that do not
+divide a workgroup, one wide head, a working set past 64 KiB of
+LDS, one and several runs of part sums, both fold precisions, and no biases.
+
+All sums are float32 (or float64 in the fold) of well-scaled terms: the bar is that
+of the other float32 parity tests.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_helpers import banner, normwise, state_of, to_device, to_host
+from ts3_synth import make_weights
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("C,H,M,N,Q,accum,biases", [
+    (96, 32, 16, 700, 64, "fp32", True),      # head width 3: 85 groups of threads, one thread idle
+    (240, 1, 16, 300, 300, "fp64", True),     # head width 240: one group of threads
+    (224, 2, 64, 500, 128, "fp32", False),    # head width 112, 104 KiB of LDS
+    (48, 3, 144, 400, 100, "fp64", True),     # 144 slices: 9 columns per lane of the softmax
+    (64, 4, 32, 9000, 100, "fp32", True),     # 90 spans: two runs
+    (64, 4, 32, 9000, 100, "fp64", False),
+])
+def test_slice_tokens_and_attention(C, H, M, N, Q, accum, biases):
+    from paper_2602_04940_amd import LayerWeights, PhysicsAttention
+    banner(f"token side: C={C} H={H} M={M} N={N} Q={Q} {accum}")
+    x64 = np.random.default_rng(5).standard_normal((N, C)).astype(np.float32).astype(np.float64)
+    W = make_weights(C, H, M, C // H, seed=6, bias_seed=7)
+    if not biases:
+        for b in ("b1", "b2", "b3"):
+            W[b] = np.zeros_like(W[b])
+    ref = oracle.build_state(x64, W, H, M, 2.0)
+    out_ref = oracle.deslice(x64, W["W2"], W["b2"], ref["Z"], W["b3"], H, M, 2.0)
+    lw = LayerWeights({k: v for k, v in W.items() if biases or not k.startswith("b")})
+    x = to_device(x64, "fp32")
+    with PhysicsAttention(C, H, M, C // H, 0.5, "fp32", group_span=Q, max_points=N, accum=accum) as layer:
+        out = layer.forward(lw, x, tile=Q)
+        st = state_of(layer)
+    for k in ("s_raw", "d", "s", "s1", "Z"):
+        e = normwise(st[k], ref[k])
+        print(f"{k}: normwise {e:.2e}", flush=True)
+        assert e <= 1e-4, (k, e)
+    assert normwise(to_host(out), out_ref) <= 1e-4
