@@ -68,7 +68,7 @@ enum Phase { PH_RESET = 0, PH_ACCUM = 1, PH_FINAL = 2, PH_ATTEND = 3 };
 // runtime-shape kernels (rt) for the other multiples of 16.  The pass entry
 // points take C and M, which only the runtime-shape ones read.
 struct Kernels {
-    void (*pass1)(const void *, int64_t, int64_t, SpanGeo, int32_t, int32_t, int32_t, int32_t, const void *,
+    hipError_t (*pass1)(const void *, int64_t, int64_t, SpanGeo, int32_t, int32_t, int32_t, int32_t, const void *,
                   const float *, float *, hipStream_t);
     hipError_t (*pass2)(const void *, int64_t, int32_t, int32_t, int32_t, const void *, const float *, const void *,
                         void *, hipStream_t);
@@ -92,7 +92,7 @@ struct Kernels {
 };
 
 template <typename T, int C, int M>
-void launch_pass1(const void *x, int64_t n, int64_t span0, SpanGeo geo, int32_t nspan, int32_t H, int32_t, int32_t,
+hipError_t launch_pass1(const void *x, int64_t n, int64_t span0, SpanGeo geo, int32_t nspan, int32_t H, int32_t, int32_t,
                   const void *w2p, const float *b2s, float *partials, hipStream_t st) {
     if constexpr (sizeof(T) == 2 && C == 256) {
         // Wide rows: two heads per workgroup, two producer and two consumer
@@ -113,6 +113,7 @@ void launch_pass1(const void *x, int64_t n, int64_t span0, SpanGeo geo, int32_t 
         hipLaunchKernelGGL((k_slice_accumulate<T, C, M>), dim3(nspan * H), dim3(256), 0, st,
                            (const T *)x, n, span0, geo, nspan, H, (const T *)w2p, b2s, partials);
     }
+    return hipSuccess;
 }
 
 // Compute units of the current device, looked up once per device.
@@ -260,35 +261,64 @@ template <typename T, int C, int M> Kernels make_kernels() {
         return Kernels{&launch_pass1<T, C, M>, &launch_pass2<T, C, M>, nullptr, nullptr, nullptr};
 }
 
+// Runtime-shape launches: the smallest tile count that holds the head's slices.
+template <typename F> void rt_dispatch(int MT, F f) {
+    if (MT <= 1) f(std::integral_constant<int, 1>{});
+    else if (MT <= 2) f(std::integral_constant<int, 2>{});
+    else if (MT <= 4) f(std::integral_constant<int, 4>{});
+    else if (MT <= 8) f(std::integral_constant<int, 8>{});
+    else f(std::integral_constant<int, 16>{});
+}
+
+// Grants a kernel the dynamic LDS it asks for (on every call, as for k_deslice_w8).
+template <typename K> hipError_t grant_lds(K *kernel, int bytes) {
+    if (bytes <= 64 * 1024) return hipSuccess;
+    return hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+}
+
 // Launches of at most RT_MAX_WGS workgroups (larger calls are split into
-// span or point ranges, which changes no result).
+// part or point ranges, which changes no result).
 constexpr int64_t RT_MAX_WGS = 1 << 22;
 
 template <typename T>
-void launch_pass1_rt(const void *x, int64_t n, int64_t span0, SpanGeo geo, int32_t nspan, int32_t H, int32_t C,
-                     int32_t M, const void *w2r, const float *b2s, float *partials, hipStream_t st) {
-    const size_t lds = (size_t)RT_PTS * (C + M) * 4;
-    const int64_t per_span = (int64_t)H * ((C + 63) / 64);
+hipError_t launch_pass1_rt(const void *x, int64_t n, int64_t span0, SpanGeo geo, int32_t nspan, int32_t H, int32_t C,
+                           int32_t M, const void *w2r, const float *b2s, float *partials, hipStream_t st) {
+    const RtPass1 cfg = rt_pass1(RT_NP<T>, C, M);
+    const int64_t per_span = (int64_t)H * ((C + cfg.CC - 1) / cfg.CC);
     const int64_t batch = std::max<int64_t>(1, RT_MAX_WGS / per_span);
-    for (int64_t s0 = 0; s0 < nspan; s0 += batch) {
-        const int64_t ns = std::min<int64_t>(batch, nspan - s0);
-        SpanGeo part = geo;
-        part.first += (int32_t)s0;
-        hipLaunchKernelGGL(k_slice_accumulate_rt<T>, dim3((unsigned)(ns * per_span)), dim3(256), lds, st,
-                           (const T *)x, n, span0 + s0, part, H, C, M, (const T *)w2r, b2s, partials);
-    }
+    hipError_t e = hipSuccess;
+    rt_dispatch(M / 16, [&](auto mt) {
+        constexpr auto kernel = &k_slice_accumulate_rt<T, decltype(mt)::value>;
+        e = grant_lds(kernel, cfg.lds);
+        for (int64_t s0 = 0; e == hipSuccess && s0 < nspan; s0 += batch) {
+            const int64_t ns = std::min<int64_t>(batch, nspan - s0);
+            SpanGeo part = geo;
+            part.first += (int32_t)s0;
+            hipLaunchKernelGGL(kernel, dim3((unsigned)(ns * per_span)), dim3(512), (size_t)cfg.lds, st, (const T *)x, n,
+                               span0 + s0, part, (int32_t)ns, H, C, M, cfg.CC, cfg.PB, (const bf16_t *)w2r, b2s, partials);
+        }
+    });
+    return e;
 }
 template <typename T>
 hipError_t launch_pass2_rt(const void *x, int64_t n, int32_t H, int32_t C, int32_t M, const void *w2r,
                            const float *b2s, const void *zr, void *out, hipStream_t st) {
-    const size_t lds = (size_t)RT_PTS * (C + M) * 4;
-    for (int64_t p0 = 0; p0 < n; p0 += RT_MAX_WGS * RT_PTS) {
-        const int64_t np = std::min<int64_t>(RT_MAX_WGS * RT_PTS, n - p0);
-        hipLaunchKernelGGL(k_deslice_rt<T>, dim3((unsigned)((np + RT_PTS - 1) / RT_PTS)), dim3(256), lds, st,
-                           (const T *)x + p0 * C, np, H, C, M, (const T *)w2r, b2s, (const T *)zr,
-                           (T *)out + p0 * C);
-    }
-    return hipSuccess;
+    const RtPass2 cfg = rt_pass2(RT_NP<T>, C, M);
+    const int lds = rt_pass2_lds(RT_NP<T>, cfg.PT, cfg.GH, C, M), P = 16 * cfg.PT;
+    hipError_t e = hipSuccess;
+    rt_dispatch(M / 16, [&](auto mt) {
+        constexpr int MT = decltype(mt)::value;
+        constexpr auto k4 = &k_deslice_rt<T, MT, 4>, k2 = &k_deslice_rt<T, MT, 2>;
+        const auto kernel = cfg.PT == 4 ? k4 : k2;
+        e = grant_lds(kernel, lds);
+        for (int64_t p0 = 0; e == hipSuccess && p0 < n; p0 += RT_MAX_WGS * P) {
+            const int64_t np = std::min<int64_t>(RT_MAX_WGS * P, n - p0);
+            hipLaunchKernelGGL(kernel, dim3((unsigned)((np + P - 1) / P)), dim3(512), (size_t)lds, st,
+                               (const T *)x + p0 * C, np, H, C, M, RtGroup(cfg.GH, M), (const bf16_t *)w2r, b2s,
+                               (const bf16_t *)zr, (T *)out + p0 * C);
+        }
+    });
+    return e;
 }
 
 bool find_kernels(int dtype, int C, int M, Kernels *k) {
@@ -318,12 +348,18 @@ bool find_any_kernels(int dtype, int C, int M, Kernels *k) {
     return true;
 }
 
-// Elements of the prepared W2' and Z buffers (fragment order, or rows for
-// the runtime-shape kernels).
-int64_t w2p_elems(const ts3_desc &d) { return (int64_t)d.H * d.M * d.C; }
-int64_t zp_elems(const ts3_desc &d, bool rt) {
+// Bytes of the prepared W2' and Z buffers (fragments of the storage type, or the
+// runtime-shape kernels' 16-bit parts).
+int64_t w2p_bytes(const ts3_desc &d, bool rt) {
+    const int es = d.io_dtype == TS3_BF16 ? 2 : 4, np = d.io_dtype == TS3_BF16 ? 1 : 3;
+    return rt ? (int64_t)d.H * d.M * rt_ck(d.C) * 32 * 2 * np : (int64_t)d.H * d.M * d.C * es;
+}
+int64_t zp_bytes(const ts3_desc &d, bool rt) {
+    const int es = d.io_dtype == TS3_BF16 ? 2 : 4, np = d.io_dtype == TS3_BF16 ? 1 : 3;
     const int KM = d.M >= 32 ? d.M / 32 : 1;
-    return rt ? (int64_t)d.H * d.M * d.C : (int64_t)d.H * (d.C / 16) * KM * 512;
+    if (!rt) return (int64_t)d.H * (d.C / 16) * KM * 512 * es;
+    const RtGroup gr(rt_pass2(np, d.C, d.M).GH, d.M);
+    return (int64_t)((d.H + gr.GH - 1) / gr.GH) * (d.C / 16) * gr.KG * 512 * 2 * np;
 }
 
 }  // namespace
@@ -424,8 +460,10 @@ constexpr int64_t PART_POINTS = 4096, PART_WGS = 256, PART_ROUNDS = 4, PART_BYTE
 
 SpanGeo span_geo(const ts3_desc &d, const Kernels &k, bool proj, int64_t E) {
     const bool pairs = d.H % 2 == 0 && d.io_dtype == TS3_BF16 && !k.rt && (d.C == 256 || (d.C == 128 && d.M >= 32));
-    const int64_t unit = proj ? 96 : !pairs ? 128 : d.C == 256 ? 32 : 64;
-    const int64_t wgs = k.rt ? (int64_t)d.H * ((d.C + 63) / 64) : pairs ? d.H / 2 : d.H;  // per part
+    const int np = d.io_dtype == TS3_BF16 ? 1 : 3;
+    const RtPass1 rt1 = k.rt ? rt_pass1(np, d.C, d.M) : RtPass1{d.C, 128, 0};
+    const int64_t unit = proj ? 96 : !pairs ? rt1.PB : d.C == 256 ? 32 : 64;
+    const int64_t wgs = pairs ? d.H / 2 : (int64_t)d.H * ((d.C + rt1.CC - 1) / rt1.CC);  // per part
     const int64_t N = std::max<int64_t>(d.max_points, 1), Q = d.group_span;
     const int64_t one_round = (N * wgs + PART_WGS - 1) / PART_WGS;
     const int64_t want = std::min(one_round, std::max(PART_POINTS, one_round / PART_ROUNDS));
@@ -447,17 +485,14 @@ ts3_status check_weights_w2(const ts3_weights *w) {
 ts3_status prep_w2(ts3_state *st, const ts3_weights *w, hipStream_t stream) {
     const ts3_desc &d = st->desc;
     const float scale = (float)(1.4426950408889634 / (double)d.temperature);
-    const int64_t total = w2p_elems(d);
+    const int64_t total = (int64_t)d.H * d.M * d.C;
     const int grid = (int)std::min<int64_t>((total + 255) / 256, 4096);
     const int grid2 = std::max(grid, (d.H * d.M + 255) / 256);
     const float *W1 = st->proj ? w->W1 : nullptr;  // the W1 fragments of the projected pass 1
     bf16_t *w1p = W1 ? (bf16_t *)st->w1p : nullptr;
-    if (st->k.rt && d.io_dtype == TS3_BF16)
-        hipLaunchKernelGGL(k_prep_w2_rt<bf16_t>, dim3(grid2), dim3(256), 0, stream, w->W2, w->b2, scale, d.C, d.H,
-                           d.M, (bf16_t *)st->w2p, st->b2s);
-    else if (st->k.rt)
-        hipLaunchKernelGGL(k_prep_w2_rt<float>, dim3(grid2), dim3(256), 0, stream, w->W2, w->b2, scale, d.C, d.H,
-                           d.M, (float *)st->w2p, st->b2s);
+    if (st->k.rt)
+        hipLaunchKernelGGL(k_prep_w2_rt, dim3(grid2), dim3(256), 0, stream, w->W2, w->b2, scale, d.C, d.H, d.M,
+                           d.io_dtype == TS3_BF16 ? 1 : 3, (bf16_t *)st->w2p, st->b2s);
     else if (d.io_dtype == TS3_BF16)
         hipLaunchKernelGGL(k_prep_w2<bf16_t>, dim3(grid2), dim3(256), 0, stream, w->W2, w->b2, scale, d.C,
                            d.H, d.M, (bf16_t *)st->w2p, st->b2s, W1, w1p);
@@ -474,14 +509,12 @@ ts3_status prep_w2(ts3_state *st, const ts3_weights *w, hipStream_t stream) {
 
 ts3_status prep_z(ts3_state *st, hipStream_t stream) {
     const ts3_desc &d = st->desc;
-    const int64_t total = zp_elems(d, st->k.rt);
+    const int64_t total = (int64_t)d.H * d.M * d.C;
     const int grid = (int)std::min<int64_t>((total + 255) / 256, 4096);
-    if (st->k.rt && d.io_dtype == TS3_BF16)
-        hipLaunchKernelGGL(k_prep_z_rt<bf16_t>, dim3(grid), dim3(256), 0, stream, st->Z, st->b3, d.C, d.H, d.M,
-                           (bf16_t *)st->zp);
-    else if (st->k.rt)
-        hipLaunchKernelGGL(k_prep_z_rt<float>, dim3(grid), dim3(256), 0, stream, st->Z, st->b3, d.C, d.H, d.M,
-                           (float *)st->zp);
+    const int np = d.io_dtype == TS3_BF16 ? 1 : 3;
+    if (st->k.rt)
+        hipLaunchKernelGGL(k_prep_z_rt, dim3(grid), dim3(256), 0, stream, st->Z, st->b3, d.C, d.H, d.M,
+                           RtGroup(rt_pass2(np, d.C, d.M).GH, d.M), np, (bf16_t *)st->zp);
     else if (d.io_dtype == TS3_BF16)
         hipLaunchKernelGGL(k_prep_z<bf16_t>, dim3(grid), dim3(256), 0, stream, st->Z, st->b3, d.C, d.H, d.M,
                            (bf16_t *)st->zp);
@@ -571,8 +604,8 @@ ts3_status ts3_state_create(const ts3_desc *desc, ts3_state **out) {
         {(void **)&st->Z, HM * d.C * 4},
         {(void **)&st->b2s, HM * 4},
         {(void **)&st->b3, (int64_t)d.C * 4},
-        {&st->w2p, w2p_elems(d) * st->esize},
-        {&st->zp, zp_elems(d, st->k.rt) * st->esize},
+        {&st->w2p, w2p_bytes(d, st->k.rt)},
+        {&st->zp, zp_bytes(d, st->k.rt)},
         {(void **)&st->bdZ, HM * d.C * 4},
         {(void **)&st->bdsr, HM * d.C * 4},
         {(void **)&st->bdsT, HM * d.C * 4},
@@ -670,7 +703,7 @@ ts3_status ts3_slice_accumulate(ts3_state *st, const ts3_weights *w, const void 
     if (st->proj)
         st->k.pass1p(x_tile, n_tile, part0, st->geo, nparts, d.H, st->w2p, st->b2s, st->w1p, st->partials, hs);
     else
-        st->k.pass1(x_tile, n_tile, part0, st->geo, nparts, d.H, d.C, d.M, st->w2p, st->b2s, st->partials, hs);
+        HIP_TRY(st->k.pass1(x_tile, n_tile, part0, st->geo, nparts, d.H, d.C, d.M, st->w2p, st->b2s, st->partials, hs));
     LAUNCH_CHECK("slice_accumulate");
     for (int64_t i = span0; i < span0 + nspan; ++i) st->span_written[(size_t)i] = 1;
     if (ragged) st->span_written[(size_t)(span0 + nspan - 1)] = 2;
@@ -690,7 +723,7 @@ namespace {
 template <typename TS, typename TA>
 void launch_tokens(ts3_state *st, const TS *src, int64_t count, const ts3_weights *w, hipStream_t hs) {
     const ts3_desc &d = st->desc;
-    hipLaunchKernelGGL((k_slice_tokens<TS, TA>), dim3((unsigned)(d.H * d.M / TOK_ROWS)), dim3(256), 0, hs, src, st->E,
+    hipLaunchKernelGGL((k_slice_tokens<TS, TA>), dim3((unsigned)(d.H * d.M / TOK_ROWS)), dim3(TOK_THREADS), 0, hs, src, st->E,
                        count, st->rowc, st->proj, w->W1, w->b1, d.H, d.M, d.dh, d.eps, st->s_raw, st->dsum, st->s);
 }
 
@@ -749,7 +782,8 @@ template <typename T> ts3_status launch_attend(ts3_state *st, const ts3_weights 
     if (lds > 64 * 1024)
         HIP_TRY(hipFuncSetAttribute((const void *)k_attend<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                     ATTN_LDS_MAX));
-    const AttendOut<T> out{st->s1, st->Z, st->b3, (T *)st->zp, st->k.rt, sf ? (bf16_t *)st->sfp : nullptr,
+    const AttendOut<T> out{st->s1, st->Z, st->b3, (T *)st->zp,
+                           st->k.rt ? rt_pass2(RT_NP<T>, d.C, d.M).GH : 0, sf ? (bf16_t *)st->sfp : nullptr,
                            sf ? (bf16_t *)st->w3p : nullptr};
     const int extra = sf ? 16 : 1;
     hipLaunchKernelGGL(k_attend<T>, dim3((unsigned)(d.H * (d.M / ATT_ROWS) + extra)), dim3(256), lds, hs, st->s, w->Wq,
@@ -1092,9 +1126,11 @@ ts3_status ts3_state_set(ts3_state *st, const ts3_weights *w, int32_t which, con
 // not a device pointer.
 namespace {
 
-// A call is accepted by the bytes that scratch_layout counts (one partial per
-// span); the array holds SCRATCH_SLACK more, for the runs of a span's parts (at
-// most PART_BYTES / FOLD as doubles, and one run of the shape's partial is counted).
+// A call is accepted by the bytes that scratch_layout counts; the array holds
+// SCRATCH_SLACK more, for the runs of the spans' parts (at most 4 MiB as doubles
+// beyond the run that is counted, PART_BYTES / FOLD) and the float32 operands'
+// third 16-bit part (half as much again as W2' and Z, which take at most a sixth of
+// the counted bytes each).
 constexpr size_t SCRATCH_BYTES = size_t(64) << 20, SCRATCH_SLACK = size_t(16) << 20;
 constexpr int SCRATCH_MAX_DEVICES = 64;
 static __device__ __align__(256) unsigned char scratch[SCRATCH_BYTES + SCRATCH_SLACK];
@@ -1125,8 +1161,9 @@ struct ScratchLayout {
     size_t s_raw, dsum, s, s1, Z, b2s, b3, w2p, zp, sfp, w3p, w1p, tail, total;
 };
 
-// The bytes that a call is refused or accepted by: a tile's spans, one partial
-// each.
+// `total` is what a call is accepted by: the operands at their storage type and
+// one partial for each span of a tile.  The operands' parts and the runs of the
+// spans' parts may take more, which SCRATCH_SLACK covers.
 ScratchLayout scratch_layout(const ts3_desc &d, int64_t N, int64_t tile) {
     auto up = [](size_t b) { return (b + 255) & ~size_t(255); };
     const int64_t HM = (int64_t)d.H * d.M;
@@ -1149,14 +1186,16 @@ ScratchLayout scratch_layout(const ts3_desc &d, int64_t N, int64_t tile) {
     take(L.Z, (size_t)(HM * d.C) * 4);
     take(L.b2s, (size_t)HM * 4);
     take(L.b3, (size_t)d.C * 4);
-    take(L.w2p, (size_t)w2p_elems(d) * esize);
-    take(L.zp, (size_t)zp_elems(d, k.rt) * esize);
     const bool sf = k.pass2sf && d.H * 16 == d.C;  // the slice-state pass 2, as for a state
     take(L.sfp, sf ? (size_t)HM * 16 * 2 : 0);
     take(L.w3p, sf ? (size_t)d.C * d.C * 2 : 0);
     take(L.w1p, proj ? (size_t)d.C * d.C * 4 : 0);
+    const int64_t zslots = k.rt ? HM * d.C : (int64_t)d.H * (d.C / 16) * (d.M >= 32 ? d.M / 32 : 1) * 512;
+    L.total = at + up((size_t)(tile_spans * E) * 4) + up((size_t)(nrun * E) * (d.accum == TS3_ACCUM_FP64 ? 8 : 4)) +
+              up((size_t)(HM * d.C * esize)) + up((size_t)(zslots * esize));
+    take(L.w2p, (size_t)w2p_bytes(d, k.rt));
+    take(L.zp, (size_t)zp_bytes(d, k.rt));
     L.tail = at;
-    L.total = at + up((size_t)(tile_spans * E) * 4) + up((size_t)(nrun * E) * (d.accum == TS3_ACCUM_FP64 ? 8 : 4));
     return L;
 }
 
@@ -1266,7 +1305,7 @@ ts3_status ts3_layer_forward_noalloc(const ts3_desc *desc, const ts3_weights *w,
         if (st.proj)
             st.k.pass1p(xt, N - t0, 0, part, (int32_t)np, d.H, st.w2p, st.b2s, st.w1p, st.partials, hs);
         else
-            st.k.pass1(xt, N - t0, 0, part, (int32_t)np, d.H, d.C, d.M, st.w2p, st.b2s, st.partials, hs);
+            HIP_TRY(st.k.pass1(xt, N - t0, 0, part, (int32_t)np, d.H, d.C, d.M, st.w2p, st.b2s, st.partials, hs));
         LAUNCH_CHECK("slice_accumulate");
         if (d.accum == TS3_ACCUM_FP64) fold_tile<double>(st.partials, E, p0, np, st.runs, hs);
         else fold_tile<float>(st.partials, E, p0, np, st.runs, hs);

@@ -69,6 +69,44 @@ __device__ __forceinline__ void mma(f32x4 &acc, const Frag<float> &a, const Frag
     for (int t = 0; t < 8; ++t) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[t], b.v[t], acc, 0, 0, 0);
 }
 
+// Float32 operands as three bfloat16 parts: v = p[0] + p[1] + p[2] (rounded
+// value, rounded remainder, remainder of that; 8 + 8 + 8 significant bits, so
+// the sum is v exactly while no part underflows).  A product of two such
+// operands takes the six part products of weight 2^-16 and more; the three that
+// are dropped are below 2^-25 of |a||b|, half an ulp of the float32 product.
+// Six 16x16x32 bf16 MFMAs take 96 cycles where the eight 16x16x4 float32 MFMAs
+// of the same K step take 256.
+template <int NP> struct Parts {
+    bf16x8 p[NP];
+};
+__device__ __forceinline__ void split8(const float (&v)[8], Parts<3> &f) {
+    u32x4 u0, u1, u2;
+#pragma unroll
+    for (int t = 0; t < 8; t += 2) {
+        const uint32_t h = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)v[t], (__bf16)v[t + 1]});
+        const float r0 = v[t] - __uint_as_float(h << 16), r1 = v[t + 1] - __uint_as_float(h & 0xffff0000u);
+        const uint32_t m = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)r0, (__bf16)r1});
+        const float s0 = r0 - __uint_as_float(m << 16), s1 = r1 - __uint_as_float(m & 0xffff0000u);
+        u0[t >> 1] = h;
+        u1[t >> 1] = m;
+        u2[t >> 1] = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)s0, (__bf16)s1});
+    }
+    f.p[0] = __builtin_bit_cast(bf16x8, u0);
+    f.p[1] = __builtin_bit_cast(bf16x8, u1);
+    f.p[2] = __builtin_bit_cast(bf16x8, u2);
+}
+// Part products (i of A, j of B) in the order they are added, smallest first:
+// number Q of those that operands of NA and NB parts take.
+template <int NA, int NB> struct PartProducts {
+    static constexpr int N = NA == 1 || NB == 1 ? NA * NB : 6;
+    static constexpr int I[6] = {NA == 1 ? 0 : NB == 1 ? 2 : 0, NA == 1 ? 0 : NB == 1 ? 1 : 2, NB == 1 || NA == 1 ? 0 : 1,
+                                 0, 1, 0};
+    static constexpr int J[6] = {NB == 1 ? 0 : 2, NB == 1 ? 0 : NA == 1 ? 1 : 0, NB == 1 || NA == 1 ? 0 : 1, 1, 0, 0};
+};
+__device__ __forceinline__ f32x4 mma_bf16(const bf16x8 &a, const bf16x8 &b, const f32x4 &c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
 // Load the 8 consecutive storage elements at p (16 B for bf16, 32 B for fp32).
 __device__ __forceinline__ void load8(Frag<bf16_t> &f, const bf16_t *p) {
     f.v = *reinterpret_cast<const bf16x8 *>(p);

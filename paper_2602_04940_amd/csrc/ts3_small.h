@@ -78,6 +78,21 @@ __global__ void k_zero(float *__restrict__ p, int64_t n) {
         p[i] = 0.f;
 }
 
+// Sum of n values at stride E, in order, added to `acc`.
+template <typename TS, typename TA>
+__device__ __forceinline__ TA ordered_sum(const TS *__restrict__ p, int64_t E, int64_t n, TA acc = 0) {
+    int64_t i = 0;
+    for (; i + 16 <= n; i += 16) {  // sixteen loads in flight
+        TS v[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) v[k] = p[(i + k) * E];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) acc += (TA)v[k];
+    }
+    for (; i < n; ++i) acc += (TA)p[i * E];
+    return acc;
+}
+
 // Ordered fold of span partials (Eq. (4) sum over tiles): element e of
 // [H][M][C+1] is summed over spans 0..nspan-1 in two fixed levels (runs of
 // FOLD spans, then the runs in order), giving the same bits for any tiling.
@@ -91,9 +106,7 @@ __global__ void k_fold_runs(const float *__restrict__ partials, int64_t E, int64
     if (e >= E) return;
     const int64_t s0 = run * FOLD;
     const int64_t s1 = s0 + FOLD < nspan ? s0 + FOLD : nspan;
-    T acc = 0;
-    for (int64_t s = s0; s < s1; ++s) acc += (T)partials[s * E + e];
-    runs[run * E + e] = acc;
+    runs[run * E + e] = ordered_sum<float, T>(partials + s0 * E + e, E, s1 - s0);
 }
 
 // The same fold taken one tile at a time: the tile's spans [g0, g0 + ns)
@@ -110,9 +123,8 @@ __global__ void k_fold_runs_tile(const float *__restrict__ partials, int64_t E, 
     const int64_t r0 = run * FOLD;
     const int64_t s0 = r0 > g0 ? r0 : g0;
     const int64_t s1 = r0 + FOLD < g0 + ns ? r0 + FOLD : g0 + ns;
-    T acc = s0 == r0 ? (T)0 : runs[run * E + e];
-    for (int64_t s = s0; s < s1; ++s) acc += (T)partials[(s - g0) * E + e];
-    runs[run * E + e] = acc;
+    const T from = s0 == r0 ? (T)0 : runs[run * E + e];
+    runs[run * E + e] = ordered_sum<float, T>(partials + (s0 - g0) * E + e, E, s1 - s0, from);
 }
 
 template <typename T>
@@ -120,8 +132,7 @@ __global__ void k_fold_final(const T *__restrict__ runs, int64_t E, int64_t nrun
                              float *__restrict__ dsum) {
     const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (e >= E) return;
-    T acc = 0;
-    for (int64_t r = 0; r < nrun; ++r) acc += runs[r * E + e];
+    const T acc = ordered_sum<T, T>(runs + e, E, nrun);
     const int64_t hm = e / (C + 1);
     const int c = (int)(e - hm * (C + 1));
     if (c < C)

@@ -11,6 +11,7 @@
 #pragma once
 #include "ts3_device.h"
 #include "ts3_pass2.h"  // zchan
+#include "ts3_rt.h"
 #include "ts3_small.h"
 
 namespace ts3 {
@@ -22,49 +23,34 @@ __device__ __forceinline__ int64_t zp_index(int h, int m, int c, int CT, int KM)
     return ((((int64_t)h * CT + ct) * KM + (m >> 5)) * 64 + g * 16 + i) * 8 + t;
 }
 
-// Sum of n values at stride E, in order.
-template <typename TS, typename TA>
-__device__ __forceinline__ TA ordered_sum(const TS *__restrict__ p, int64_t E, int64_t n) {
-    TA acc = 0;
-    int64_t i = 0;
-    for (; i + 8 <= n; i += 8) {  // eight loads in flight
-        TS v[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] = p[(i + k) * E];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) acc += (TA)v[k];
-    }
-    for (; i < n; ++i) acc += (TA)p[i * E];
-    return acc;
-}
-
-constexpr int TOK_ROWS = 8;       // slice rows (h, m) per workgroup of k_slice_tokens
+constexpr int TOK_ROWS = 2;       // slice rows (h, m) per workgroup of k_slice_tokens
+constexpr int TOK_THREADS = 512;
 constexpr int TOK_MAX_C = 512;
 
 // The fold's last level and the slice tokens, for TOK_ROWS rows per workgroup
-// (grid H*M / TOK_ROWS, 256 threads; M is a multiple of 16, so a workgroup's rows
+// (grid H*M / TOK_ROWS, 512 threads; M is a multiple of 16, so a workgroup's rows
 // are one head's):
 //   s_raw, d = sum over `count` terms at stride E, in order (runs of part sums,
 //              or the part sums themselves when they make up one run),
 //   s[m][j]  = b1 + (s_raw / (d + eps))[m][:] . W1[:, h*dh + j]   (rowc = C), or
 //   s[m][j]  = b1 + (t / (d + eps))[m][j]                         (projected).
 // The mean is taken before Linear1 (the physical state of Appendix A.4); an empty
-// slice (d + eps <= 0) has mean zero.  256 / dh groups of threads take every
-// (256/dh)-th channel each and are added in order.  At C = 256, M = 64, H = 8:
+// slice (d + eps <= 0) has mean zero.  512 / dh groups of threads take every
+// (512/dh)-th channel each and are added in order.  At C = 256, M = 64, H = 8:
 // 30 us as one wave per token (a chain of 256 dependent loads and sums, one
 // division each).
 template <typename TS, typename TA>
-__global__ __launch_bounds__(256) void k_slice_tokens(const TS *__restrict__ src, int64_t E, int64_t count, int rowc,
+__global__ __launch_bounds__(TOK_THREADS) void k_slice_tokens(const TS *__restrict__ src, int64_t E, int64_t count, int rowc,
                                                       bool projected, const float *__restrict__ W1,
                                                       const float *__restrict__ b1, int H, int M, int dh, float eps,
                                                       float *__restrict__ s_raw, float *__restrict__ dsum,
                                                       float *__restrict__ s) {
     __shared__ float raw[TOK_ROWS * (TOK_MAX_C + 1)];
-    __shared__ float red[256 * TOK_ROWS];
+    __shared__ float red[TOK_THREADS * TOK_ROWS];
     const int tid = threadIdx.x;
     const int hm0 = (int)blockIdx.x * TOK_ROWS, h = hm0 / M;
     const int ld = rowc + 1, HD = H * dh;
-    for (int e = tid; e < TOK_ROWS * ld; e += 256) {
+    for (int e = tid; e < TOK_ROWS * ld; e += TOK_THREADS) {
         const float v = (float)ordered_sum<TS, TA>(src + (int64_t)hm0 * ld + e, E, count);
         raw[e] = v;
         const int r = e / ld, c = e - r * ld;
@@ -73,20 +59,20 @@ __global__ __launch_bounds__(256) void k_slice_tokens(const TS *__restrict__ src
     }
     __syncthreads();
     if (projected) {
-        for (int i = tid; i < TOK_ROWS * dh; i += 256) {
+        for (int i = tid; i < TOK_ROWS * dh; i += TOK_THREADS) {
             const int r = i / dh, j = i - r * dh;
             const float den = raw[r * ld + rowc] + eps;
             s[(int64_t)(hm0 + r) * dh + j] = (den > 0.f ? raw[r * ld + j] / den : 0.f) + (b1 ? b1[h * dh + j] : 0.f);
         }
         return;
     }
-    for (int e = tid; e < TOK_ROWS * rowc; e += 256) {
+    for (int e = tid; e < TOK_ROWS * rowc; e += TOK_THREADS) {
         const int r = e / rowc, c = e - r * rowc;
         const float den = raw[r * ld + rowc] + eps;
         raw[r * ld + c] = den > 0.f ? raw[r * ld + c] / den : 0.f;
     }
     __syncthreads();
-    const int groups = 256 / dh, cg = tid / dh, j = tid - cg * dh;  // dh <= 256
+    const int groups = TOK_THREADS / dh, cg = tid / dh, j = tid - cg * dh;  // dh <= 256
     if (cg < groups) {
         float acc[TOK_ROWS];
 #pragma unroll
@@ -101,7 +87,7 @@ __global__ __launch_bounds__(256) void k_slice_tokens(const TS *__restrict__ src
         for (int r = 0; r < TOK_ROWS; ++r) red[(cg * TOK_ROWS + r) * dh + j] = acc[r];
     }
     __syncthreads();
-    for (int i = tid; i < TOK_ROWS * dh; i += 256) {
+    for (int i = tid; i < TOK_ROWS * dh; i += TOK_THREADS) {
         float acc = b1 ? b1[h * dh + i % dh] : 0.f;
         for (int q = 0; q < groups; ++q) acc += red[q * TOK_ROWS * dh + i];
         s[(int64_t)hm0 * dh + i] = acc;
@@ -111,17 +97,58 @@ __global__ __launch_bounds__(256) void k_slice_tokens(const TS *__restrict__ src
 // Where the decoding operands go; what a layer does not use is NULL.
 template <typename T> struct AttendOut {
     float *s1, *Z, *b3;
-    T *zp;         // fragments [H][CT][KM][64][8], or rows [H*M][C] (rows = true)
-    bool rows;
+    T *zp;         // fragments [H][CT][KM][64][8], or the runtime-shape parts (rt heads at a time)
+    int rt;        // 0, or GH of the runtime-shape layout
     bf16_t *sf;    // slice-state pass 2 (dh = 16, M a multiple of 32): s'^T fragments
     bf16_t *w3f;   // and W3^T fragments
 };
 
 constexpr int ATT_ROWS = 16;  // token rows per workgroup of k_attend
-constexpr int ATT_KV = 8;     // rows of k and v that a thread forms at a time
+constexpr int ATT_KV = 8;     // rows of q, k and v that a thread forms at a time
 
 __host__ __device__ __forceinline__ size_t attend_lds_bytes(int M, int dh) {
-    return (size_t)(3 * M * dh + M + ATT_ROWS * M + 2 * ATT_ROWS * dh) * 4;
+    const int dp = (dh + 3) & ~3;
+    return (size_t)(2 * M * dp + M * (dp + 4) + ATT_ROWS * M + 2 * ATT_ROWS * dp) * 4;
+}
+__device__ __forceinline__ float dot4(float acc, const float4 &a, const float4 &b) {
+    return fmaf(a.w, b.w, fmaf(a.z, b.z, fmaf(a.y, b.y, fmaf(a.x, b.x, acc))));
+}
+
+// Rows rg, rg + groups, ... (count of them) of in [.][dp] times w [dh][dh], column
+// j, for one or two matrices: out[row * ld + j].  Rows of `in` are zero past dh.
+template <int NW>
+__device__ __forceinline__ void token_rows(const float *in, int rows, int rg, int groups, int dh, int dp, int j,
+                                           const float *const (&w)[NW], float *const (&out)[NW], const int (&ld)[NW]) {
+    for (int rb = rg; rb < rows; rb += groups * ATT_KV) {
+        float acc[NW][ATT_KV];
+#pragma unroll
+        for (int k = 0; k < NW; ++k)
+#pragma unroll
+            for (int i = 0; i < ATT_KV; ++i) acc[k][i] = 0.f;
+#pragma unroll 4
+        for (int u = 0; u < dp; u += 4) {
+            float4 wv[NW];
+#pragma unroll
+            for (int k = 0; k < NW; ++k) {
+                const float *p = w[k] + u * dh + j;
+                wv[k] = float4{p[0], u + 1 < dh ? p[dh] : 0.f, u + 2 < dh ? p[2 * dh] : 0.f, u + 3 < dh ? p[3 * dh] : 0.f};
+            }
+#pragma unroll
+            for (int i = 0; i < ATT_KV; ++i) {
+                const int r = rb + i * groups;
+                const float4 x = *reinterpret_cast<const float4 *>(in + (r < rows ? r : 0) * dp + u);
+#pragma unroll
+                for (int k = 0; k < NW; ++k) acc[k][i] = dot4(acc[k][i], x, wv[k]);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < ATT_KV; ++i) {
+            const int r = rb + i * groups;
+            if (r < rows)
+#pragma unroll
+                for (int k = 0; k < NW; ++k) out[k][r * ld[k] + j] = acc[k][i];
+        }
+    }
 }
 
 // Attention among a head's M tokens, Linear3 and the decoding operands, for
@@ -130,15 +157,16 @@ __host__ __device__ __forceinline__ size_t attend_lds_bytes(int M, int dh) {
 // W3[h*dh .. h*dh+dh-1][c], stored with b3 / H as the decoding operand (k_prep_z
 // has its order).  Every workgroup of a head forms all of k and v again, which
 // costs M/16 times 2*M*dh*dh products but no second launch.  Grid H * M / 16, then
-// `extra` workgroups for W3^T fragments and b3; 256 threads.  110 us at C = 256, M
-// = 64, H = 8 (48 us at C = 128) as one workgroup per head and 64 channels, of
-// which most was the softmax of a whole row by one thread.
+// `extra` workgroups for W3^T fragments and b3; 256 threads.  Bound by LDS
+// instructions: rows are padded to four floats and read as such (36 us at C = 256,
+// M = 64, H = 8 with single floats; 110 us as one workgroup per head and 64
+// channels, of which most was the softmax of a whole row by one thread).
 template <typename T>
 __global__ __launch_bounds__(256) void k_attend(const float *__restrict__ s, const float *__restrict__ Wq,
                                                 const float *__restrict__ Wk, const float *__restrict__ Wv,
                                                 const float *__restrict__ W3, const float *__restrict__ b3, int C,
                                                 int H, int M, int dh, int extra, AttendOut<T> out) {
-    extern __shared__ float sm[];
+    extern __shared__ __attribute__((aligned(16))) float sm[];
     const int tid = threadIdx.x;
     const int tiles = M / ATT_ROWS, main = H * tiles;
     if ((int)blockIdx.x >= main) {
@@ -153,53 +181,36 @@ __global__ __launch_bounds__(256) void k_attend(const float *__restrict__ s, con
                 store_elem(out.w3f + i, W3[(int64_t)k * C + zchan(ct, lane & 15)]);
             }
         }
+        if (out.rt) rt_zero_pad((bf16_t *)out.zp, C, H, M, RtGroup(out.rt, M), RT_NP<T>, tid + part * 256, extra * 256);
         if (part == 0)
             for (int c = tid; c < C; c += 256) out.b3[c] = b3 ? b3[c] : 0.f;
         return;
     }
     const int h = (int)blockIdx.x / tiles, m0 = ((int)blockIdx.x - h * tiles) * ATT_ROWS;
-    const int n = M * dh, kld = dh + 1;
-    float *ss = sm;                    // [M][dh]
-    float *k = ss + n;                 // [M][dh + 1]: the rows' lanes fall on different banks
-    float *v = k + M * kld;            // [M][dh]
-    float *q = v + n;                  // [16][dh]
-    float *A = q + ATT_ROWS * dh;      // [16][M]
-    float *o = A + ATT_ROWS * M;       // [16][dh]
-    for (int i = tid; i < n; i += 256) ss[i] = s[(int64_t)h * n + i];
+    const int dp = (dh + 3) & ~3, kld = dp + 4;
+    float *ss = sm;                // [M][dp]
+    float *k = ss + M * dp;        // [M][dp + 4]: the rows' lanes fall on different banks
+    float *v = k + M * kld;        // [M][dp]
+    float *q = v + M * dp;         // [16][dp]
+    float *A = q + ATT_ROWS * dp;  // [16][M]
+    float *o = A + ATT_ROWS * M;   // [16][dp]
+    for (int i = tid; i < M * dp; i += 256) {
+        const int m = i / dp, u = i - m * dp;
+        ss[i] = u < dh ? s[((int64_t)h * M + m) * dh + u] : 0.f;
+    }
+    if (dp != dh)  // columns past dh of q, k and v are read as part of four floats
+        for (int i = tid; i < M * (dp - dh); i += 256) {
+            const int m = i / (dp - dh), u = dh + i - m * (dp - dh);
+            k[m * kld + u] = 0.f;
+            v[m * dp + u] = 0.f;
+            if (m < ATT_ROWS) q[m * dp + u] = o[m * dp + u] = 0.f;
+        }
     __syncthreads();
-    const float *wq = Wq + (int64_t)h * dh * dh, *wk = Wk + (int64_t)h * dh * dh, *wv = Wv + (int64_t)h * dh * dh;
+    const int64_t wh = (int64_t)h * dh * dh;
     const int groups = 256 / dh, rg = tid / dh, j = tid - rg * dh;
     if (rg < groups) {
-        for (int mb = rg; mb < M; mb += groups * ATT_KV) {
-            float ak[ATT_KV], av[ATT_KV];
-#pragma unroll
-            for (int r = 0; r < ATT_KV; ++r) ak[r] = av[r] = 0.f;
-#pragma unroll 8
-            for (int u = 0; u < dh; ++u) {
-                const float a = wk[u * dh + j], b = wv[u * dh + j];
-#pragma unroll
-                for (int r = 0; r < ATT_KV; ++r) {
-                    const int m = mb + r * groups;
-                    const float x = ss[(m < M ? m : 0) * dh + u];
-                    ak[r] = fmaf(x, a, ak[r]);
-                    av[r] = fmaf(x, b, av[r]);
-                }
-            }
-#pragma unroll
-            for (int r = 0; r < ATT_KV; ++r) {
-                const int m = mb + r * groups;
-                if (m < M) {
-                    k[m * kld + j] = ak[r];
-                    v[m * dh + j] = av[r];
-                }
-            }
-        }
-        for (int r = rg; r < ATT_ROWS; r += groups) {
-            float aq = 0.f;
-#pragma unroll 8
-            for (int u = 0; u < dh; ++u) aq = fmaf(ss[(m0 + r) * dh + u], wq[u * dh + j], aq);
-            q[r * dh + j] = aq;
-        }
+        token_rows<2>(ss, M, rg, groups, dh, dp, j, {Wk + wh, Wv + wh}, {k, v}, {kld, dp});
+        token_rows<1>(ss + m0 * dp, ATT_ROWS, rg, groups, dh, dp, j, {Wq + wh}, {q}, {dp});
     }
     __syncthreads();
     // Row r's scores and softmax on the 16 lanes of one DPP row.
@@ -209,7 +220,10 @@ __global__ __launch_bounds__(256) void k_attend(const float *__restrict__ s, con
         float mx = -INFINITY;
         for (int b = l; b < M; b += 16) {
             float acc = 0.f;
-            for (int u = 0; u < dh; ++u) acc = fmaf(q[r * dh + u], k[b * kld + u], acc);
+#pragma unroll 4
+            for (int u = 0; u < dp; u += 4)
+                acc = dot4(acc, *reinterpret_cast<const float4 *>(q + r * dp + u),
+                           *reinterpret_cast<const float4 *>(k + b * kld + u));
             acc *= scale;
             A[r * M + b] = acc;
             mx = fmaxf(mx, acc);
@@ -225,16 +239,33 @@ __global__ __launch_bounds__(256) void k_attend(const float *__restrict__ s, con
         for (int b = l; b < M; b += 16) A[r * M + b] /= sum;
     }
     __syncthreads();
-    for (int jj = l; jj < dh; jj += 16) {
-        float acc = 0.f;
-#pragma unroll 8
-        for (int b = 0; b < M; ++b) acc = fmaf(A[r * M + b], v[b * dh + jj], acc);
-        o[r * dh + jj] = acc;
+    for (int j4 = 4 * l; j4 < dp; j4 += 64) {
+        float4 acc{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+        for (int b = 0; b < M; b += 4) {
+            const float4 a = *reinterpret_cast<const float4 *>(A + r * M + b);
+            const float aw[4] = {a.x, a.y, a.z, a.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float4 x = *reinterpret_cast<const float4 *>(v + (b + i) * dp + j4);
+                acc.x = fmaf(aw[i], x.x, acc.x);
+                acc.y = fmaf(aw[i], x.y, acc.y);
+                acc.z = fmaf(aw[i], x.z, acc.z);
+                acc.w = fmaf(aw[i], x.w, acc.w);
+            }
+        }
+        *reinterpret_cast<float4 *>(o + r * dp + j4) = acc;
+        const float av[4] = {acc.x, acc.y, acc.z, acc.w};
         const int m = m0 + r;
-        out.s1[((int64_t)h * M + m) * dh + jj] = acc;
-        if (out.sf) {
-            const int mm = m & 31, t = (mm >> 4) * 4 + (mm & 3), lane = ((mm & 15) >> 2) * 16 + jj;
-            store_elem(out.sf + (((int64_t)h * (M / 32) + (m >> 5)) * 64 + lane) * 8 + t, acc);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int jj = j4 + i;
+            if (jj >= dh) break;
+            out.s1[((int64_t)h * M + m) * dh + jj] = av[i];
+            if (out.sf) {
+                const int mm = m & 31, t = (mm >> 4) * 4 + (mm & 3), lane = ((mm & 15) >> 2) * 16 + jj;
+                store_elem(out.sf + (((int64_t)h * (M / 32) + (m >> 5)) * 64 + lane) * 8 + t, av[i]);
+            }
         }
     }
     __syncthreads();
@@ -244,19 +275,22 @@ __global__ __launch_bounds__(256) void k_attend(const float *__restrict__ s, con
         float acc[ATT_ROWS];
 #pragma unroll
         for (int i = 0; i < ATT_ROWS; ++i) acc[i] = 0.f;
-#pragma unroll 8
-        for (int u = 0; u < dh; ++u) {
-            const float w = W3[(int64_t)(h * dh + u) * C + c];
+        const float *w3 = W3 + (int64_t)h * dh * C + c;
+#pragma unroll 4
+        for (int u = 0; u < dp; u += 4) {
+            const float *p = w3 + (int64_t)u * C;
+            const float4 w{p[0], u + 1 < dh ? p[C] : 0.f, u + 2 < dh ? p[2 * C] : 0.f, u + 3 < dh ? p[3 * C] : 0.f};
 #pragma unroll
-            for (int i = 0; i < ATT_ROWS; ++i) acc[i] = fmaf(o[i * dh + u], w, acc[i]);
+            for (int i = 0; i < ATT_ROWS; ++i) acc[i] = dot4(acc[i], *reinterpret_cast<const float4 *>(o + i * dp + u), w);
         }
         const float bb = b3 ? b3[c] * bscale : 0.f;
 #pragma unroll
         for (int i = 0; i < ATT_ROWS; ++i) {
             const int m = m0 + i;
             out.Z[((int64_t)h * M + m) * C + c] = acc[i];
-            if (out.rows) {
-                store_elem(out.zp + ((int64_t)h * M + m) * C + c, acc[i] + bb);
+            if (out.rt) {
+                store_parts((bf16_t *)out.zp, rt_z_index(h, m, c, CT, M, RtGroup(out.rt, M), RT_NP<T>), acc[i] + bb,
+                            RT_NP<T>);
             } else {
                 const int64_t at = zp_index(h, m, c, CT, KM);
                 store_elem(out.zp + at, acc[i] + bb);
