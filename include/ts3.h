@@ -58,8 +58,8 @@ typedef enum { TS3_ACCUM_FP32 = 0, TS3_ACCUM_FP64 = 1 } ts3_accum;
  *                (128,16), (128,32), (128,64)}, and (256,64) with bf16
  *                storage and even H.  Any other C and M that are multiples
  *                of 16 with C <= 512 and M <= 256 run on runtime-shape
- *                vector kernels (same results up to float32 rounding order,
- *                same tiling independence, far slower; no backward).  In
+ *                kernels (same results up to float32 rounding order,
+ *                same tiling independence, slower; no backward).  In
  *                every case (5*M*dh + M*M) * 4 bytes <= 160 KiB (the
  *                token-attention working set); otherwise TS3_ERR_UNSUPPORTED.
  *  temperature : tau > 0 of the slice softmax; +inf gives uniform weights.
@@ -68,8 +68,9 @@ typedef enum { TS3_ACCUM_FP32 = 0, TS3_ACCUM_FP64 = 1 } ts3_accum;
  *  io_dtype    : ts3_dtype of x and out.  TS3_BF16 stores bf16 and computes
  *                the slice-weight and contraction products on bf16 matrix
  *                cores with float32 accumulation; TS3_FP32 uses float32
- *                matrix cores throughout.  The runtime-shape kernels read
- *                either storage type and compute in float32 on vector units.
+ *                matrix cores throughout.  The runtime-shape kernels keep the
+ *                slice weights and, for TS3_FP32, every operand to float32
+ *                precision, as sums of three bf16 parts on bf16 matrix cores.
  *  group_span  : Q, points per accumulation span (1 <= Q <= 2^30).  Pass 1
  *                reduces each span to partials of its consecutive parts and sums
  *                them in index order, so results do not depend on how the mesh
