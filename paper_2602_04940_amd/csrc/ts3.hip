@@ -22,6 +22,8 @@
 #include "ts3_pass1pcp.h"
 #include "ts3_pass2pc.h"
 #include "ts3_backward.h"
+#include "ts3_sum3.h"
+#include "ts3_fp32.h"
 #include "ts3_pass2.h"
 #include "ts3_small.h"
 #include "ts3_token.h"
@@ -73,11 +75,10 @@ struct Kernels {
     hipError_t (*pass2)(const void *, int64_t, int32_t, int32_t, int32_t, const void *, const float *, const void *,
                         void *, hipStream_t);
     // Backward (float32 storage only; NULL for bfloat16).
-    void (*bw_head)(const float *, const float *, int64_t, int64_t, SpanGeo, int32_t, int32_t, const float *,
+    void (*bw_head)(const float *, const float *, int64_t, int64_t, SpanGeo, int32_t, int32_t, const void *,
                     const float *, float *, hipStream_t);
-    void (*bw_dx)(const float *, const float *, int64_t, int32_t, const float *, const float *, const float *,
-                  const float *, const float *, const float *, const float *, float, float *, float *,
-                  hipStream_t);
+    void (*bw_dx)(const float *, const float *, int64_t, int32_t, const void *, const float *, const BwOperands &,
+                  const float *, float, float *, float *, hipStream_t);
     void (*bw_dw2)(const float *, const float *, int64_t, int64_t, SpanGeo, int32_t, int32_t, float *,
                    hipStream_t);
     // Pass 1 in the projected form (bfloat16, C = 128, head width 16): x, n,
@@ -94,12 +95,15 @@ struct Kernels {
 template <typename T, int C, int M>
 hipError_t launch_pass1(const void *x, int64_t n, int64_t span0, SpanGeo geo, int32_t nspan, int32_t H, int32_t, int32_t,
                   const void *w2p, const float *b2s, float *partials, hipStream_t st) {
-    if constexpr (sizeof(T) == 2 && C == 256) {
+    if constexpr (sizeof(T) == 4) {
+        hipLaunchKernelGGL((k_sum3<C, M, SUM3_X>), dim3(nspan * H), dim3(512), 0, st, (const float *)x, (const float *)x, n,
+                           span0, geo, nspan, H, (const bf16_t *)w2p, b2s, partials);
+    } else if constexpr (C == 256) {
         // Wide rows: two heads per workgroup, two producer and two consumer
         // waves per head (H is even for every wide shape check_desc accepts).
         hipLaunchKernelGGL((k_slice_accumulate_pcw<C, M>), dim3(nspan * (H / 2)), dim3(512), 0, st,
                            (const bf16_t *)x, n, span0, geo, nspan, H, (const bf16_t *)w2p, b2s, partials);
-    } else if constexpr (sizeof(T) == 2 && M >= 32 && C == 128) {
+    } else if constexpr (M >= 32 && C == 128) {
         // Two heads per workgroup whenever H is even (independently of the
         // span count, so that every tiling sums a span the same way); the one
         // odd case, H = 1, takes the generic kernel.
@@ -137,8 +141,6 @@ int device_cu_count() {
 template <typename T, int C, int M>
 hipError_t launch_pass2(const void *x, int64_t n, int32_t H, int32_t, int32_t, const void *w2p, const float *b2s,
                         const void *zp, void *out, hipStream_t st) {
-    using Cfg = Pass2Cfg<T, C, M>;
-    const int64_t nblk = (n + Cfg::POINTS_PER_WG - 1) / Cfg::POINTS_PER_WG;
     if constexpr (sizeof(T) == 2 && C == 256) {
         // Producer and consumer waves, heads streamed through LDS, persistent
         // workgroups of 128-point blocks.  (At C = 128 the same kernel ran
@@ -185,37 +187,41 @@ hipError_t launch_pass2(const void *x, int64_t n, int32_t H, int32_t, int32_t, c
         // bounds H*M*C); a shape that does not has no decoding kernel.
         return hipErrorInvalidConfiguration;
     } else {
-        hipLaunchKernelGGL((k_deslice<T, C, M>), dim3((unsigned)nblk), dim3(256), 0, st, (const T *)x, n, H,
-                           (const T *)w2p, b2s, (const T *)zp, (T *)out);
+        // Blocks of 256 points; of 128 where those fill no more than one round of
+        // compute units (half the time per block, and half the chip would idle).
+        const int64_t cus = device_cu_count();
+        auto launch = [&](auto nt) {
+            constexpr int NT = decltype(nt)::value;
+            const int64_t nblk = (n + Deslice3Cfg<C, M, NT>::PTS - 1) / Deslice3Cfg<C, M, NT>::PTS;
+            hipLaunchKernelGGL((k_deslice3<C, M, NT>), dim3((unsigned)std::min(nblk, cus)), dim3(512), 0, st,
+                               (const float *)x, n, H, (const bf16_t *)w2p, b2s, (const bf16_t *)zp, (float *)out);
+        };
+        if (n <= cus * Deslice3Cfg<C, M, 1>::PTS) launch(std::integral_constant<int, 1>{});
+        else launch(std::integral_constant<int, 2>{});
         return hipSuccess;
     }
 }
 
 template <int C, int M>
 void launch_bw_head(const float *x, const float *g, int64_t n, int64_t span0, SpanGeo geo, int32_t nspan,
-                    int32_t H, const float *w2p, const float *b2s, float *partials, hipStream_t st) {
-    const int64_t places = (int64_t)BW_XCDS * ((nspan + BW_XCDS - 1) / BW_XCDS) * H;
-    hipLaunchKernelGGL((k_bw_head<C, M>), dim3((unsigned)places), dim3(512), 0, st, x, g, n, span0, geo, nspan, H,
-                       w2p, b2s, partials);
+                    int32_t H, const void *w2p, const float *b2s, float *partials, hipStream_t st) {
+    hipLaunchKernelGGL((k_sum3<C, M, SUM3_G>), dim3(nspan * H), dim3(512), 0, st, x, g, n, span0, geo, nspan, H,
+                       (const bf16_t *)w2p, b2s, partials);
 }
 
 template <int C, int M>
 void launch_bw_dw2(const float *x, const float *dzs, int64_t n, int64_t span0, SpanGeo geo, int32_t nspan, int32_t H,
                    float *partials, hipStream_t st) {
-    const int64_t places = (int64_t)BW_XCDS * ((nspan + BW_XCDS - 1) / BW_XCDS) * H;
-    hipLaunchKernelGGL((k_bw_dw2<C, M>), dim3((unsigned)places), dim3(512), 0, st, x, dzs, n, span0, geo, nspan, H,
-                       partials);
+    hipLaunchKernelGGL((k_sum3<C, M, SUM3_STORED>), dim3(nspan * H), dim3(512), 0, st, dzs, x, n, span0, geo, nspan, H,
+                       (const bf16_t *)nullptr, (const float *)nullptr, partials);
 }
 
-constexpr int BW_DX_TILES_PER_WAVE = 4;  // each L2 A fragment serves four 16-point tiles
-
 template <int C, int M>
-void launch_bw_dx(const float *x, const float *g, int64_t n, int32_t H, const float *w2p, const float *b2s,
-                  const float *W2, const float *Z, const float *dsr, const float *dsT, const float *dd,
-                  float inv_tau, float *dx, float *dzs, hipStream_t st) {
-    constexpr int NT = BW_DX_TILES_PER_WAVE;
-    hipLaunchKernelGGL((k_bw_dx<C, M, NT>), dim3((unsigned)((n + 64 * NT - 1) / (64 * NT))), dim3(256), 0, st, x, g,
-                       n, H, w2p, b2s, W2, Z, dsr, dsT, dd, inv_tau, dx, dzs);
+void launch_bw_dx(const float *x, const float *g, int64_t n, int32_t H, const void *w2p, const float *b2s,
+                  const BwOperands &op, const float *dd, float inv_tau, float *dx, float *dzs, hipStream_t st) {
+    constexpr int PTS = BwDx3Cfg<C, M>::PTS;
+    hipLaunchKernelGGL((k_bw_dx3<C, M>), dim3((unsigned)((n + PTS - 1) / PTS)), dim3(512), 0, st, x, g, n, H,
+                       (const bf16_t *)w2p, b2s, op, dd, inv_tau, dx, dzs);
 }
 
 template <int C, int M>
@@ -348,16 +354,16 @@ bool find_any_kernels(int dtype, int C, int M, Kernels *k) {
     return true;
 }
 
-// Bytes of the prepared W2' and Z buffers (fragments of the storage type, or the
-// runtime-shape kernels' 16-bit parts).
+// Bytes of the prepared W2' and Z buffers (bf16 fragments, or parts: three for
+// float32 storage).
 int64_t w2p_bytes(const ts3_desc &d, bool rt) {
-    const int es = d.io_dtype == TS3_BF16 ? 2 : 4, np = d.io_dtype == TS3_BF16 ? 1 : 3;
-    return rt ? (int64_t)d.H * d.M * rt_ck(d.C) * 32 * 2 * np : (int64_t)d.H * d.M * d.C * es;
+    const int np = d.io_dtype == TS3_BF16 ? 1 : 3;
+    return (int64_t)d.H * d.M * (rt ? rt_ck(d.C) * 32 : d.C) * 2 * np;
 }
 int64_t zp_bytes(const ts3_desc &d, bool rt) {
-    const int es = d.io_dtype == TS3_BF16 ? 2 : 4, np = d.io_dtype == TS3_BF16 ? 1 : 3;
+    const int np = d.io_dtype == TS3_BF16 ? 1 : 3;
     const int KM = d.M >= 32 ? d.M / 32 : 1;
-    if (!rt) return (int64_t)d.H * (d.C / 16) * KM * 512 * es;
+    if (!rt) return (int64_t)d.H * (d.C / 16) * KM * 512 * 2 * np;
     const RtGroup gr(rt_pass2(np, d.C, d.M).GH, d.M);
     return (int64_t)((d.H + gr.GH - 1) / gr.GH) * (d.C / 16) * gr.KG * 512 * 2 * np;
 }
@@ -376,8 +382,9 @@ struct ts3_state {
     // device buffers
     float *partials = nullptr, *runs = nullptr, *s_raw = nullptr, *dsum = nullptr, *s = nullptr,
           *s1 = nullptr, *Z = nullptr, *b2s = nullptr, *b3 = nullptr;
-    // backward: dZ, ds_raw [H][M][C], ds_raw transposed [H][C][M], dd [H][M], dW2^T [H][M][C]
-    float *bdZ = nullptr, *bdsr = nullptr, *bdsT = nullptr, *bdd = nullptr, *bdW2T = nullptr;
+    // backward: dZ, ds_raw [H][M][C], dd [H][M], dW2^T [H][M][C]
+    float *bdZ = nullptr, *bdsr = nullptr, *bdd = nullptr, *bdW2T = nullptr;
+    void *bop[4] = {nullptr, nullptr, nullptr, nullptr};  // BwOperands: zr, ds, w2t, dst (float32 only)
     // backward: dz [H][points][M] of one tile, allocated by the first backward
     // whose tile needs more than it holds
     float *bdz = nullptr;
@@ -497,8 +504,8 @@ ts3_status prep_w2(ts3_state *st, const ts3_weights *w, hipStream_t stream) {
         hipLaunchKernelGGL(k_prep_w2<bf16_t>, dim3(grid2), dim3(256), 0, stream, w->W2, w->b2, scale, d.C,
                            d.H, d.M, (bf16_t *)st->w2p, st->b2s, W1, w1p);
     else
-        hipLaunchKernelGGL(k_prep_w2<float>, dim3(grid2), dim3(256), 0, stream, w->W2, w->b2, scale, d.C,
-                           d.H, d.M, (float *)st->w2p, st->b2s, W1, w1p);
+        hipLaunchKernelGGL(k_prep_w2x, dim3(grid2), dim3(256), 0, stream, w->W2, w->b2, scale, d.C, d.H, d.M,
+                           (bf16_t *)st->w2p, st->b2s);
     LAUNCH_CHECK("prep_w2");
     if (W1) st->W1 = W1;
     st->W2 = w->W2;
@@ -519,8 +526,7 @@ ts3_status prep_z(ts3_state *st, hipStream_t stream) {
         hipLaunchKernelGGL(k_prep_z<bf16_t>, dim3(grid), dim3(256), 0, stream, st->Z, st->b3, d.C, d.H, d.M,
                            (bf16_t *)st->zp);
     else
-        hipLaunchKernelGGL(k_prep_z<float>, dim3(grid), dim3(256), 0, stream, st->Z, st->b3, d.C, d.H, d.M,
-                           (float *)st->zp);
+        hipLaunchKernelGGL(k_prep_z3, dim3(grid), dim3(256), 0, stream, st->Z, st->b3, d.C, d.H, d.M, (bf16_t *)st->zp);
     LAUNCH_CHECK("prep_z");
     return TS3_OK;
 }
@@ -549,8 +555,8 @@ ts3_status ts3_state_free(ts3_state *st) {
     if (!st) return TS3_OK;
     hipError_t e = hipDeviceSynchronize();
     void *bufs[] = {st->partials, st->runs, st->s_raw, st->dsum, st->s,    st->s1,    st->Z,
-                    st->b2s,      st->b3,   st->w2p,   st->zp,   st->bdZ,  st->bdsr,  st->bdsT,
-                    st->bdd,      st->bdW2T, st->bdz,  st->sfp,  st->w3p,   st->w1p};
+                    st->b2s,      st->b3,   st->w2p,   st->zp,   st->bdZ,  st->bdsr,  st->bop[0], st->bop[1],
+                    st->bop[2], st->bop[3], st->bdd, st->bdW2T, st->bdz,  st->sfp,  st->w3p,   st->w1p};
     for (void *b : bufs)
         if (b) (void)hipFree(b);
     if (st->ev_fork) (void)hipEventDestroy(st->ev_fork);
@@ -608,7 +614,11 @@ ts3_status ts3_state_create(const ts3_desc *desc, ts3_state **out) {
         {&st->zp, zp_bytes(d, st->k.rt)},
         {(void **)&st->bdZ, HM * d.C * 4},
         {(void **)&st->bdsr, HM * d.C * 4},
-        {(void **)&st->bdsT, HM * d.C * 4},
+        // operand parts of the dx pass, where there is one
+        {&st->bop[0], st->k.bw_dx ? w2p_bytes(d, false) : 0},
+        {&st->bop[1], st->k.bw_dx ? w2p_bytes(d, false) : 0},
+        {&st->bop[2], st->k.bw_dx ? zp_bytes(d, false) : 0},
+        {&st->bop[3], st->k.bw_dx ? zp_bytes(d, false) : 0},
         {(void **)&st->bdd, HM * 4},
         {(void **)&st->bdW2T, HM * d.C * 4},
         // slice-state pass 2 (head width 16 only; empty otherwise)
@@ -960,7 +970,7 @@ ts3_status ts3_layer_backward(ts3_state *st, const ts3_weights *w, const void *x
     const float inv_tau = 1.f / d.temperature;
     const int64_t HM = (int64_t)d.H * d.M;
     const float *xf = (const float *)x, *gf = (const float *)g;
-    const float *w2p = (const float *)st->w2p;
+    const void *w2p = st->w2p;
     const int64_t nt_max = std::min(tile, N);
     if (st->bdz_points < nt_max) {
         // dz of one tile, [H][points][M]; kept by the state for later calls
@@ -997,15 +1007,19 @@ ts3_status ts3_layer_backward(ts3_state *st, const ts3_weights *w, const void *x
     if (lds > (size_t)ATTN_LDS_MAX) return fail(TS3_ERR_UNSUPPORTED, "token backward needs %zu bytes of LDS", lds);
     HIP_TRY(hipFuncSetAttribute((const void *)k_bw_token, hipFuncAttributeMaxDynamicSharedMemorySize, ATTN_LDS_MAX));
     hipLaunchKernelGGL(k_bw_token, dim3(d.H), dim3(256), lds, hs, st->s_raw, st->dsum, st->s, st->s1, st->bdZ,
-                       w->W1, w->Wq, w->Wk, w->Wv, w->W3, d.C, d.H, d.M, d.dh, d.eps, st->bdsr, st->bdsT, st->bdd,
+                       w->W1, w->Wq, w->Wk, w->Wv, w->W3, d.C, d.H, d.M, d.dh, d.eps, st->bdsr, st->bdd,
                        gr->dW1, gr->db1, gr->dWq, gr->dWk, gr->dWv, gr->dW3, gr->db3);
     LAUNCH_CHECK("token backward");
+    const BwOperands op{(bf16_t *)st->bop[0], (bf16_t *)st->bop[1], (bf16_t *)st->bop[2], (bf16_t *)st->bop[3]};
+    hipLaunchKernelGGL(k_bw_prep, dim3((unsigned)std::min<int64_t>((HM * d.C + 255) / 256, 4096)), dim3(256), 0, hs,
+                       st->Z, st->bdsr, w->W2, d.C, d.H, d.M, op);
+    LAUNCH_CHECK("backward operands");
     // Per tile: dx (which stores dz), then the tile's span partials of dW2^T
     // and db2 from the stored dz.
     for (int64_t t0 = 0; t0 < N; t0 += tile) {
         const int64_t nt = std::min(tile, N - t0);
-        st->k.bw_dx(xf + t0 * d.C, gf + t0 * d.C, nt, d.H, w2p, st->b2s, w->W2, st->Z, st->bdsr, st->bdsT, st->bdd,
-                    inv_tau, (float *)dx + t0 * d.C, st->bdz, hs);
+        st->k.bw_dx(xf + t0 * d.C, gf + t0 * d.C, nt, d.H, w2p, st->b2s, op, st->bdd, inv_tau, (float *)dx + t0 * d.C,
+                    st->bdz, hs);
         LAUNCH_CHECK("backward dx pass");
         st->k.bw_dw2(xf + t0 * d.C, st->bdz, nt, t0 / Q * st->geo.S, st->geo, (int32_t)st->geo.parts(nt), d.H,
                      st->partials, hs);

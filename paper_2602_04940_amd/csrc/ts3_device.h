@@ -24,13 +24,6 @@ struct bf16_t {
 // An 8-slot operand fragment for one K32 step.
 template <typename T> struct Frag;
 
-template <> struct Frag<float> {
-    float v[8];
-    __device__ __forceinline__ void set(int t, float x) { v[t] = x; }
-    // slots t and t+1 (t even) from two floats
-    __device__ __forceinline__ void set2(int t, float a, float b) { v[t] = a; v[t + 1] = b; }
-};
-
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
 template <> struct Frag<bf16_t> {
@@ -64,11 +57,6 @@ __device__ __forceinline__ void mma(f32x4 &acc, const Frag<f16_t> &a, const Frag
 __device__ __forceinline__ void mma(f32x4 &acc, const Frag<bf16_t> &a, const Frag<bf16_t> &b) {
     acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, b.v, acc, 0, 0, 0);
 }
-__device__ __forceinline__ void mma(f32x4 &acc, const Frag<float> &a, const Frag<float> &b) {
-#pragma unroll
-    for (int t = 0; t < 8; ++t) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[t], b.v[t], acc, 0, 0, 0);
-}
-
 // Float32 operands as three bfloat16 parts: v = p[0] + p[1] + p[2] (rounded
 // value, rounded remainder, remainder of that; 8 + 8 + 8 significant bits, so
 // the sum is v exactly while no part underflows).  A product of two such
@@ -107,30 +95,16 @@ __device__ __forceinline__ f32x4 mma_bf16(const bf16x8 &a, const bf16x8 &b, cons
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-// Load the 8 consecutive storage elements at p (16 B for bf16, 32 B for fp32).
+// Load the 8 consecutive storage elements at p (16 B).
 __device__ __forceinline__ void load8(Frag<bf16_t> &f, const bf16_t *p) {
     f.v = *reinterpret_cast<const bf16x8 *>(p);
-}
-__device__ __forceinline__ void load8(Frag<float> &f, const float *p) {
-    const float4 a = reinterpret_cast<const float4 *>(p)[0];
-    const float4 b = reinterpret_cast<const float4 *>(p)[1];
-    f.v[0] = a.x; f.v[1] = a.y; f.v[2] = a.z; f.v[3] = a.w;
-    f.v[4] = b.x; f.v[5] = b.y; f.v[6] = b.z; f.v[7] = b.w;
 }
 __device__ __forceinline__ void zero8(Frag<bf16_t> &f) {
     f.v = bf16x8{};
 }
-__device__ __forceinline__ void zero8(Frag<float> &f) {
-#pragma unroll
-    for (int t = 0; t < 8; ++t) f.v[t] = 0.f;
-}
 __device__ __forceinline__ void ones8(Frag<bf16_t> &f) {
 #pragma unroll
     for (int t = 0; t < 8; ++t) f.v[t] = (__bf16)1.0f;
-}
-__device__ __forceinline__ void ones8(Frag<float> &f) {
-#pragma unroll
-    for (int t = 0; t < 8; ++t) f.v[t] = 1.f;
 }
 
 // Storage element <-> float.
@@ -144,7 +118,6 @@ __device__ __forceinline__ uint16_t elem_bits(const Frag<bf16_t> &f, int t) {
     const u32x4 u = __builtin_bit_cast(u32x4, f.v);
     return (uint16_t)((t & 1) ? (u[t >> 1] >> 16) : (u[t >> 1] & 0xffffu));
 }
-__device__ __forceinline__ float elem_f32(const Frag<float> &f, int t) { return f.v[t]; }
 
 // Cross-lane reductions among the 16 lanes of a DPP row (all lanes get the result).
 template <int CTRL> __device__ __forceinline__ float dpp(float v) {

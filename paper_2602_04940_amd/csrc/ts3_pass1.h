@@ -24,10 +24,10 @@
 //            d[m] += sum_p w[p][m] (A = w^T against a ones operand), with
 //            ds_read_b64_tr_b16 giving operands whose K slots hold points:
 //            slot (g, t) <-> point row 8g+t.
-// With bf16 storage the block loop is unrolled by the ring depth (every tile
+// The block loop is unrolled by the ring depth (every tile
 // address is then a fixed per-lane offset plus an immediate), and block b-1's
 // contraction (matrix cores) is interleaved with block b's softmax (vector
-// ALU).  fp32 storage, the parity path, runs the steps of a block back to back.
+// ALU).
 #pragma once
 #include <type_traits>
 #include "ts3_device.h"
@@ -39,12 +39,12 @@ template <typename T, int C, int M> struct Pass1Cfg {
     static constexpr int MT = M / 16;      // 16-slice tiles
     static constexpr int CK = C / 32;      // K32 steps over channels
     static constexpr int WAVES = 4;
-    static constexpr bool PIPE = sizeof(T) == 2;
+    static_assert(sizeof(T) == 2, "float32 storage has its own kernel");
     static constexpr int XROW = C * (int)sizeof(T);    // bytes per point row of x
     static constexpr int WROW = M * (int)sizeof(T);    // bytes per point row of w
     static constexpr int XTILE = 32 * XROW;
     static constexpr int WTILE = 32 * WROW;
-    static constexpr int NS = PIPE ? 3 : 1;            // ring depth (x and w tiles)
+    static constexpr int NS = 3;                       // ring depth (x and w tiles)
     static constexpr int ROWS_PER_LOAD = 1024 / XROW;  // rows per 1 KB wave copy
     static constexpr int LOADS = 32 / ROWS_PER_LOAD;   // wave copies per block
     static constexpr int WAVE_BYTES = NS * (XTILE + WTILE);
@@ -114,24 +114,13 @@ __device__ __forceinline__ const unsigned char *tr_addr(const unsigned char *til
     const int byte = (col0 + 4 * (j & 3)) * 2;
     return tile + (XT ? xoff<ROWB>(r, byte) : woff<ROWB>(r, byte));
 }
-// fp32 tiles: the same fragment read element by element (fp32 storage is the
-// parity path, not the fast one).
-template <int ROWB, bool XT>
-__device__ __forceinline__ void tr_frag_f32(Frag<float> &f, const unsigned char *tile, int g, int col0, int i) {
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-        const int o = XT ? xoff<ROWB>(8 * g + t, (col0 + i) * 4) : woff<ROWB>(8 * g + t, (col0 + i) * 4);
-        f.v[t] = *reinterpret_cast<const float *>(tile + o);
-    }
-}
-
 template <int V> using ic = std::integral_constant<int, V>;
 
 // x       : tile base, [n_tile][C] storage elements
 // n_tile  : points in this tile (tile starts on a span boundary)
 // span0   : global index of the tile's first span
-// Q       : points per span
-// nspan   : spans in this tile (= ceil(n_tile / Q)); grid = nspan * H
+// geo     : the spans and the parts they are summed in
+// nspan   : parts in this launch; grid = nspan * H
 // w2p     : prepared W2' fragments [H][MT][CK][64 lanes][8]
 // b2s     : W2'-scaled bias [H*M]
 // partials: [span][H][M][C+1] float32
@@ -222,76 +211,8 @@ __global__ __launch_bounds__(256, 1) void k_slice_accumulate(
     // assume its own copies are the only memory operations in flight.
     wait_vmcnt<0>();
 
-    // Logits for the block in x slot SL: L[mt][pt] lane (g, li) holds slices
-    // 16*mt + 4*g .. +3 of point row prow(pt, li).  The B operand (channels
-    // 32*kc + 8*g .. +8 of that row) is read just before use.
-    auto logits = [&](auto slot, f32x4 (&L)[MT][2]) {
-        constexpr int SL = decltype(slot)::value;
-        const unsigned char *tile = xring + SL * XTILE;
-#pragma unroll
-        for (int pt = 0; pt < 2; ++pt) {
-            const int R = prow(pt, li);
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) L[mt][pt] = bias[mt];
-#pragma unroll
-            for (int kc = 0; kc < CK; ++kc) {
-                const int byte = (kc * 32 + g * 8) * (int)sizeof(T);
-                Frag<T> xb;
-                if constexpr (sizeof(T) == 2) {
-                    xb.v = *reinterpret_cast<const bf16x8 *>(tile + xoff<XROW>(R, byte));
-                } else {
-                    const float4 a = *reinterpret_cast<const float4 *>(tile + xoff<XROW>(R, byte));
-                    const float4 b = *reinterpret_cast<const float4 *>(tile + xoff<XROW>(R, byte + 16));
-                    xb.v[0] = a.x; xb.v[1] = a.y; xb.v[2] = a.z; xb.v[3] = a.w;
-                    xb.v[4] = b.x; xb.v[5] = b.y; xb.v[6] = b.z; xb.v[7] = b.w;
-                }
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) mma(L[mt][pt], w2[mt][kc], xb);
-            }
-        }
-    };
-    // S += w^T x, d += sum_p w for the block in slot SL.
-    auto contract = [&](auto slot) {
-        constexpr int SL = decltype(slot)::value;
-        const unsigned char *xt = xring + SL * XTILE, *wt = wring + SL * WTILE;
-        Frag<T> a[MT];
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            if constexpr (sizeof(T) == 2) tr_frag<WROW>(a[mt], tr_addr<WROW, false>(wt, g, mt * 16, li));
-            else tr_frag_f32<WROW, false>(a[mt], wt, g, mt * 16, li);
-        }
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) mma(D[mt], a[mt], ones);
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
-            Frag<T> b;
-            if constexpr (sizeof(T) == 2) tr_frag<XROW>(b, tr_addr<XROW, true>(xt, g, ct * 16, li));
-            else tr_frag_f32<XROW, true>(b, xt, g, ct * 16, li);
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) mma(S[mt][ct], a[mt], b);
-        }
-    };
-    // exp2 of the logits in place; per point the reciprocal row sum (zero for
-    // padding points).  Returns false if a row left the unshifted window.
-    auto softmax_fast = [&](f32x4 (&L)[MT][2], float (&inv)[2], int valid) {
-        bool ok = true;
-#pragma unroll
-        for (int pt = 0; pt < 2; ++pt) {
-            float sum = 0.f;
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const float e = fast_exp2(L[mt][pt][r]);
-                    L[mt][pt][r] = e;
-                    sum += e;
-                }
-            sum = xrow_sum(sum);
-            ok = ok && softmax_sum_ok(sum);
-            inv[pt] = prow(pt, li) < valid ? fast_rcp(sum) : 0.f;
-        }
-        return ok;
-    };
+    // Max-shifted exp2 of the logits in place; per point the reciprocal row sum (zero
+    // for padding points).
     auto softmax_shifted = [&](f32x4 (&L)[MT][2], float (&inv)[2], int valid) {
 #pragma unroll
         for (int pt = 0; pt < 2; ++pt) {
@@ -313,34 +234,12 @@ __global__ __launch_bounds__(256, 1) void k_slice_accumulate(
             inv[pt] = prow(pt, li) < valid ? fast_rcp(xrow_sum(sum)) : 0.f;
         }
     };
-    // Normalised w rows into w slot SL: lane (g, li) stores slices
-    // 16*mt + 4*g .. +3 of point row prow(pt, li).
-    auto store_w = [&](auto slot, const f32x4 (&E)[MT][2], const float (&inv)[2]) {
-        constexpr int SL = decltype(slot)::value;
-        unsigned char *tile = wring + SL * WTILE;
-#pragma unroll
-        for (int pt = 0; pt < 2; ++pt)
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                const int R = prow(pt, li), byte = (mt * 16 + g * 4) * (int)sizeof(T);
-                const float a0 = E[mt][pt][0] * inv[pt], a1 = E[mt][pt][1] * inv[pt];
-                const float a2 = E[mt][pt][2] * inv[pt], a3 = E[mt][pt][3] * inv[pt];
-                if constexpr (sizeof(T) == 2) {
-                    typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
-                    *reinterpret_cast<bf16x4 *>(tile + woff<WROW>(R, byte)) =
-                        bf16x4{(__bf16)a0, (__bf16)a1, (__bf16)a2, (__bf16)a3};
-                } else {
-                    *reinterpret_cast<float2 *>(tile + woff<WROW>(R, byte)) = float2{a0, a1};
-                    *reinterpret_cast<float2 *>(tile + woff<WROW>(R, byte + 8)) = float2{a2, a3};
-                }
-            }
-    };
     auto block_valid = [&](int j) {
         const int64_t left = p_end - (p_begin + ((int64_t)(wave + Cfg::WAVES * j) << 5));
         return (int)(left < 32 ? left : 32);
     };
 
-    if constexpr (Cfg::PIPE) {
+    {
         // bf16 tile addresses as (per-lane base) ^ (tile-index constant) +
         // (immediate): with 16-bit elements a tile step moves whole chunks or
         // slots whose index bits do not overlap the base's, and neither
@@ -497,24 +396,6 @@ __global__ __launch_bounds__(256, 1) void k_slice_accumulate(
             case 0: contract16(ic<0>{}); break;
             case 1: contract16(ic<1>{}); break;
             default: contract16(ic<2>{}); break;
-        }
-    } else {
-        for (int j = 0; j < nmine; ++j) {
-            const int valid = block_valid(j);
-            issue_x(j, ic<0>{});
-            wait_vmcnt<0>();
-            asm volatile("" ::: "memory");
-            f32x4 L[MT][2];
-            logits(ic<0>{}, L);
-            float inv[2];
-            if (__any(!softmax_fast(L, inv, valid))) {
-                logits(ic<0>{}, L);
-                softmax_shifted(L, inv, valid);
-            }
-            store_w(ic<0>{}, L, inv);
-            asm volatile("" ::: "memory");
-            contract(ic<0>{});
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         }
     }
 

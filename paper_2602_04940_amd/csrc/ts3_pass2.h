@@ -92,7 +92,7 @@ __device__ __forceinline__ void store_rows(const f32x4 (&O)[CT][PT], T *__restri
 }
 
 // One wave block decoded from global-memory fragments with the max-shifted
-// softmax: the generic kernel's body, and the rare fallback of the staged one.
+// softmax: the rare fallback of the staged kernel.
 template <typename T, int C, int M, int PT>
 __device__ void deslice_block_global(const T *__restrict__ x, int64_t n, int64_t p0, int32_t H,
                                      const T *__restrict__ w2p, const float *__restrict__ b2s,
@@ -146,31 +146,6 @@ __device__ void deslice_block_global(const T *__restrict__ x, int64_t n, int64_t
             }
     }
     store_rows<T, CT, PT, C>(O, out, p0, n, g, li);
-}
-
-template <typename T, int C, int M> struct Pass2Cfg {
-    static constexpr int PT = sizeof(T) == 2 ? 4 : 2;  // 16-point tiles per wave block
-    static constexpr int WAVES = 4;
-    static constexpr int POINTS_PER_WG = WAVES * 16 * PT;
-};
-
-// Generic decoding kernel (fp32 storage, and shapes whose weights do not fit
-// the staged kernel's LDS): every fragment comes from global memory.
-// x   : [n][C] storage elements; out: [n][C]
-// w2p : prepared W2' fragments [H][MT][CK][64][8] (also the A = W2'^T layout)
-// b2s : scaled bias [H*M]
-// zp  : prepared Z fragments [H][CT][KM][64][8], b3/H folded in
-template <typename T, int C, int M>
-__global__ __launch_bounds__(256, 1) void k_deslice(const T *__restrict__ x, int64_t n, int32_t H,
-                                                    const T *__restrict__ w2p,
-                                                    const float *__restrict__ b2s,
-                                                    const T *__restrict__ zp, T *__restrict__ out) {
-    using Cfg = Pass2Cfg<T, C, M>;
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int64_t p0 = ((int64_t)blockIdx.x * Cfg::WAVES + wave) * (16 * Cfg::PT);
-    if (p0 >= n) return;
-    deslice_block_global<T, C, M, Cfg::PT>(x, n, p0, H, w2p, b2s, zp, out, lane);
 }
 
 // Staged decoding kernel for 16-bit storage: eight waves (two per SIMD, so one

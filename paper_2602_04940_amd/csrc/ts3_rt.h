@@ -110,6 +110,23 @@ __device__ __forceinline__ void mma_parts(f32x4 *acc, const Parts<NA> (&a)[N], c
         for (int i = 0; i < N; ++i) acc[i] = mma_bf16(a[i].p[PP::I[q]], b.p[PP::J[q]], acc[i]);
 }
 
+// The same for a long sum over points: the step's products are summed from zero and
+// then added to acc on the vector unit, or, where the step's A operand is negated,
+// subtracted.  A bf16 MFMA drops the low bits of its terms that lie below its largest
+// one, and it rounds down (measured: a sum that starts from the accumulator lost
+// 2.6e-5 of the float32 weight gradients of 2M points, one that starts from zero
+// 7.4e-6, against 1.1e-6 with float32 MFMAs): from zero fewer bits are dropped, and
+// negating every other step's A turns the bias of those over.
+template <int N, int NA, int NB>
+__device__ __forceinline__ void mma_parts_add(f32x4 *acc, const Parts<NA> (&a)[N], const Parts<NB> &b, bool negated) {
+    f32x4 t[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) t[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    mma_parts<N, NA, NB>(t, a, b);
+#pragma unroll
+    for (int i = 0; i < N; ++i) acc[i] = negated ? acc[i] - t[i] : acc[i] + t[i];
+}
+
 // Eight storage elements of a point row as operand parts (zero past the row).
 __device__ __forceinline__ void rt_load8(float (&v)[8], const float *p, bool ok) {
     const float4 a = ok ? reinterpret_cast<const float4 *>(p)[0] : float4{0.f, 0.f, 0.f, 0.f};
@@ -133,10 +150,10 @@ template <> struct RtRow<bf16_t> {
 
 // Max-shifted softmax over a head's MT <= MTMAX slice tiles of 16 points (lane (g,
 // li): slices 16mt + 4g + r of point li), then the weights' three parts, four
-// slices (8 bytes) per tile and part, to ws + part * plane + 32 * mt.  Weights of
-// a point that is not `valid` are zero.
+// slices (8 bytes) per tile and part, to ws + part * plane + 32 * mt, times `scale`
+// (0 for a point past the end, -1 to negate).
 template <int MTMAX>
-__device__ __forceinline__ void rt_softmax_store(f32x4 (&L)[MTMAX], int MT, bool valid, unsigned char *ws, int plane) {
+__device__ __forceinline__ void rt_softmax_store(f32x4 (&L)[MTMAX], int MT, float scale, unsigned char *ws, int plane) {
     float mx = -INFINITY;
 #pragma unroll
     for (int mt = 0; mt < MTMAX; ++mt)
@@ -155,7 +172,7 @@ __device__ __forceinline__ void rt_softmax_store(f32x4 (&L)[MTMAX], int MT, bool
                 sum += e;
             }
     const float tot = xrow_sum(sum);  // every lane takes part in the cross-row swaps
-    const float inv = valid ? 1.f / tot : 0.f;
+    const float inv = scale / tot;
     typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 #pragma unroll
     for (int mt = 0; mt < MTMAX; ++mt)
@@ -300,10 +317,12 @@ __global__ __launch_bounds__(512, 1) void k_slice_accumulate_rt(const T *__restr
 #pragma unroll
                         for (int k = 0; k < NP; ++k) *reinterpret_cast<bf16x8 *>(xd + k * xplane + c * 2) = f.p[k];
                 });
-            rt_softmax_store<MTMAX>(L, MT, valid, ws + (wave * 16 + li) * wstride + 8 * g, wplane);
+            rt_softmax_store<MTMAX>(L, MT, valid ? (wave & 2 ? -1.f : 1.f) : 0.f, ws + (wave * 16 + li) * wstride + 8 * g,
+                                    wplane);
         }
         __syncthreads();
         for (int r0 = 0; r0 < PB; r0 += 32) {
+            const float sign = r0 & 32 ? -1.f : 1.f;  // odd 32-point tiles hold negated weights
             Parts<NP> b[NCT];
 #pragma unroll
             for (int i = 0; i < NCT; ++i) {
@@ -318,15 +337,24 @@ __global__ __launch_bounds__(512, 1) void k_slice_accumulate_rt(const T *__restr
                     Parts<3> a;
 #pragma unroll
                     for (int k = 0; k < 3; ++k) a.p[k] = rt_tr(ws + k * wplane, wstride, r0, mt * 16, lane);
+                    // summed from zero and then added or subtracted: see mma_parts_add
                     using PP = PartProducts<3, NP>;
+                    f32x4 t[NCT], d{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int i = 0; i < NCT; ++i) t[i] = d;
 #pragma unroll
                     for (int q = 0; q < PP::N; ++q)
 #pragma unroll
                         for (int i = 0; i < NCT; ++i)
-                            if (wave + 8 * i < cct) S[i][mt] = mma_bf16(a.p[PP::I[q]], b[i].p[PP::J[q]], S[i][mt]);
-                    if (chunk == 0 && (mt & 7) == wave)
+                            if (wave + 8 * i < cct) t[i] = mma_bf16(a.p[PP::I[q]], b[i].p[PP::J[q]], t[i]);
 #pragma unroll
-                        for (int k = 2; k >= 0; --k) D[mt >> 3] = mma_bf16(a.p[k], ones.v, D[mt >> 3]);
+                    for (int i = 0; i < NCT; ++i)
+                        if (wave + 8 * i < cct) S[i][mt] += sign * t[i];
+                    if (chunk == 0 && (mt & 7) == wave) {
+#pragma unroll
+                        for (int k = 2; k >= 0; --k) d = mma_bf16(a.p[k], ones.v, d);
+                        D[mt >> 3] += sign * d;
+                    }
                 }
             }
         }
@@ -400,7 +428,7 @@ __global__ __launch_bounds__(512, 1) void k_deslice_rt(const T *__restrict__ x, 
                         f.p[k] = *reinterpret_cast<const bf16x8 *>(row + k * xplane + kc * 64);
                 },
                 [&](int, bool, const Parts<NP> &r, Parts<NP> &f) { f = r; });
-            rt_softmax_store<MTMAX>(L, MT, true, ws + (pt0 * 16 + li) * wstride + hh * M * 2 + 8 * g, wplane);
+            rt_softmax_store<MTMAX>(L, MT, 1.f, ws + (pt0 * 16 + li) * wstride + hh * M * 2 + 8 * g, wplane);
         }
         __syncthreads();
         if (wave < CT) {

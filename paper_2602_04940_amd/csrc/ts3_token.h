@@ -11,6 +11,7 @@
 #pragma once
 #include "ts3_device.h"
 #include "ts3_pass2.h"  // zchan
+#include "ts3_fp32.h"
 #include "ts3_rt.h"
 #include "ts3_small.h"
 
@@ -97,7 +98,8 @@ __global__ __launch_bounds__(TOK_THREADS) void k_slice_tokens(const TS *__restri
 // Where the decoding operands go; what a layer does not use is NULL.
 template <typename T> struct AttendOut {
     float *s1, *Z, *b3;
-    T *zp;         // fragments [H][CT][KM][64][8], or the runtime-shape parts (rt heads at a time)
+    T *zp;         // fragments [H][CT][KM][64][8], or parts: the runtime-shape layout (rt heads
+                   // at a time), or for float32 that of k_deslice3
     int rt;        // 0, or GH of the runtime-shape layout
     bf16_t *sf;    // slice-state pass 2 (dh = 16, M a multiple of 32): s'^T fragments
     bf16_t *w3f;   // and W3^T fragments
@@ -291,6 +293,10 @@ __global__ __launch_bounds__(256) void k_attend(const float *__restrict__ s, con
             if (out.rt) {
                 store_parts((bf16_t *)out.zp, rt_z_index(h, m, c, CT, M, RtGroup(out.rt, M), RT_NP<T>), acc[i] + bb,
                             RT_NP<T>);
+            } else if constexpr (sizeof(T) == 4) {
+                const int64_t at = z3_index(h, m, c, CT, KM);
+                store_parts((bf16_t *)out.zp, at, acc[i] + bb, 3);
+                if (M == 16) store_parts((bf16_t *)out.zp, at + 4, 0.f, 3);  // slots 4..7: past M
             } else {
                 const int64_t at = zp_index(h, m, c, CT, KM);
                 store_elem(out.zp + at, acc[i] + bb);
