@@ -454,16 +454,18 @@ ts3_status check_desc(const ts3_desc *d) {
 // sums one part for one head or head pair, so a mesh of few spans would leave
 // most compute units idle: at 100,003 points and spans of 32,768 (bf16, C =
 // 128, H = 8, M = 64) pass 1 ran 16 workgroups and took 343 us, with parts of
-// 1,632 points 248 workgroups.  The part length gives one workgroup per compute
-// unit for the whole mesh (a second round would pay a workgroup's start and end
-// again, about 3 us against 1.3 us per 96 points), but at most PART_POINTS, so that
-// a mesh that arrives in tiles still spreads each tile, unless the mesh fills
-// PART_ROUNDS rounds with longer ones: at 16M points parts of 5,216 instead of
-// whole spans of 15,625 made the layer 1.8% slower.  Never more than PART_BYTES of
-// partials through the split, and a multiple of the points that a workgroup's
-// waves take per step.  Only desc enters the rule, so a state's sums do not depend
-// on the tiling.
-constexpr int64_t PART_POINTS = 4096, PART_WGS = 256, PART_ROUNDS = 4, PART_BYTES = int64_t(128) << 20;
+// 1,632 points 248 workgroups and 48 us.  The part length gives one workgroup per
+// compute unit for the whole mesh (a second round would pay a workgroup's start and
+// end again, about 3 us against 1.3 us per 96 points), but at most PART_POINTS, so
+// that a mesh that arrives in tiles still spreads each tile, unless the mesh fills
+// PART_ROUNDS rounds with longer ones.  1M points streamed in tiles of 65,536 took
+// 0.87 ms with 4,096 and 4 rounds, 0.62 ms with these; the same mesh in one call 423
+// and 451 us (470 us with whole spans of 15,625, one round of 256 workgroups).  At 16M
+// points parts of 5,216 made the layer 1.8% slower than whole spans of 15,625.  Never
+// more than PART_BYTES of partials through the split, and a multiple of the points
+// that a workgroup's waves take per step.  Only desc enters the rule, so a state's sums
+// do not depend on the tiling.
+constexpr int64_t PART_POINTS = 2048, PART_WGS = 256, PART_ROUNDS = 8, PART_BYTES = int64_t(128) << 20;
 
 SpanGeo span_geo(const ts3_desc &d, const Kernels &k, bool proj, int64_t E) {
     const bool pairs = d.H % 2 == 0 && d.io_dtype == TS3_BF16 && !k.rt && (d.C == 256 || (d.C == 128 && d.M >= 32));
