@@ -156,35 +156,44 @@ __global__ void k_prep_mlp(const float *__restrict__ Wa, const float *__restrict
 // x, pa  : [n][C] bf16, the block input and its Physics-Attention output
 // ln2_*  : LN2 affine [C]; frag: k_prep_mlp output; ba [F], bb [C]
 // lnn_*  : the next block's LN1 affine, or NULL (then xn is not written)
-// xo     : [n][C] bf16 block output (may alias x: the producer reads x before
-//          the first barrier, the consumer writes xo after the last); xn: LN1
+// xo     : [n][C] bf16 block output (may alias x: a wave reads and writes the
+//          same rows); xn: LN1
 //          of xo for the next block (may alias nothing that is read here)
 // grid   : ceil(n / 128) workgroups of 512 threads
 //
-// Producer and consumer waves, two per SIMD (one of each), 32 points per
-// pair, 128 points per workgroup:
-//   wave q      (producer) keeps LN2(y) of the pair's 32 points as B fragments
-//               and, per 64-unit chunk j, runs GEMM1 and the GELU, writing h
-//               (the f16 B fragments of GEMM2, in fragment order) to the
-//               pair's h tile;
-//   wave q + 4  (consumer) runs GEMM2 of chunk j-1 from that h tile into the
-//               32 x C output accumulator, issues the weight copies, and at
-//               the end writes the block output (and the next LN1).
-// Every weight fragment read from LDS then feeds two MFMAs (two 16-point
-// tiles), half the LDS traffic per point of the eight-wave kernel, and the
-// GELU's vector work runs beside the other wave's matrix work.  W_a^T and W_b
-// halves of a chunk are staged in separate slots (two each): step j reads
-// W_a(j) and W_b(j-1) and copies W_a(j+1) and W_b(j).  One barrier per step;
-// NCHUNK + 1 steps.  LDS: 4 x 64C bf16 weight slots + 2 x 4 KB h tiles per
-// pair (160 KB at C = 256).
+// Producer and consumer waves, two per SIMD (one of each): groups of 64 points, two
+// producers and two consumers each, 128 points per workgroup.
+//   each wave   first makes LN2(y) of 16 of the block's points, as B fragments, through
+//               LDS, and at the end writes 16 points' output and next LN1 from the sums
+//               that the consumers leave there;
+//   wave q      (producer, group q >> 1, half q & 1) keeps the group's 64
+//               points' fragments and, per 64-unit chunk j, runs GEMM1 and the
+//               GELU for its half of the chunk's hidden units, which is one K step of
+//               GEMM2: it writes that step's h (f16 B fragments, in fragment order) to
+//               the group's h tile;
+//   wave q + 4  (consumer) runs GEMM2 of chunk j-1 from that h tile for its half of
+//               the channels into a 64 x C/2 output accumulator and issues a quarter
+//               of the weight copies.
+// Every weight fragment read from LDS feeds four MFMAs (four 16-point tiles).  With
+// pairs of waves on 32 points (two MFMAs per fragment) the LDS reads alone took longer
+// than the products: 272 KB per chunk, 2,100 cycles at 128 bytes, against 2,048 cycles
+// of MFMAs per SIMD; now 160 KB.  The GELU's vector work runs beside the other wave's
+// matrix work.  W_a^T and W_b halves of a chunk are staged in separate slots (two
+// each): step j reads W_a(j) and W_b(j-1) and copies W_a(j+1) and W_b(j).  One barrier
+// per step; NCHUNK + 1 steps.  LDS: 4 x 64C bf16 weight slots + 2 x 8 KB h tiles per
+// group (160 KB at C = 256).
 template <int C> struct MlpPCCfg {
-    static constexpr int FC = 64, HT = FC / 16, KM = FC / 32, CK = C / 32, CT = C / 16, PT = 2;
+    static constexpr int FC = 64, KM = FC / 32, CK = C / 32, CT = C / 16, PT = 4;
+    static constexpr int CTH = CT / 2;                   // a consumer's channel tiles
+    static constexpr int ZLD = C + 4;                    // floats per row of output sums (bank spread)
     static constexpr int PART = 64 * C;                 // elements of each half of a chunk
     static constexpr int PART_BYTES = PART * 2;
     static constexpr int PART_COPIES = PART_BYTES / 1024;
-    static constexpr int HTILE = PT * KM * 64 * 16;      // bytes: a pair's h fragments
-    static constexpr int LDS_BYTES = 4 * PART_BYTES + 4 * 2 * HTILE;
+    static constexpr int HTILE = PT * KM * 64 * 16;      // bytes: a group's h fragments
+    static constexpr int LDS_BYTES = 4 * PART_BYTES + 2 * 2 * HTILE;
+    static_assert(128 * ZLD * 4 <= LDS_BYTES && 8 * CK * 1024 <= 2 * PART_BYTES, "rows pass through the slots");
     static_assert(PART_COPIES % 4 == 0, "each consumer issues a quarter of a part's copies");
+    static_assert(KM == 2, "a producer's hidden units are one K step");
 };
 
 template <int C, int F>
@@ -194,7 +203,7 @@ __global__ __launch_bounds__(512, 1) void k_mlp_residual_pc(
     const float *__restrict__ bb, const float *__restrict__ lnn_g, const float *__restrict__ lnn_b, bf16_t *xo,
     bf16_t *__restrict__ xn) {
     using Cfg = MlpPCCfg<C>;
-    constexpr int CK = Cfg::CK, CT = Cfg::CT, HT = Cfg::HT, KM = Cfg::KM, PT = Cfg::PT;
+    constexpr int CK = Cfg::CK, CTH = Cfg::CTH, KM = Cfg::KM, PT = Cfg::PT;
     constexpr int NCHUNK = F / Cfg::FC, PB = Cfg::PART_BYTES, HTILE = Cfg::HTILE;
     static_assert(F % Cfg::FC == 0, "hidden width in 64-unit chunks");
     __shared__ __attribute__((aligned(1024))) unsigned char lds[Cfg::LDS_BYTES];
@@ -204,14 +213,15 @@ __global__ __launch_bounds__(512, 1) void k_mlp_residual_pc(
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int q = wave & 3, role = wave >> 2;
+    const int grp = q >> 1, half = q & 1;
     const int li = lane & 15, g = lane >> 4;
-    const int64_t p0 = (int64_t)blockIdx.x * 128 + q * 32;
-    unsigned char *const hslots = lds + 4 * PB + q * 2 * HTILE;  // the pair's two h tiles
+    const int64_t p0 = (int64_t)blockIdx.x * 128 + grp * 64;
+    unsigned char *const hslots = lds + 4 * PB + grp * 2 * HTILE;  // the group's two h tiles
 
     // A consumer's quarter of part `half` (0: W_a^T, 1: W_b) of chunk j into slot sl.
-    auto issue_part = [&](int j, int half, int sl) {
-        const unsigned char *src = reinterpret_cast<const unsigned char *>(frag) + ((size_t)(2 * j + half)) * PB;
-        const uint32_t base = lds_addr(lds) + (half * 2 + sl) * PB;
+    auto issue_part = [&](int j, int part, int sl) {
+        const unsigned char *src = reinterpret_cast<const unsigned char *>(frag) + ((size_t)(2 * j + part)) * PB;
+        const uint32_t base = lds_addr(lds) + (part * 2 + sl) * PB;
 #pragma unroll
         for (int c = 0; c < Cfg::PART_COPIES / 4; ++c) {
             const int k = q * (Cfg::PART_COPIES / 4) + c;
@@ -219,70 +229,99 @@ __global__ __launch_bounds__(512, 1) void k_mlp_residual_pc(
         }
     };
 
-    if (role == 0) {
-        // ---------------------------------------------------------------- producer
-        // y = x + pa and LN2(y) as B fragments: tile pt, lane (li, g) holds
-        // point p0 + 16pt + li, channels 32k + 8g .. +7 in slot t of fragment k.
-        Frag<bf16_t> yb[PT][CK];
+    // Wave w takes points 16w .. of the block, whole rows, before and after the chunks
+    // (one memory round trip each way, no row read twice): lane (li, g) holds channels
+    // 32k + 8g .. +7 of point row(w) = blk + 16w + li.
+    const int64_t pr = (int64_t)blockIdx.x * 128 + wave * 16 + li;
+    const int64_t prc = pr < n ? pr : n - 1;
+    auto load_row = [&](uint4 (&xv)[CK], uint4 (&pv)[CK]) {
 #pragma unroll
-        for (int pt = 0; pt < PT; ++pt) {
-            int64_t p = p0 + 16 * pt + li;
-            p = p < n ? p : n - 1;
-            float y[CK][8];
-            float s = 0.f;
+        for (int k = 0; k < CK; ++k) {
+            xv[k] = *reinterpret_cast<const uint4 *>(x + prc * C + 32 * k + 8 * g);
+            pv[k] = *reinterpret_cast<const uint4 *>(pa + prc * C + 32 * k + 8 * g);
+        }
+    };
+    // Normalises v over the row (statistics over its four lanes).
+    auto normalise = [&](float (&v)[CK][8], const float *gam, const float *bet) {
+        float s = 0.f;
 #pragma unroll
-            for (int k = 0; k < CK; ++k) {
-                float a[8], b[8];
-                unpack8(*reinterpret_cast<const uint4 *>(x + p * C + 32 * k + 8 * g), a);
-                unpack8(*reinterpret_cast<const uint4 *>(pa + p * C + 32 * k + 8 * g), b);
+        for (int k = 0; k < CK; ++k)
 #pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    y[k][t] = a[t] + b[t];
-                    s += y[k][t];
-                }
+            for (int t = 0; t < 8; ++t) s += v[k][t];
+        const float mean = xrow_sum(s) * (1.f / C);
+        float qq = 0.f;
+#pragma unroll
+        for (int k = 0; k < CK; ++k)
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                v[k][t] -= mean;
+                qq += v[k][t] * v[k][t];
             }
-            const float mean = xrow_sum(s) * (1.f / C);
-            float qq = 0.f;
+        const float rstd = 1.f / sqrtf(xrow_sum(qq) * (1.f / C) + BLOCK_LN_EPS);
 #pragma unroll
-            for (int k = 0; k < CK; ++k)
+        for (int k = 0; k < CK; ++k) {
+            const f32x4 g0 = *reinterpret_cast<const f32x4 *>(gam + 32 * k + 8 * g);
+            const f32x4 g1 = *reinterpret_cast<const f32x4 *>(gam + 32 * k + 8 * g + 4);
+            const f32x4 b0 = *reinterpret_cast<const f32x4 *>(bet + 32 * k + 8 * g);
+            const f32x4 b1 = *reinterpret_cast<const f32x4 *>(bet + 32 * k + 8 * g + 4);
 #pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    y[k][t] -= mean;
-                    qq += y[k][t] * y[k][t];
-                }
-            const float rstd = 1.f / sqrtf(xrow_sum(qq) * (1.f / C) + BLOCK_LN_EPS);
-#pragma unroll
-            for (int k = 0; k < CK; ++k) {
-                const float4 g0 = *reinterpret_cast<const float4 *>(ln2_g + 32 * k + 8 * g);
-                const float4 g1 = *reinterpret_cast<const float4 *>(ln2_g + 32 * k + 8 * g + 4);
-                const float4 b0 = *reinterpret_cast<const float4 *>(ln2_b + 32 * k + 8 * g);
-                const float4 b1 = *reinterpret_cast<const float4 *>(ln2_b + 32 * k + 8 * g + 4);
-                const float gg[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
-                const float bbv[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
-#pragma unroll
-                for (int t = 0; t < 8; t += 2)
-                    yb[pt][k].set2(t, y[k][t] * rstd * gg[t] + bbv[t], y[k][t + 1] * rstd * gg[t + 1] + bbv[t + 1]);
+            for (int t = 0; t < 4; ++t) {
+                v[k][t] = v[k][t] * rstd * g0[t] + b0[t];
+                v[k][t + 4] = v[k][t + 4] * rstd * g1[t] + b1[t];
             }
         }
-        wait_vmcnt<0>();
-        __syncthreads();  // W_a(0) staged (the consumers' copies)
+    };
+    if (role == 1) issue_part(0, 0, 0);
+    {   // LN2(x + pa) as B fragments of tile `wave`, through the W_b slots
+        uint4 xv[CK], pv[CK];
+        load_row(xv, pv);
+        float y[CK][8];
+#pragma unroll
+        for (int k = 0; k < CK; ++k) {
+            float a[8], b[8];
+            unpack8(xv[k], a);
+            unpack8(pv[k], b);
+#pragma unroll
+            for (int t = 0; t < 8; ++t) y[k][t] = a[t] + b[t];
+        }
+        normalise(y, ln2_g, ln2_b);
+#pragma unroll
+        for (int k = 0; k < CK; ++k)
+            *reinterpret_cast<uint4 *>(wb_slots + ((wave * CK + k) * 64 + lane) * 16) = pack8(y[k]);
+    }
+    wait_vmcnt<0>();
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __syncthreads();  // every tile's fragments and W_a(0) are in LDS
+    float *const zrows = reinterpret_cast<float *>(lds);  // after the chunks: [128][ZLD] output sums
+    constexpr int ZLD = Cfg::ZLD;
+
+    if (role == 0) {
+        // ---------------------------------------------------------------- producer
+        Frag<bf16_t> yb[PT][CK];
+#pragma unroll
+        for (int pt = 0; pt < PT; ++pt)
+#pragma unroll
+            for (int k = 0; k < CK; ++k)
+                yb[pt][k].v = *reinterpret_cast<const bf16x8 *>(wb_slots + (((grp * PT + pt) * CK + k) * 64 + lane) * 16);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __syncthreads();  // the W_b slots are free
 #pragma unroll 1
         for (int j = 0; j <= NCHUNK; ++j) {
             if (j < NCHUNK) {
                 const unsigned char *wa = wa_slots + (j & 1) * PB;
-                f32x4 Hh[HT][PT];
+                f32x4 Hh[2][PT];
 #pragma unroll
-                for (int ht = 0; ht < HT; ++ht) {
-                    const float4 b = *reinterpret_cast<const float4 *>(ba + 64 * j + 16 * ht + 4 * g);
+                for (int i = 0; i < 2; ++i) {
+                    const float4 b = *reinterpret_cast<const float4 *>(ba + 64 * j + 16 * (2 * half + i) + 4 * g);
 #pragma unroll
-                    for (int pt = 0; pt < PT; ++pt) Hh[ht][pt] = f32x4{b.x, b.y, b.z, b.w};
+                    for (int pt = 0; pt < PT; ++pt) Hh[i][pt] = f32x4{b.x, b.y, b.z, b.w};
                 }
                 // A fragments are read one K step ahead of their products.
-                Frag<bf16_t> a1[2][HT];
-                auto read1 = [&](int kc, Frag<bf16_t>(&dst)[HT]) {
+                Frag<bf16_t> a1[2][2];
+                auto read1 = [&](int kc, Frag<bf16_t>(&dst)[2]) {
 #pragma unroll
-                    for (int ht = 0; ht < HT; ++ht)
-                        dst[ht].v = *reinterpret_cast<const bf16x8 *>(wa + ((ht * CK + kc) * 64 + lane) * 16);
+                    for (int i = 0; i < 2; ++i)
+                        dst[i].v = *reinterpret_cast<const bf16x8 *>(wa + (((2 * half + i) * CK + kc) * 64 + lane) * 16);
                 };
                 read1(0, a1[0]);
                 __builtin_amdgcn_s_setprio(2);  // GEMM1 first on the matrix core; GEMM2 fills the GELU
@@ -290,69 +329,62 @@ __global__ __launch_bounds__(512, 1) void k_mlp_residual_pc(
                 for (int kc = 0; kc < CK; ++kc) {
                     if (kc + 1 < CK) read1(kc + 1, a1[(kc + 1) & 1]);
 #pragma unroll
-                    for (int ht = 0; ht < HT; ++ht)
+                    for (int i = 0; i < 2; ++i)
 #pragma unroll
-                        for (int pt = 0; pt < PT; ++pt) mma(Hh[ht][pt], a1[kc & 1][ht], yb[pt][kc]);
+                        for (int pt = 0; pt < PT; ++pt) mma(Hh[i][pt], a1[kc & 1][i], yb[pt][kc]);
                 }
                 __builtin_amdgcn_s_setprio(0);
-                // GELU into the f16 B fragments of GEMM2, stored in fragment order.
+                // GELU into the f16 B fragments of GEMM2's K step `half`.
                 unsigned char *ht_out = hslots + (j & 1) * HTILE;
 #pragma unroll
-                for (int pt = 0; pt < PT; ++pt)
+                for (int pt = 0; pt < PT; ++pt) {
+                    u32x4 u;
 #pragma unroll
-                    for (int km = 0; km < KM; ++km) {
-                        u32x4 u;
-#pragma unroll
-                        for (int t = 0; t < 8; t += 2) {
-                            const int ht = 2 * km + (t >> 2);
-                            u[t >> 1] =
-                                __builtin_bit_cast(uint32_t, gelu2_f16(Hh[ht][pt][t & 3], Hh[ht][pt][(t & 3) + 1]));
-                        }
-                        *reinterpret_cast<u32x4 *>(ht_out + ((pt * KM + km) * 64 + lane) * 16) = u;
-                    }
+                    for (int t = 0; t < 8; t += 2)
+                        u[t >> 1] = __builtin_bit_cast(uint32_t, gelu2_f16(Hh[t >> 2][pt][t & 3], Hh[t >> 2][pt][(t & 3) + 1]));
+                    *reinterpret_cast<u32x4 *>(ht_out + ((half * PT + pt) * 64 + lane) * 16) = u;
+                }
             }
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             __syncthreads();  // h(j) written; W_a(j+1) and W_b(j) staged
         }
     } else {
         // ---------------------------------------------------------------- consumer
-        f32x4 Z[CT][PT];
+        f32x4 Z[CTH][PT];  // channel tiles CTH * half + ct
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct)
+        for (int ct = 0; ct < CTH; ++ct)
 #pragma unroll
             for (int pt = 0; pt < PT; ++pt) Z[ct][pt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        issue_part(0, 0, 0);
-        wait_vmcnt<0>();
-        __syncthreads();  // W_a(0) staged
+        __syncthreads();  // the W_b slots are free
 #pragma unroll 1
         for (int j = 0; j <= NCHUNK; ++j) {
             if (j + 1 < NCHUNK) issue_part(j + 1, 0, (j + 1) & 1);
             if (j < NCHUNK) issue_part(j, 1, j & 1);
             if (j > 0) {
-                // GEMM2 of chunk j-1: the W_b fragment of channel tile ct+1 is
-                // read while tile ct's products run.
+                // GEMM2 of chunk j-1, K steps outermost: the two products into one
+                // accumulator are CTH * PT apart; the fragment of step q2+2 is read
+                // while step q2's products run.
                 const unsigned char *wb = wb_slots + ((j - 1) & 1) * PB;
                 const unsigned char *hin = hslots + ((j - 1) & 1) * HTILE;
-                Frag<f16_t> hb[PT][KM];
-#pragma unroll
-                for (int pt = 0; pt < PT; ++pt)
-#pragma unroll
-                    for (int km = 0; km < KM; ++km)
-                        hb[pt][km].v = *reinterpret_cast<const f16x8 *>(hin + ((pt * KM + km) * 64 + lane) * 16);
-                // K steps outermost: the two products into one accumulator are
-                // CT * PT apart (a dependent MFMA issues at half rate); the
-                // fragment of step q+2 is read while step q's products run.
-                constexpr int NQ = KM * CT;
-                auto bfrag = [&](int q2) { return wb + (((q2 % CT) * KM + q2 / CT) * 64 + lane) * 16; };
+                Frag<f16_t> hb[KM][PT];
+                constexpr int NQ = KM * CTH;
+                auto bfrag = [&](int q2) {
+                    return wb + (((CTH * half + q2 % CTH) * KM + q2 / CTH) * 64 + lane) * 16;
+                };
                 Frag<f16_t> a2[4];
                 a2[0].v = *reinterpret_cast<const f16x8 *>(bfrag(0));
+#pragma unroll
+                for (int km = 0; km < KM; ++km)
+#pragma unroll
+                    for (int pt = 0; pt < PT; ++pt)
+                        hb[km][pt].v = *reinterpret_cast<const f16x8 *>(hin + ((km * PT + pt) * 64 + lane) * 16);
                 a2[1].v = *reinterpret_cast<const f16x8 *>(bfrag(1));
 #pragma unroll
                 for (int q2 = 0; q2 < NQ; ++q2) {
                     if (q2 + 2 < NQ) a2[(q2 + 2) & 3].v = *reinterpret_cast<const f16x8 *>(bfrag(q2 + 2));
-                    const int km = q2 / CT, ct = q2 % CT;
+                    const int km = q2 / CTH, ct = q2 % CTH;
 #pragma unroll
-                    for (int pt = 0; pt < PT; ++pt) mma(Z[ct][pt], a2[q2 & 3], hb[pt][km]);
+                    for (int pt = 0; pt < PT; ++pt) mma(Z[ct][pt], a2[q2 & 3], hb[km][pt]);
                 }
             }
             wait_vmcnt<0>();  // this wave's copies of the step landed
@@ -360,55 +392,43 @@ __global__ __launch_bounds__(512, 1) void k_mlp_residual_pc(
             __syncthreads();
         }
 
-        // out = x + pa + z + bb; lane (li, g) of tile pt holds channels
-        // 32k + 8g + 4h + r in Z[2k + h][pt][r].
+        // lane (li, g) of tile pt holds channels C/2 half + 32k + 8g + 4i + r in Z[2k + i][pt][r]
 #pragma unroll
-        for (int pt = 0; pt < PT; ++pt) {
-            const int64_t p = p0 + 16 * pt + li;
-            const int64_t pc = p < n ? p : n - 1;
-            float o[CK][8];
+        for (int ct = 0; ct < CTH; ++ct)
 #pragma unroll
-            for (int k = 0; k < CK; ++k) {
-                float a[8], b[8];
-                unpack8(*reinterpret_cast<const uint4 *>(x + pc * C + 32 * k + 8 * g), a);
-                unpack8(*reinterpret_cast<const uint4 *>(pa + pc * C + 32 * k + 8 * g), b);
-                const float4 c0 = *reinterpret_cast<const float4 *>(bb + 32 * k + 8 * g);
-                const float4 c1 = *reinterpret_cast<const float4 *>(bb + 32 * k + 8 * g + 4);
-                const float cb[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
-#pragma unroll
-                for (int t = 0; t < 8; ++t) o[k][t] = (a[t] + b[t]) + (Z[2 * k + (t >> 2)][pt][t & 3] + cb[t]);
-            }
-            if (lnn_g) {  // uniform
-                // the next block's LN1 of the rounded output
-                float sr = 0.f;
-#pragma unroll
-                for (int k = 0; k < CK; ++k)
-#pragma unroll
-                    for (int t = 0; t < 8; ++t) {
-                        o[k][t] = (float)(__bf16)o[k][t];
-                        sr += o[k][t];
-                    }
-                const float mean = xrow_sum(sr) * (1.f / C);
-                float qq = 0.f;
-#pragma unroll
-                for (int k = 0; k < CK; ++k)
-#pragma unroll
-                    for (int t = 0; t < 8; ++t) qq += (o[k][t] - mean) * (o[k][t] - mean);
-                const float rstd = 1.f / sqrtf(xrow_sum(qq) * (1.f / C) + BLOCK_LN_EPS);
-#pragma unroll
-                for (int k = 0; k < CK; ++k) {
-                    float v[8];
-#pragma unroll
-                    for (int t = 0; t < 8; ++t)
-                        v[t] = (o[k][t] - mean) * rstd * lnn_g[32 * k + 8 * g + t] + lnn_b[32 * k + 8 * g + t];
-                    if (p < n) *reinterpret_cast<uint4 *>(xn + p * C + 32 * k + 8 * g) = pack8(v);
-                }
-            }
-            if (p < n)
-#pragma unroll
-                for (int k = 0; k < CK; ++k) *reinterpret_cast<uint4 *>(xo + p * C + 32 * k + 8 * g) = pack8(o[k]);
-        }
+            for (int pt = 0; pt < PT; ++pt)
+                *reinterpret_cast<f32x4 *>(zrows + (grp * 64 + pt * 16 + li) * ZLD + half * (C / 2) + 32 * (ct >> 1) + 8 * g +
+                                           4 * (ct & 1)) = Z[ct][pt];
     }
+    // out = x + pa + z + bb and the next block's LN1 of the rounded output
+    uint4 xv[CK], pv[CK];
+    load_row(xv, pv);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __syncthreads();  // the sums are in LDS
+    float o[CK][8];
+#pragma unroll
+    for (int k = 0; k < CK; ++k) {
+        float a[8], b[8];
+        unpack8(xv[k], a);
+        unpack8(pv[k], b);
+        const float *zr = zrows + (wave * 16 + li) * ZLD + 32 * k + 8 * g;
+        const f32x4 z0 = *reinterpret_cast<const f32x4 *>(zr), z1 = *reinterpret_cast<const f32x4 *>(zr + 4);
+        const f32x4 d0 = *reinterpret_cast<const f32x4 *>(bb + 32 * k + 8 * g);
+        const f32x4 d1 = *reinterpret_cast<const f32x4 *>(bb + 32 * k + 8 * g + 4);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            o[k][t] = (a[t] + b[t]) + (z0[t] + d0[t]);
+            o[k][t + 4] = (a[t + 4] + b[t + 4]) + (z1[t] + d1[t]);
+        }
+        const uint4 u = pack8(o[k]);
+        if (pr < n) *reinterpret_cast<uint4 *>(xo + pr * C + 32 * k + 8 * g) = u;
+        unpack8(u, o[k]);
+    }
+    if (!lnn_g) return;  // uniform
+    normalise(o, lnn_g, lnn_b);
+    if (pr < n)
+#pragma unroll
+        for (int k = 0; k < CK; ++k) *reinterpret_cast<uint4 *>(xn + pr * C + 32 * k + 8 * g) = pack8(o[k]);
 }
 
 }  // namespace ts3
