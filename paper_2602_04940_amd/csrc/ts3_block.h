@@ -10,7 +10,7 @@
 //   k_layernorm     LN1 of the first block (later blocks get theirs from the
 //                   previous block's feed-forward epilogue).
 //   k_prep_mlp      W_a (bf16) and W_b (f16) as matrix-core fragments, chunked
-//                   by 64 hidden units: [F/64][W_a^T part | W_b part], 64*C
+//                   by FC hidden units: [F/FC][W_a^T part | W_b part], FC*C
 //                   elements each, so one linear copy stages a chunk.
 //   k_mlp_residual_pc  one kernel for the rest of the block: y = x + PA
 //                   output, LN2, both feed-forward products with GELU (its
@@ -19,7 +19,7 @@
 //
 // k_mlp_residual_pc: 128 points per workgroup, 32 per pair of waves sharing a
 // SIMD.  The producer keeps LN2(y) of its points as B fragments (K = channels)
-// in registers; the hidden layer is walked in 64-unit chunks staged in LDS:
+// in registers; the hidden layer is walked in chunks staged in LDS:
 //   GEMM1  H^T[f][p] = W_a^T[f][:] . LN2(y)[p][:] + b_a[f]   (A = staged W_a^T)
 //   GELU   on packed halves; the 16 x 4 outputs of two hidden tiles are
 //          exactly a B fragment of the second product (K slot (g, t) <->
@@ -116,16 +116,19 @@ __global__ __launch_bounds__(256) void k_layernorm(const bf16_t *__restrict__ x,
     }
 }
 
+// Hidden units per chunk.  At C = 128 a chunk of 32 leaves room for a second workgroup
+// per compute unit (68 KB of LDS, 122 registers): its products run while the other
+// loads or writes its rows, which take as long as the products there.
 template <int C> struct MlpCfg {
-    static constexpr int FC = 64, KM = FC / 32, CK = C / 32;
-    static constexpr int PART = 64 * C;                 // elements of each half of a chunk
+    static constexpr int FC = C <= 128 ? 32 : 64, KM = FC / 32, CK = C / 32;
+    static constexpr int PART = FC * C;                 // elements of each half of a chunk
 };
 
-// Fragments of chunk j (hidden units 64j .. 64j+63):
+// Fragments of chunk j (hidden units FC j .. FC j + FC - 1):
 //   W_a^T part, index ((ht*CK + kc)*64 + l)*8 + t:
-//       W_a[c = 32kc + 8(l>>4) + t][f = 64j + 16ht + (l&15)]
+//       W_a[c = 32kc + 8(l>>4) + t][f = FC j + 16ht + (l&15)]
 //   W_b part,   index ((ct*KM + km)*64 + l)*8 + t:
-//       W_b[f = 64j + 32km + 16(t>>2) + 4(l>>4) + (t&3)][c = zchan(ct, l&15)]
+//       W_b[f = FC j + 32km + 16(t>>2) + 4(l>>4) + (t&3)][c = zchan(ct, l&15)]
 template <int C>
 __global__ void k_prep_mlp(const float *__restrict__ Wa, const float *__restrict__ Wb, int F,
                            bf16_t *__restrict__ frag) {
@@ -139,12 +142,12 @@ __global__ void k_prep_mlp(const float *__restrict__ Wa, const float *__restrict
         if (e < Cfg::PART) {
             const int kc = r % Cfg::CK, ht = r / Cfg::CK;
             const int c = 32 * kc + 8 * (l >> 4) + t;
-            const int64_t f = 64 * j + 16 * ht + (l & 15);
+            const int64_t f = Cfg::FC * j + 16 * ht + (l & 15);
             v = Wa[(int64_t)c * F + f];
         } else {
             const int r2 = r - Cfg::PART / 512;
             const int km = r2 % Cfg::KM, ct = r2 / Cfg::KM;
-            const int64_t f = 64 * j + 32 * km + 16 * (t >> 2) + 4 * (l >> 4) + (t & 3);
+            const int64_t f = Cfg::FC * j + 32 * km + 16 * (t >> 2) + 4 * (l >> 4) + (t & 3);
             const int c = zchan(ct, l & 15);
             frag[i].bits = __builtin_bit_cast(uint16_t, (_Float16)Wb[f * C + c]);  // f16: the second product
             continue;
@@ -167,10 +170,10 @@ __global__ void k_prep_mlp(const float *__restrict__ Wa, const float *__restrict
 //               LDS, and at the end writes 16 points' output and next LN1 from the sums
 //               that the consumers leave there;
 //   wave q      (producer, group q >> 1, half q & 1) keeps the group's 64
-//               points' fragments and, per 64-unit chunk j, runs GEMM1 and the
-//               GELU for its half of the chunk's hidden units, which is one K step of
-//               GEMM2: it writes that step's h (f16 B fragments, in fragment order) to
-//               the group's h tile;
+//               points' fragments and, per chunk j of hidden units (64, or 32 at C =
+//               128), runs GEMM1 and the GELU for its half of them, which is one K
+//               step of GEMM2 or half of one: it writes that h (f16 B fragments, in
+//               fragment order) to the group's h tile;
 //   wave q + 4  (consumer) runs GEMM2 of chunk j-1 from that h tile for its half of
 //               the channels into a 64 x C/2 output accumulator and issues a quarter
 //               of the weight copies.
@@ -183,29 +186,32 @@ __global__ void k_prep_mlp(const float *__restrict__ Wa, const float *__restrict
 // per step; NCHUNK + 1 steps.  LDS: 4 x 64C bf16 weight slots + 2 x 8 KB h tiles per
 // group (160 KB at C = 256).
 template <int C> struct MlpPCCfg {
-    static constexpr int FC = 64, KM = FC / 32, CK = C / 32, CT = C / 16, PT = 4;
+    static constexpr int FC = MlpCfg<C>::FC, KM = FC / 32, CK = C / 32, CT = C / 16, PT = 4;
+    static constexpr int HT = FC / 32;                   // a producer's hidden tiles
     static constexpr int CTH = CT / 2;                   // a consumer's channel tiles
     static constexpr int ZLD = C + 4;                    // floats per row of output sums (bank spread)
-    static constexpr int PART = 64 * C;                 // elements of each half of a chunk
+    static constexpr int PART = FC * C;                 // elements of each half of a chunk
     static constexpr int PART_BYTES = PART * 2;
     static constexpr int PART_COPIES = PART_BYTES / 1024;
     static constexpr int HTILE = PT * KM * 64 * 16;      // bytes: a group's h fragments
-    static constexpr int LDS_BYTES = 4 * PART_BYTES + 2 * 2 * HTILE;
-    static_assert(128 * ZLD * 4 <= LDS_BYTES && 8 * CK * 1024 <= 2 * PART_BYTES, "rows pass through the slots");
+    static constexpr int YB = PART_BYTES;                // LN2(y) fragments on their way: past W_a's first slot
+    static constexpr int PIPE = 4 * PART_BYTES + 2 * 2 * HTILE, ROWS = 128 * ZLD * 4;
+    static constexpr int LDS_BYTES = PIPE > ROWS ? PIPE : ROWS;
+    static_assert(YB + 8 * CK * 1024 <= LDS_BYTES, "rows pass through the slots");
     static_assert(PART_COPIES % 4 == 0, "each consumer issues a quarter of a part's copies");
-    static_assert(KM == 2, "a producer's hidden units are one K step");
+    static_assert(HT == 1 || HT == 2, "a producer's hidden units are half a K step or one");
 };
 
 template <int C, int F>
-__global__ __launch_bounds__(512, 1) void k_mlp_residual_pc(
+__global__ __launch_bounds__(512, C <= 128 ? 4 : 1) void k_mlp_residual_pc(
     const bf16_t *x, const bf16_t *__restrict__ pa, int64_t n, const float *__restrict__ ln2_g,
     const float *__restrict__ ln2_b, const bf16_t *__restrict__ frag, const float *__restrict__ ba,
     const float *__restrict__ bb, const float *__restrict__ lnn_g, const float *__restrict__ lnn_b, bf16_t *xo,
     bf16_t *__restrict__ xn) {
     using Cfg = MlpPCCfg<C>;
-    constexpr int CK = Cfg::CK, CTH = Cfg::CTH, KM = Cfg::KM, PT = Cfg::PT;
+    constexpr int CK = Cfg::CK, CTH = Cfg::CTH, KM = Cfg::KM, PT = Cfg::PT, HT = Cfg::HT;
     constexpr int NCHUNK = F / Cfg::FC, PB = Cfg::PART_BYTES, HTILE = Cfg::HTILE;
-    static_assert(F % Cfg::FC == 0, "hidden width in 64-unit chunks");
+    static_assert(F % Cfg::FC == 0, "hidden width in whole chunks");
     __shared__ __attribute__((aligned(1024))) unsigned char lds[Cfg::LDS_BYTES];
     unsigned char *const wa_slots = lds;               // W_a^T parts, two slots
     unsigned char *const wb_slots = lds + 2 * PB;      // W_b parts, two slots
@@ -272,7 +278,7 @@ __global__ __launch_bounds__(512, 1) void k_mlp_residual_pc(
         }
     };
     if (role == 1) issue_part(0, 0, 0);
-    {   // LN2(x + pa) as B fragments of tile `wave`, through the W_b slots
+    {   // LN2(x + pa) as B fragments of tile `wave`, through LDS
         uint4 xv[CK], pv[CK];
         load_row(xv, pv);
         float y[CK][8];
@@ -287,7 +293,7 @@ __global__ __launch_bounds__(512, 1) void k_mlp_residual_pc(
         normalise(y, ln2_g, ln2_b);
 #pragma unroll
         for (int k = 0; k < CK; ++k)
-            *reinterpret_cast<uint4 *>(wb_slots + ((wave * CK + k) * 64 + lane) * 16) = pack8(y[k]);
+            *reinterpret_cast<uint4 *>(lds + Cfg::YB + ((wave * CK + k) * 64 + lane) * 16) = pack8(y[k]);
     }
     wait_vmcnt<0>();
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -302,26 +308,27 @@ __global__ __launch_bounds__(512, 1) void k_mlp_residual_pc(
         for (int pt = 0; pt < PT; ++pt)
 #pragma unroll
             for (int k = 0; k < CK; ++k)
-                yb[pt][k].v = *reinterpret_cast<const bf16x8 *>(wb_slots + (((grp * PT + pt) * CK + k) * 64 + lane) * 16);
+                yb[pt][k].v =
+                    *reinterpret_cast<const bf16x8 *>(lds + Cfg::YB + (((grp * PT + pt) * CK + k) * 64 + lane) * 16);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        __syncthreads();  // the W_b slots are free
+        __syncthreads();  // the fragments are in registers, the slots free
 #pragma unroll 1
         for (int j = 0; j <= NCHUNK; ++j) {
             if (j < NCHUNK) {
                 const unsigned char *wa = wa_slots + (j & 1) * PB;
-                f32x4 Hh[2][PT];
+                f32x4 Hh[HT][PT];
 #pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    const float4 b = *reinterpret_cast<const float4 *>(ba + 64 * j + 16 * (2 * half + i) + 4 * g);
+                for (int i = 0; i < HT; ++i) {
+                    const float4 b = *reinterpret_cast<const float4 *>(ba + Cfg::FC * j + 16 * (HT * half + i) + 4 * g);
 #pragma unroll
                     for (int pt = 0; pt < PT; ++pt) Hh[i][pt] = f32x4{b.x, b.y, b.z, b.w};
                 }
                 // A fragments are read one K step ahead of their products.
-                Frag<bf16_t> a1[2][2];
-                auto read1 = [&](int kc, Frag<bf16_t>(&dst)[2]) {
+                Frag<bf16_t> a1[2][HT];
+                auto read1 = [&](int kc, Frag<bf16_t>(&dst)[HT]) {
 #pragma unroll
-                    for (int i = 0; i < 2; ++i)
-                        dst[i].v = *reinterpret_cast<const bf16x8 *>(wa + (((2 * half + i) * CK + kc) * 64 + lane) * 16);
+                    for (int i = 0; i < HT; ++i)
+                        dst[i].v = *reinterpret_cast<const bf16x8 *>(wa + (((HT * half + i) * CK + kc) * 64 + lane) * 16);
                 };
                 read1(0, a1[0]);
                 __builtin_amdgcn_s_setprio(2);  // GEMM1 first on the matrix core; GEMM2 fills the GELU
@@ -329,20 +336,22 @@ __global__ __launch_bounds__(512, 1) void k_mlp_residual_pc(
                 for (int kc = 0; kc < CK; ++kc) {
                     if (kc + 1 < CK) read1(kc + 1, a1[(kc + 1) & 1]);
 #pragma unroll
-                    for (int i = 0; i < 2; ++i)
+                    for (int i = 0; i < HT; ++i)
 #pragma unroll
                         for (int pt = 0; pt < PT; ++pt) mma(Hh[i][pt], a1[kc & 1][i], yb[pt][kc]);
                 }
                 __builtin_amdgcn_s_setprio(0);
-                // GELU into the f16 B fragments of GEMM2's K step `half`.
-                unsigned char *ht_out = hslots + (j & 1) * HTILE;
+                // GELU into the f16 B fragments of GEMM2: K step `half`, or slots 4 half .. +3
+                // of the only one.
+                unsigned char *ht_out = hslots + (j & 1) * HTILE + (HT == 2 ? half * PT * 1024 : half * 8);
 #pragma unroll
                 for (int pt = 0; pt < PT; ++pt) {
-                    u32x4 u;
+                    typedef __attribute__((ext_vector_type(2 * HT))) uint32_t uh_t;
+                    uh_t u;
 #pragma unroll
-                    for (int t = 0; t < 8; t += 2)
+                    for (int t = 0; t < 4 * HT; t += 2)
                         u[t >> 1] = __builtin_bit_cast(uint32_t, gelu2_f16(Hh[t >> 2][pt][t & 3], Hh[t >> 2][pt][(t & 3) + 1]));
-                    *reinterpret_cast<u32x4 *>(ht_out + ((half * PT + pt) * 64 + lane) * 16) = u;
+                    *reinterpret_cast<uh_t *>(ht_out + (pt * 64 + lane) * 16) = u;
                 }
             }
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -355,7 +364,7 @@ __global__ __launch_bounds__(512, 1) void k_mlp_residual_pc(
         for (int ct = 0; ct < CTH; ++ct)
 #pragma unroll
             for (int pt = 0; pt < PT; ++pt) Z[ct][pt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        __syncthreads();  // the W_b slots are free
+        __syncthreads();  // the fragments are in registers, the slots free
 #pragma unroll 1
         for (int j = 0; j <= NCHUNK; ++j) {
             if (j + 1 < NCHUNK) issue_part(j + 1, 0, (j + 1) & 1);
