@@ -50,7 +50,8 @@ __device__ __forceinline__ void softmax_tile(f32x4 (&E)[MT], float scale) {
         for (int r = 0; r < 4; ++r) E[mt][r] *= inv;
 }
 
-// Token side of the backward, one workgroup per head (256 threads):
+// Token side of the backward, one workgroup per head (1,024 threads; a row's softmax and
+// sums on 16 lanes; 211 us at C = 128, M = 64 with 256 threads and a row per thread):
 //   Z[h] = s1[h] W3_h            -> ds1, dW3_h
 //   s1 = softmax(q k^T / sqrt(dh)) v, q,k,v = s Wq,Wk,Wv  -> ds, dWq, dWk, dWv
 //   s = mean W1_h + b1_h          -> dmean, dW1_h, db1_h
@@ -58,7 +59,8 @@ __device__ __forceinline__ void softmax_tile(f32x4 (&E)[MT], float scale) {
 // and db3 = sum_m dZ[0][m] (every head's weights sum to one per point).
 // Dynamic LDS: floats mean, dZ [M][C] and s, s1, q, k, v, ds1, dq, dk, dv, ds
 // [M][dh] and P, dP [M][M].
-__global__ __launch_bounds__(256, 1) void k_bw_token(
+constexpr int BW_TOKEN_THREADS = 1024;
+__global__ __launch_bounds__(BW_TOKEN_THREADS, 1) void k_bw_token(
     const float *__restrict__ s_raw, const float *__restrict__ dsum, const float *__restrict__ s,
     const float *__restrict__ s1, const float *__restrict__ dZ, const float *__restrict__ W1,
     const float *__restrict__ Wq, const float *__restrict__ Wk, const float *__restrict__ Wv,
@@ -89,7 +91,9 @@ __global__ __launch_bounds__(256, 1) void k_bw_token(
     for (int i = tid; i < M * dh; i += nt) {
         const int m = i / dh, j = i % dh;
         float a = 0.f, aq = 0.f, ak = 0.f, av = 0.f;
+#pragma unroll 8
         for (int c = 0; c < C; ++c) a += gz[m * C + c] * W3[(size_t)(h * dh + j) * C + c];
+#pragma unroll 8
         for (int t = 0; t < dh; ++t) {
             const float sv = ss[m * dh + t];
             aq += sv * Wq[((size_t)h * dh + t) * dh + j];
@@ -126,23 +130,27 @@ __global__ __launch_bounds__(256, 1) void k_bw_token(
         dP[i] = dpv;
     }
     __syncthreads();
-    for (int a_ = tid; a_ < M; a_ += nt) {
-        float mx = P[a_ * M];
-        for (int b_ = 1; b_ < M; ++b_) mx = fmaxf(mx, P[a_ * M + b_]);
+    // a row on the 16 lanes of one DPP row (M is a multiple of 16)
+    for (int a_ = tid >> 4; a_ < M; a_ += nt >> 4) {
+        const int l = tid & 15;
+        float mx = -INFINITY;
+        for (int b_ = l; b_ < M; b_ += 16) mx = fmaxf(mx, P[a_ * M + b_]);
+        mx = row16_max(mx);
         float sum = 0.f;
-        for (int b_ = 0; b_ < M; ++b_) {
+        for (int b_ = l; b_ < M; b_ += 16) {
             const float e = expf(P[a_ * M + b_] - mx);
             P[a_ * M + b_] = e;
             sum += e;
         }
-        const float inv = 1.f / sum;
+        const float inv = 1.f / row16_sum(sum);
         float dot = 0.f;
-        for (int b_ = 0; b_ < M; ++b_) {
+        for (int b_ = l; b_ < M; b_ += 16) {
             P[a_ * M + b_] *= inv;
             dot += dP[a_ * M + b_] * P[a_ * M + b_];
         }
+        dot = row16_sum(dot);
         // dP becomes da = P (dP - rowsum(dP P))
-        for (int b_ = 0; b_ < M; ++b_) dP[a_ * M + b_] = P[a_ * M + b_] * (dP[a_ * M + b_] - dot);
+        for (int b_ = l; b_ < M; b_ += 16) dP[a_ * M + b_] = P[a_ * M + b_] * (dP[a_ * M + b_] - dot);
     }
     __syncthreads();
     // dv = P^T ds1; dq = da k * scale; dk = da^T q * scale
@@ -205,11 +213,12 @@ __global__ __launch_bounds__(256, 1) void k_bw_token(
         dsr[(size_t)h * M * C + i] = r;
     }
     __syncthreads();
-    for (int m = tid; m < M; m += nt) {
+    for (int m = tid >> 4; m < M; m += nt >> 4) {
         const float den = dsum[h * M + m] + eps;
         float a = 0.f;
-        for (int c = 0; c < C; ++c) a += gz[m * C + c] * mean[m * C + c];
-        dd[h * M + m] = den > 0.f ? -a / den : 0.f;
+        for (int c = tid & 15; c < C; c += 16) a += gz[m * C + c] * mean[m * C + c];
+        a = row16_sum(a);
+        if ((tid & 15) == 0) dd[h * M + m] = den > 0.f ? -a / den : 0.f;
     }
 }
 
