@@ -454,35 +454,51 @@ ts3_status check_desc(const ts3_desc *d) {
 // sums one part for one head or head pair, so a mesh of few spans would leave
 // most compute units idle: at 100,003 points and spans of 32,768 (bf16, C =
 // 128, H = 8, M = 64) pass 1 ran 16 workgroups and took 343 us, with parts of
-// 1,632 points 248 workgroups and 48 us.  The part length gives one workgroup per
-// compute unit for the whole mesh (a second round would pay a workgroup's start and
-// end again, about 3 us against 1.3 us per 96 points), but at most PART_POINTS, so
+// 1,728 points 232 workgroups and 30 us.  Parts are at most PART_POINTS long, so
 // that a mesh that arrives in tiles still spreads each tile, unless the mesh fills
-// PART_ROUNDS rounds with longer ones.  1M points streamed in tiles of 65,536 took
-// 0.87 ms with 4,096 and 4 rounds, 0.62 ms with these; the same mesh in one call 423
-// and 451 us (470 us with whole spans of 15,625, one round of 256 workgroups).  At 16M
-// points parts of 5,216 made the layer 1.8% slower than whole spans of 15,625.  Never
-// more than PART_BYTES of partials through the split, and a multiple of the points
+// PART_ROUNDS rounds of compute units with longer ones (1M points streamed in tiles of
+// 65,536 took 0.87 ms with 4,096 and 4 rounds, 0.62 ms with these; the same mesh in one
+// call 423 and 451 us, 470 us with whole spans of 15,625, one round of 256 workgroups;
+// at 16M points parts of 5,216 made the layer 1.8% slower than whole spans).  Of the
+// lengths below that, down to one round for the whole mesh, the one whose rounds, each a
+// part and a workgroup's start and end (about PART_START points), take the least: spans
+// do not divide into parts evenly, and a few workgroups past a round cost a whole one.
+// Those 100,003 points in parts of 1,632 were 260 workgroups and took 48 us, a float32
+// training step of 60,001 points with 280 workgroups 895 us against 725 us with 248.
+// Never more than PART_BYTES of partials through the split, and a multiple of the points
 // that a workgroup's waves take per step.  Only desc enters the rule, so a state's sums
 // do not depend on the tiling.
-constexpr int64_t PART_POINTS = 2048, PART_WGS = 256, PART_ROUNDS = 8, PART_BYTES = int64_t(128) << 20;
+constexpr int64_t PART_POINTS = 2048, PART_WGS = 256, PART_ROUNDS = 8, PART_START = 128, PART_BYTES = int64_t(128) << 20;
 
 SpanGeo span_geo(const ts3_desc &d, const Kernels &k, bool proj, int64_t E) {
     const bool pairs = d.H % 2 == 0 && d.io_dtype == TS3_BF16 && !k.rt && (d.C == 256 || (d.C == 128 && d.M >= 32));
     const int np = d.io_dtype == TS3_BF16 ? 1 : 3;
-    const RtPass1 rt1 = k.rt ? rt_pass1(np, d.C, d.M) : RtPass1{d.C, 128, 0};
-    const int64_t unit = proj ? 96 : !pairs ? rt1.PB : d.C == 256 ? 32 : 64;
+    const RtPass1 rt1 = k.rt ? rt_pass1(np, d.C, d.M) : RtPass1{d.C, 0, 0};
+    const int64_t unit = proj ? 96 : k.rt ? rt1.PB : pairs ? (d.C == 256 ? 32 : 64) : np == 3 ? 64 : 128;
     const int64_t wgs = pairs ? d.H / 2 : (int64_t)d.H * ((d.C + rt1.CC - 1) / rt1.CC);  // per part
-    const int64_t N = std::max<int64_t>(d.max_points, 1), Q = d.group_span;
+    // (a mesh past 2^40 points has whole spans whatever its size)
+    const int64_t N = std::min(std::max<int64_t>(d.max_points, 1), int64_t(1) << 40), Q = d.group_span, q = std::min(N, Q);
     const int64_t one_round = (N * wgs + PART_WGS - 1) / PART_WGS;
-    const int64_t want = std::min(one_round, std::max(PART_POINTS, one_round / PART_ROUNDS));
+    const int64_t longest = std::max(PART_POINTS, one_round / PART_ROUNDS);
     const int64_t nspan = (N + Q - 1) / Q;
-    int64_t S = (Q + want - 1) / want;
-    S = std::max<int64_t>(1, std::min<int64_t>(S, PART_BYTES / (nspan * E * 4)));
-    if (S <= 1) return SpanGeo{(int32_t)Q, (int32_t)Q, 1, 0};
-    const int64_t L = ((Q + S - 1) / S + unit - 1) / unit * unit;
-    if (L >= Q) return SpanGeo{(int32_t)Q, (int32_t)Q, 1, 0};
-    return SpanGeo{(int32_t)Q, (int32_t)L, (int32_t)((Q + L - 1) / L), 0};
+    const int64_t most = PART_BYTES / (nspan * E * 4);
+    const int64_t first = std::max<int64_t>(1, std::min(most, (q + longest - 1) / longest));
+    // one_round >= q * wgs / PART_WGS, so at most PART_WGS lengths
+    const int64_t last = std::max(first, std::min(most, (q + one_round - 1) / one_round));
+    SpanGeo best{(int32_t)Q, (int32_t)Q, 1, 0};
+    int64_t least = INT64_MAX;
+    for (int64_t S = first; S <= last; ++S) {
+        SpanGeo geo{(int32_t)Q, (int32_t)Q, 1, 0};
+        const int64_t L = S > 1 ? ((q + S - 1) / S + unit - 1) / unit * unit : Q;
+        if (L < Q) geo = SpanGeo{(int32_t)Q, (int32_t)L, (int32_t)((Q + L - 1) / L), 0};
+        const int64_t rounds = (geo.parts(N) * wgs + PART_WGS - 1) / PART_WGS;
+        const int64_t cost = rounds * (std::min(L, q) + PART_START);
+        if (cost < least) {
+            least = cost;
+            best = geo;
+        }
+    }
+    return best;
 }
 
 ts3_status check_weights_w2(const ts3_weights *w) {
