@@ -146,12 +146,16 @@ hipError_t launch_pass2(const void *x, int64_t n, int32_t H, int32_t, int32_t, c
         // workgroups of 128-point blocks.  (At C = 128 the same kernel ran
         // 22% slower than the eight-wave one below: the producer's softmax is
         // twice as large against its MFMAs.)
-        using PCfg = Pass2PCCfg<C, M>;
-        const int64_t blocks = (n + PCfg::POINTS_PER_WG - 1) / PCfg::POINTS_PER_WG;
-        const int64_t grid = std::min<int64_t>(blocks, device_cu_count());
-        if (grid > 0)
-            hipLaunchKernelGGL((k_deslice_pc<C, M>), dim3((unsigned)grid), dim3(512), 0, st, (const bf16_t *)x, n, H,
-                               (const bf16_t *)w2p, b2s, (const bf16_t *)zp, (bf16_t *)out);
+        // 64-point blocks while those fill at most one round of compute units.
+        if (n <= 0) return hipSuccess;
+        const int64_t cus = device_cu_count();
+        auto launch = [&](auto pt) {
+            constexpr int PT = decltype(pt)::value, PTS = Pass2PCCfg<C, M, PT>::POINTS_PER_WG;
+            hipLaunchKernelGGL((k_deslice_pc<C, M, PT>), dim3((unsigned)std::min((n + PTS - 1) / PTS, cus)), dim3(512), 0,
+                               st, (const bf16_t *)x, n, H, (const bf16_t *)w2p, b2s, (const bf16_t *)zp, (bf16_t *)out);
+        };
+        if (n <= cus * 64) launch(std::integral_constant<int, 1>{});
+        else launch(std::integral_constant<int, 2>{});
         return hipSuccess;
     } else if constexpr (sizeof(T) == 2 && C <= 128) {
         using WCfg = Pass2W8Cfg<T, C, M>;

@@ -17,8 +17,7 @@
 //                   tanh form in half precision, gelu2_f16) between them, the
 //                   residual, and optionally the next block's LN1.
 //
-// k_mlp_residual_pc: 128 points per workgroup, 32 per pair of waves sharing a
-// SIMD.  The producer keeps LN2(y) of its points as B fragments (K = channels)
+// k_mlp_residual_pc: 32 PT (128, or fewer for a small call) points per workgroup.  The producer keeps LN2(y) of its points as B fragments (K = channels)
 // in registers; the hidden layer is walked in chunks staged in LDS:
 //   GEMM1  H^T[f][p] = W_a^T[f][:] . LN2(y)[p][:] + b_a[f]   (A = staged W_a^T)
 //   GELU   on packed halves; the 16 x 4 outputs of two hidden tiles are
@@ -162,7 +161,7 @@ __global__ void k_prep_mlp(const float *__restrict__ Wa, const float *__restrict
 // xo     : [n][C] bf16 block output (may alias x: a wave reads and writes the
 //          same rows); xn: LN1
 //          of xo for the next block (may alias nothing that is read here)
-// grid   : ceil(n / 128) workgroups of 512 threads
+// grid   : ceil(n / (32 PT)) workgroups of 512 threads
 //
 // Producer and consumer waves, two per SIMD (one of each): groups of 64 points, two
 // producers and two consumers each, 128 points per workgroup.
@@ -185,8 +184,14 @@ __global__ void k_prep_mlp(const float *__restrict__ Wa, const float *__restrict
 // each): step j reads W_a(j) and W_b(j-1) and copies W_a(j+1) and W_b(j).  One barrier
 // per step; NCHUNK + 1 steps.  LDS: 4 x 64C bf16 weight slots + 2 x 8 KB h tiles per
 // group (160 KB at C = 256).
-template <int C> struct MlpPCCfg {
-    static constexpr int FC = MlpCfg<C>::FC, KM = FC / 32, CK = C / 32, CT = C / 16, PT = 4;
+//
+// PT: 16-point tiles per group (the workgroup takes 32 PT points; the figures above are
+// for 4).  A workgroup's steps are one chain, so a call of a few thousand points is
+// bound by the points per workgroup: 4,096 points at C = 256 ran 32 workgroups and took
+// 44 us, with PT = 1 128 workgroups and 24 us.  mlp_tiles() has the rule.  A point's products and their order do
+// not depend on PT, nor does its result.
+template <int C, int PT> struct MlpPCCfg {
+    static constexpr int FC = MlpCfg<C>::FC, KM = FC / 32, CK = C / 32, CT = C / 16, PTS = 32 * PT;
     static constexpr int HT = FC / 32;                   // a producer's hidden tiles
     static constexpr int CTH = CT / 2;                   // a consumer's channel tiles
     static constexpr int ZLD = C + 4;                    // floats per row of output sums (bank spread)
@@ -195,21 +200,21 @@ template <int C> struct MlpPCCfg {
     static constexpr int PART_COPIES = PART_BYTES / 1024;
     static constexpr int HTILE = PT * KM * 64 * 16;      // bytes: a group's h fragments
     static constexpr int YB = PART_BYTES;                // LN2(y) fragments on their way: past W_a's first slot
-    static constexpr int PIPE = 4 * PART_BYTES + 2 * 2 * HTILE, ROWS = 128 * ZLD * 4;
+    static constexpr int PIPE = 4 * PART_BYTES + 2 * 2 * HTILE, ROWS = PTS * ZLD * 4;
     static constexpr int LDS_BYTES = PIPE > ROWS ? PIPE : ROWS;
-    static_assert(YB + 8 * CK * 1024 <= LDS_BYTES, "rows pass through the slots");
+    static_assert(YB + 2 * PT * CK * 1024 <= LDS_BYTES, "rows pass through the slots");
     static_assert(PART_COPIES % 4 == 0, "each consumer issues a quarter of a part's copies");
     static_assert(HT == 1 || HT == 2, "a producer's hidden units are half a K step or one");
 };
 
-template <int C, int F>
+template <int C, int F, int PT>
 __global__ __launch_bounds__(512, C <= 128 ? 4 : 1) void k_mlp_residual_pc(
     const bf16_t *x, const bf16_t *__restrict__ pa, int64_t n, const float *__restrict__ ln2_g,
     const float *__restrict__ ln2_b, const bf16_t *__restrict__ frag, const float *__restrict__ ba,
     const float *__restrict__ bb, const float *__restrict__ lnn_g, const float *__restrict__ lnn_b, bf16_t *xo,
     bf16_t *__restrict__ xn) {
-    using Cfg = MlpPCCfg<C>;
-    constexpr int CK = Cfg::CK, CTH = Cfg::CTH, KM = Cfg::KM, PT = Cfg::PT, HT = Cfg::HT;
+    using Cfg = MlpPCCfg<C, PT>;
+    constexpr int CK = Cfg::CK, CTH = Cfg::CTH, KM = Cfg::KM, HT = Cfg::HT;
     constexpr int NCHUNK = F / Cfg::FC, PB = Cfg::PART_BYTES, HTILE = Cfg::HTILE;
     static_assert(F % Cfg::FC == 0, "hidden width in whole chunks");
     __shared__ __attribute__((aligned(1024))) unsigned char lds[Cfg::LDS_BYTES];
@@ -221,7 +226,6 @@ __global__ __launch_bounds__(512, C <= 128 ? 4 : 1) void k_mlp_residual_pc(
     const int q = wave & 3, role = wave >> 2;
     const int grp = q >> 1, half = q & 1;
     const int li = lane & 15, g = lane >> 4;
-    const int64_t p0 = (int64_t)blockIdx.x * 128 + grp * 64;
     unsigned char *const hslots = lds + 4 * PB + grp * 2 * HTILE;  // the group's two h tiles
 
     // A consumer's quarter of part `half` (0: W_a^T, 1: W_b) of chunk j into slot sl.
@@ -235,10 +239,11 @@ __global__ __launch_bounds__(512, C <= 128 ? 4 : 1) void k_mlp_residual_pc(
         }
     };
 
-    // Wave w takes points 16w .. of the block, whole rows, before and after the chunks
+    // Wave w < 2 PT takes points 16w .. of the block, whole rows, before and after the chunks
     // (one memory round trip each way, no row read twice): lane (li, g) holds channels
     // 32k + 8g .. +7 of point row(w) = blk + 16w + li.
-    const int64_t pr = (int64_t)blockIdx.x * 128 + wave * 16 + li;
+    const bool rows = wave < 2 * PT;
+    const int64_t pr = (int64_t)blockIdx.x * Cfg::PTS + wave * 16 + li;
     const int64_t prc = pr < n ? pr : n - 1;
     auto load_row = [&](uint4 (&xv)[CK], uint4 (&pv)[CK]) {
 #pragma unroll
@@ -278,7 +283,7 @@ __global__ __launch_bounds__(512, C <= 128 ? 4 : 1) void k_mlp_residual_pc(
         }
     };
     if (role == 1) issue_part(0, 0, 0);
-    {   // LN2(x + pa) as B fragments of tile `wave`, through LDS
+    if (rows) {  // LN2(x + pa) as B fragments of tile `wave`, through LDS
         uint4 xv[CK], pv[CK];
         load_row(xv, pv);
         float y[CK][8];
@@ -298,7 +303,7 @@ __global__ __launch_bounds__(512, C <= 128 ? 4 : 1) void k_mlp_residual_pc(
     wait_vmcnt<0>();
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __syncthreads();  // every tile's fragments and W_a(0) are in LDS
-    float *const zrows = reinterpret_cast<float *>(lds);  // after the chunks: [128][ZLD] output sums
+    float *const zrows = reinterpret_cast<float *>(lds);  // after the chunks: [PTS][ZLD] output sums
     constexpr int ZLD = Cfg::ZLD;
 
     if (role == 0) {
@@ -406,14 +411,15 @@ __global__ __launch_bounds__(512, C <= 128 ? 4 : 1) void k_mlp_residual_pc(
         for (int ct = 0; ct < CTH; ++ct)
 #pragma unroll
             for (int pt = 0; pt < PT; ++pt)
-                *reinterpret_cast<f32x4 *>(zrows + (grp * 64 + pt * 16 + li) * ZLD + half * (C / 2) + 32 * (ct >> 1) + 8 * g +
+                *reinterpret_cast<f32x4 *>(zrows + (grp * 16 * PT + pt * 16 + li) * ZLD + half * (C / 2) + 32 * (ct >> 1) + 8 * g +
                                            4 * (ct & 1)) = Z[ct][pt];
     }
     // out = x + pa + z + bb and the next block's LN1 of the rounded output
     uint4 xv[CK], pv[CK];
-    load_row(xv, pv);
+    if (rows) load_row(xv, pv);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __syncthreads();  // the sums are in LDS
+    if (!rows) return;
     float o[CK][8];
 #pragma unroll
     for (int k = 0; k < CK; ++k) {

@@ -31,28 +31,32 @@
 
 namespace ts3 {
 
-template <int C, int M> struct Pass2PCCfg {
-    static constexpr int MT = M / 16, CK = C / 32, CT = C / 16, KM = M / 32, PT = 2;
+// PT: 16-point tiles per pair of waves, 2 or, for a call that fills at most one round of
+// compute units so, 1 (the figures above are for 2).  A workgroup's heads are one chain:
+// 4,096 points ran 32 workgroups and took 18.5 us, with 64-point
+// blocks 13.2 us (16,384 points 20.3 and 15.5 us).
+template <int C, int M, int PT> struct Pass2PCCfg {
+    static constexpr int MT = M / 16, CK = C / 32, CT = C / 16, KM = M / 32;
     static constexpr int PART = M * C;               // elements of W2'_h (= of Z_h)
     static constexpr int PB = PART * 2;              // bytes
     static constexpr int PART_COPIES = PB / 1024;
     static constexpr int HTILE = PT * KM * 64 * 16;  // bytes: a pair's w fragments
     static constexpr int LDS_BYTES = 4 * PB + 4 * 2 * HTILE;
-    static constexpr int POINTS_PER_WG = 128;
+    static constexpr int POINTS_PER_WG = 64 * PT;
     static_assert(M % 32 == 0, "slice tiles pair into K32 steps");
     static_assert(PART_COPIES % 4 == 0, "each consumer issues a quarter of a part's copies");
 };
 
 // x: [n][C] bf16; w2p: [H][MT][CK][64][8]; zp: [H][CT][KM][64][8]; b2s:
-// [H*M]; out: [n][C] bf16.  Grid: at most ceil(n / 128) persistent
+// [H*M]; out: [n][C] bf16.  Grid: at most ceil(n / (64 PT)) persistent
 // workgroups of 512 threads.
-template <int C, int M>
+template <int C, int M, int PT>
 __global__ __launch_bounds__(512, 1) void k_deslice_pc(const bf16_t *__restrict__ x, int64_t n, int32_t H,
                                                        const bf16_t *__restrict__ w2p, const float *__restrict__ b2s,
                                                        const bf16_t *__restrict__ zp, bf16_t *__restrict__ out) {
-    using Cfg = Pass2PCCfg<C, M>;
+    using Cfg = Pass2PCCfg<C, M, PT>;
     using T = bf16_t;
-    constexpr int MT = Cfg::MT, CK = Cfg::CK, CT = Cfg::CT, KM = Cfg::KM, PT = Cfg::PT;
+    constexpr int MT = Cfg::MT, CK = Cfg::CK, CT = Cfg::CT, KM = Cfg::KM;
     constexpr int PB = Cfg::PB, HTILE = Cfg::HTILE;
     __shared__ __attribute__((aligned(1024))) unsigned char lds[Cfg::LDS_BYTES];
     unsigned char *const wslots = lds;           // W2'_h parts, two slots
@@ -67,7 +71,7 @@ __global__ __launch_bounds__(512, 1) void k_deslice_pc(const bf16_t *__restrict_
     if (n <= 0 || H <= 0 || (int64_t)blockIdx.x >= nblk) return;  // uniform over the workgroup
     const int iters = (int)((nblk - 1 - blockIdx.x) / gridDim.x + 1);  // blocks of this workgroup
     const int S = iters * H;                                          // (block, head) steps
-    const int64_t pw = (int64_t)blockIdx.x * Cfg::POINTS_PER_WG + q * 32;
+    const int64_t pw = (int64_t)blockIdx.x * Cfg::POINTS_PER_WG + q * (16 * PT);
     const int64_t bstride = (int64_t)gridDim.x * Cfg::POINTS_PER_WG;
 
     if (role == 0) {

@@ -34,12 +34,29 @@ template <int C> void launch_ln(const bf16_t *x, int64_t n, const float *g, cons
 template <int C> void launch_prep(const float *Wa, const float *Wb, int F, bf16_t *frag, hipStream_t st) {
     hipLaunchKernelGGL(k_prep_mlp<C>, dim3(1024), dim3(256), 0, st, Wa, Wb, F, frag);
 }
+// Point tiles per group of the feed-forward kernel: the fewest whose workgroups fill at
+// most one round of compute units, which hold two workgroups each at C = 128.  With the
+// operands' preparation, PT = 4 and the rule's, in us: C = 256, 4,096 points 50 and 30,
+// 8,192 (1) 53 and 33, 16,384 (2) 58 and 43; C = 128, 4,096 points 24 and 18, 16,384 (1)
+// 27 and 21, 32,768 (2) 33 and 32.
+int mlp_tiles(int64_t n, int C) {
+    const int64_t round = (int64_t)device_cu_count() * (C <= 128 ? 2 : 1);
+    return n <= round * 32 ? 1 : n <= round * 64 ? 2 : 4;
+}
 template <int C, int F>
 void launch_mlp(const bf16_t *x, const bf16_t *pa, int64_t n, const float *l2g, const float *l2b,
                 const bf16_t *frag, const float *ba, const float *bb, const float *lng, const float *lnb, bf16_t *xo,
                 bf16_t *xn, hipStream_t st) {
-    hipLaunchKernelGGL((k_mlp_residual_pc<C, F>), dim3((unsigned)((n + 127) / 128)), dim3(512), 0, st, x, pa, n,
-                       l2g, l2b, frag, ba, bb, lng, lnb, xo, xn);
+    auto launch = [&](auto pt) {
+        constexpr int PT = decltype(pt)::value, PTS = MlpPCCfg<C, PT>::PTS;
+        hipLaunchKernelGGL((k_mlp_residual_pc<C, F, PT>), dim3((unsigned)((n + PTS - 1) / PTS)), dim3(512), 0, st, x, pa,
+                           n, l2g, l2b, frag, ba, bb, lng, lnb, xo, xn);
+    };
+    switch (mlp_tiles(n, C)) {
+        case 1: return launch(std::integral_constant<int, 1>{});
+        case 2: return launch(std::integral_constant<int, 2>{});
+        default: return launch(std::integral_constant<int, 4>{});
+    }
 }
 
 bool find_stack_kernels(int C, int F, StackKernels *k) {

@@ -127,3 +127,32 @@ def test_feedforward_half_matches_the_oracle_and_writes_the_next_layernorm():
     ref = y + BK.mlp(BK.layer_norm(y, b[0]["ln2_g"], b[0]["ln2_b"]), b[0]["Wa"], b[0]["ba"], b[0]["Wb"], b[0]["bb"])
     assert_bf16_close(got, ref, "feed-forward", BF16_TOL)
     assert_bf16_close(got_xn, BK.layer_norm(ref, b[1]["ln1_g"], b[1]["ln1_b"]), "next LN1", BF16_TOL)
+
+
+@pytest.mark.parametrize("C,n", [(128, 1), (128, 33), (128, 16_384), (128, 16_385), (256, 31), (256, 8_192), (256, 16_384)])
+def test_a_small_call_gives_the_rows_of_a_large_one(C, n):
+    """Small calls take fewer points per workgroup (at C = 256 up to 8,192 and 16,384
+    points on 256 compute units, at C = 128 twice that): a point's result must not
+    depend on it."""
+    import torch
+    H, M, L, big = 8, 64, 2, 34_000
+    F = 4 * C
+    banner(f"feed-forward and decoding in small calls, C={C} n={n}")
+    rng = np.random.default_rng(29)
+    x = to_device(round_bf16(rng.standard_normal((big, C))), "bf16")
+    pa = to_device(round_bf16(0.5 * rng.standard_normal((big, C))), "bf16")
+    dev = _dev_blocks(_blocks(C, H, M, F, L, seed=70))
+    with _stack(C, H, M, L, 4096, big) as st:
+        whole, xn = x.clone(), torch.empty_like(x)
+        st.feedforward(dev, 0, whole, pa, xn_next=xn)
+        few, few_xn = x[:n].clone(), torch.full_like(x[:n + 1], 7.0)
+        st.feedforward(dev, 0, few, pa[:n], xn_next=few_xn[:n])
+        mesh = x.clone()
+        st.forward(dev, mesh, tile=4096, chunk=big)
+        q, q_few = x.clone(), x[:n].clone()
+        st.decode(dev, q, chunk=big)
+        st.decode(dev, q_few, chunk=n)
+        torch.cuda.synchronize()
+    assert torch.equal(few, whole[:n])
+    assert torch.equal(few_xn[:n], xn[:n]) and bool((few_xn[n] == 7.0).all())
+    assert torch.equal(q_few, q[:n])
