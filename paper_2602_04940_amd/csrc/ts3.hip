@@ -1025,10 +1025,13 @@ ts3_status ts3_layer_backward(ts3_state *st, const ts3_weights *w, const void *x
     ts3_status s = fold_partials(st, st->geo.parts(N), d.C, st->bdZ, st->bdd, hs);
     if (s != TS3_OK) return s;
     // token side: ds_raw, dd and the Linear1 / attention / Linear3 gradients
-    const size_t lds = (size_t)(2 * d.M * d.C + 10 * d.M * d.dh + 2 * d.M * d.M) * 4;
+    size_t lds = bw_token_lds(d.C, d.M, d.dh, false);
     if (lds > (size_t)ATTN_LDS_MAX) return fail(TS3_ERR_UNSUPPORTED, "token backward needs %zu bytes of LDS", lds);
-    HIP_TRY(hipFuncSetAttribute((const void *)k_bw_token, hipFuncAttributeMaxDynamicSharedMemorySize, ATTN_LDS_MAX));
-    hipLaunchKernelGGL(k_bw_token, dim3(d.H), dim3(BW_TOKEN_THREADS), lds, hs, st->s_raw, st->dsum, st->s, st->s1, st->bdZ,
+    const bool staged = bw_token_lds(d.C, d.M, d.dh, true) <= (size_t)ATTN_LDS_MAX;
+    if (staged) lds = bw_token_lds(d.C, d.M, d.dh, true);
+    const auto token = staged ? &k_bw_token<true> : &k_bw_token<false>;
+    HIP_TRY(hipFuncSetAttribute((const void *)token, hipFuncAttributeMaxDynamicSharedMemorySize, ATTN_LDS_MAX));
+    hipLaunchKernelGGL(token, dim3(d.H), dim3(BW_TOKEN_THREADS), lds, hs, st->s_raw, st->dsum, st->s, st->s1, st->bdZ,
                        w->W1, w->Wq, w->Wk, w->Wv, w->W3, d.C, d.H, d.M, d.dh, d.eps, st->bdsr, st->bdd,
                        gr->dW1, gr->db1, gr->dWq, gr->dWk, gr->dWv, gr->dW3, gr->db3);
     LAUNCH_CHECK("token backward");

@@ -58,8 +58,17 @@ __device__ __forceinline__ void softmax_tile(f32x4 (&E)[MT], float scale) {
 //   mean = s_raw / (d + eps) (0 where d + eps <= 0) -> ds_raw, dd
 // and db3 = sum_m dZ[0][m] (every head's weights sum to one per point).
 // Dynamic LDS: floats mean, dZ [M][C] and s, s1, q, k, v, ds1, dq, dk, dv, ds
-// [M][dh] and P, dP [M][M].
+// [M][dh] and P, dP [M][M]; STAGED also W3_h and then W1_h^T [dh][C], with a float of
+// padding per row of those, dZ, k and v.  Bound by LDS and by the lines that a load
+// touches: where lanes run over the rows of W3_h or W1_h each load from memory takes one
+// line per lane, and where they run over k's rows sixteen share a bank.  131 us at C =
+// 128, M = 64 from memory and without padding, 49 us staged; the other form serves the
+// shape whose LDS that would exceed (one head of width 128).
 constexpr int BW_TOKEN_THREADS = 1024;
+inline size_t bw_token_lds(int C, int M, int dh, bool staged) {
+    return (size_t)(2 * M * C + 10 * M * dh + 2 * M * M + (staged ? dh * (C + 1) + 3 * M : 0)) * 4;
+}
+template <bool STAGED>
 __global__ __launch_bounds__(BW_TOKEN_THREADS, 1) void k_bw_token(
     const float *__restrict__ s_raw, const float *__restrict__ dsum, const float *__restrict__ s,
     const float *__restrict__ s1, const float *__restrict__ dZ, const float *__restrict__ W1,
@@ -71,28 +80,31 @@ __global__ __launch_bounds__(BW_TOKEN_THREADS, 1) void k_bw_token(
     extern __shared__ float sm[];
     const int h = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
     const int HD = H * dh;
+    const int gp = STAGED ? C + 1 : C, kp = STAGED ? dh + 1 : dh;  // row strides of gz (and wl), k and v
     float *mean = sm, *gz = mean + M * C;
-    float *ss = gz + M * C, *s1s = ss + M * dh, *q = s1s + M * dh, *k = q + M * dh, *v = k + M * dh;
-    float *ds1 = v + M * dh, *dq = ds1 + M * dh, *dk = dq + M * dh, *dv = dk + M * dh, *ds = dv + M * dh;
-    float *P = ds + M * dh, *dP = P + M * M;
+    float *ss = gz + M * gp, *s1s = ss + M * dh, *q = s1s + M * dh, *k = q + M * dh, *v = k + M * kp;
+    float *ds1 = v + M * kp, *dq = ds1 + M * dh, *dk = dq + M * dh, *dv = dk + M * dh, *ds = dv + M * dh;
+    float *P = ds + M * dh, *dP = P + M * M, *wl = dP + M * M;
     const float scale = 1.f / sqrtf((float)dh);
     for (int i = tid; i < M * C; i += nt) {
         const int m = i / C;
         const float den = dsum[h * M + m] + eps;
         mean[i] = den > 0.f ? s_raw[(size_t)h * M * C + i] / den : 0.f;
-        gz[i] = dZ[(size_t)h * M * C + i];
+        gz[m * gp + (i - m * C)] = dZ[(size_t)h * M * C + i];
     }
     for (int i = tid; i < M * dh; i += nt) {
         ss[i] = s[(size_t)h * M * dh + i];
         s1s[i] = s1[(size_t)h * M * dh + i];
     }
+    if constexpr (STAGED)
+        for (int i = tid; i < dh * C; i += nt) wl[i / C * gp + i % C] = W3[(size_t)h * dh * C + i];
     __syncthreads();
     // ds1 = dZ W3_h^T; dW3_h = s1^T dZ; q, k, v
     for (int i = tid; i < M * dh; i += nt) {
         const int m = i / dh, j = i % dh;
         float a = 0.f, aq = 0.f, ak = 0.f, av = 0.f;
 #pragma unroll 8
-        for (int c = 0; c < C; ++c) a += gz[m * C + c] * W3[(size_t)(h * dh + j) * C + c];
+        for (int c = 0; c < C; ++c) a += gz[m * gp + c] * (STAGED ? wl[j * gp + c] : W3[(size_t)(h * dh + j) * C + c]);
 #pragma unroll 8
         for (int t = 0; t < dh; ++t) {
             const float sv = ss[m * dh + t];
@@ -102,29 +114,34 @@ __global__ __launch_bounds__(BW_TOKEN_THREADS, 1) void k_bw_token(
         }
         ds1[i] = a;
         q[i] = aq;
-        k[i] = ak;
-        v[i] = av;
+        k[m * kp + j] = ak;
+        v[m * kp + j] = av;
     }
     for (int i = tid; i < dh * C; i += nt) {
         const int j = i / C, c = i % C;
         float a = 0.f;
-        for (int m = 0; m < M; ++m) a += s1s[m * dh + j] * gz[m * C + c];
+#pragma unroll 8
+        for (int m = 0; m < M; ++m) a += s1s[m * dh + j] * gz[m * gp + c];
         dW3[(size_t)(h * dh + j) * C + c] = a;
     }
     if (h == 0)
         for (int c = tid; c < C; c += nt) {
             float a = 0.f;
-            for (int m = 0; m < M; ++m) a += gz[m * C + c];
+#pragma unroll 8
+            for (int m = 0; m < M; ++m) a += gz[m * gp + c];
             db3[c] = a;
         }
     __syncthreads();
+    if constexpr (STAGED)  // W3_h is no longer read
+        for (int i = tid; i < dh * C; i += nt) wl[i % dh * gp + i / dh] = W1[(size_t)(i / dh) * HD + h * dh + i % dh];
     // P = softmax_rows(q k^T * scale); dP = ds1 v^T
     for (int i = tid; i < M * M; i += nt) {
         const int a_ = i / M, b_ = i % M;
         float dot = 0.f, dpv = 0.f;
+#pragma unroll 8
         for (int j = 0; j < dh; ++j) {
-            dot += q[a_ * dh + j] * k[b_ * dh + j];
-            dpv += ds1[a_ * dh + j] * v[b_ * dh + j];
+            dot += q[a_ * dh + j] * k[b_ * kp + j];
+            dpv += ds1[a_ * dh + j] * v[b_ * kp + j];
         }
         P[i] = dot * scale;
         dP[i] = dpv;
@@ -157,9 +174,10 @@ __global__ __launch_bounds__(BW_TOKEN_THREADS, 1) void k_bw_token(
     for (int i = tid; i < M * dh; i += nt) {
         const int m = i / dh, j = i % dh;
         float av = 0.f, aq = 0.f, ak = 0.f;
+#pragma unroll 8
         for (int t = 0; t < M; ++t) {
             av += P[t * M + m] * ds1[t * dh + j];
-            aq += dP[m * M + t] * k[t * dh + j];
+            aq += dP[m * M + t] * k[t * kp + j];
             ak += dP[t * M + m] * q[t * dh + j];
         }
         dv[i] = av;
@@ -171,6 +189,7 @@ __global__ __launch_bounds__(BW_TOKEN_THREADS, 1) void k_bw_token(
     for (int i = tid; i < dh * dh; i += nt) {
         const int t = i / dh, j = i % dh;
         float aq = 0.f, ak = 0.f, av = 0.f;
+#pragma unroll 8
         for (int m = 0; m < M; ++m) {
             const float sv = ss[m * dh + t];
             aq += sv * dq[m * dh + j];
@@ -184,6 +203,7 @@ __global__ __launch_bounds__(BW_TOKEN_THREADS, 1) void k_bw_token(
     for (int i = tid; i < M * dh; i += nt) {
         const int m = i / dh, t = i % dh;
         float a = 0.f;
+#pragma unroll 8
         for (int j = 0; j < dh; ++j)
             a += dq[m * dh + j] * Wq[((size_t)h * dh + t) * dh + j] + dk[m * dh + j] * Wk[((size_t)h * dh + t) * dh + j] +
                  dv[m * dh + j] * Wv[((size_t)h * dh + t) * dh + j];
@@ -194,11 +214,13 @@ __global__ __launch_bounds__(BW_TOKEN_THREADS, 1) void k_bw_token(
     for (int i = tid; i < C * dh; i += nt) {
         const int c = i / dh, j = i % dh;
         float a = 0.f;
+#pragma unroll 8
         for (int m = 0; m < M; ++m) a += mean[m * C + c] * ds[m * dh + j];
         dW1[(size_t)c * HD + h * dh + j] = a;
     }
     for (int j = tid; j < dh; j += nt) {
         float a = 0.f;
+#pragma unroll 8
         for (int m = 0; m < M; ++m) a += ds[m * dh + j];
         db1[h * dh + j] = a;
     }
@@ -206,17 +228,18 @@ __global__ __launch_bounds__(BW_TOKEN_THREADS, 1) void k_bw_token(
     for (int i = tid; i < M * C; i += nt) {
         const int m = i / C, c = i % C;
         float a = 0.f;
-        for (int j = 0; j < dh; ++j) a += ds[m * dh + j] * W1[(size_t)c * HD + h * dh + j];
+#pragma unroll 8
+        for (int j = 0; j < dh; ++j) a += ds[m * dh + j] * (STAGED ? wl[j * gp + c] : W1[(size_t)c * HD + h * dh + j]);
         const float den = dsum[h * M + m] + eps;
         const float r = den > 0.f ? a / den : 0.f;
-        gz[i] = a;
+        gz[m * gp + c] = a;
         dsr[(size_t)h * M * C + i] = r;
     }
     __syncthreads();
     for (int m = tid >> 4; m < M; m += nt >> 4) {
         const float den = dsum[h * M + m] + eps;
         float a = 0.f;
-        for (int c = tid & 15; c < C; c += 16) a += gz[m * C + c] * mean[m * C + c];
+        for (int c = tid & 15; c < C; c += 16) a += gz[m * gp + c] * mean[m * C + c];
         a = row16_sum(a);
         if ((tid & 15) == 0) dd[h * M + m] = den > 0.f ? -a / den : 0.f;
     }

@@ -16,6 +16,33 @@ from ts3_synth import make_weights
 pytestmark = pytest.mark.gpu
 
 
+@pytest.mark.parametrize("C,H,M", [
+    (128, 1, 16),   # one head of width 128: its backward leaves Linear1 and Linear3 in memory
+    (128, 2, 32),   # 150 KB of LDS with them
+    (64, 16, 16),   # heads of width 4
+])
+def test_token_backward(C, H, M):
+    import torch
+    from oracle import backward as BW
+    from paper_2602_04940_amd import LayerWeights, PhysicsAttention
+    N = 700
+    banner(f"token backward: C={C} H={H} M={M}")
+    rng = np.random.default_rng(9)
+    x64, g64 = (rng.standard_normal((N, C)).astype(np.float32).astype(np.float64) for _ in range(2))
+    W = make_weights(C, H, M, C // H, seed=6, bias_seed=7)
+    ref = BW.layer_backward(x64, {k: np.asarray(v, np.float64) for k, v in W.items()}, g64, H, M, 2.0)
+    lw, x, g = LayerWeights(W), to_device(x64, "fp32"), to_device(g64, "fp32")
+    with PhysicsAttention(C, H, M, C // H, 0.5, "fp32", group_span=256, max_points=N) as layer:
+        layer.forward(lw, x, tile=256)
+        dx, grads = layer.backward(lw, x, g, tile=256)
+        torch.cuda.synchronize()
+    got = dict(dx=to_host(dx), **{k: v.cpu().numpy().astype(np.float64) for k, v in grads.items()})
+    for k in ("dx", "dW2", "db2", "dW1", "db1", "dWq", "dWk", "dWv", "dW3", "db3"):
+        e = normwise(got[k], ref[k])
+        print(f"{k}: normwise {e:.2e}", flush=True)
+        assert e <= 1e-4, (k, e)
+
+
 @pytest.mark.parametrize("C,H,M,N,Q,accum,biases", [
     (96, 32, 16, 700, 64, "fp32", True),      # head width 3: 85 groups of threads, one thread idle
     (240, 1, 16, 300, 300, "fp64", True),     # head width 240: one group of threads
