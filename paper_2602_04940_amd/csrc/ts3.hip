@@ -29,6 +29,7 @@
 #include "ts3_token.h"
 #include "ts3_rt.h"
 #include "ts3_pass2sf.h"
+#include "ts3_pass2sh.h"
 
 using namespace ts3;
 
@@ -243,6 +244,14 @@ hipError_t launch_pass2sf(const void *x, int64_t n, const void *w2p, const float
     // fallback blocks in a 64-bit mask); larger calls are split, which changes
     // no result: every point is decoded alone.
     const int64_t cus = device_cu_count();
+    // A head per wave while no compute unit has more than SH_MAX_ITERS of its blocks
+    // (see k_deslice_sh for both sides' times).
+    if (n > 0 && n <= cus * SH_MAX_ITERS * 32) {
+        hipLaunchKernelGGL((k_deslice_sh<C, M>), dim3((unsigned)std::min((n + 31) / 32, cus)), dim3(4 * C), 0, st,
+                           (const bf16_t *)x, n, (const bf16_t *)w2p, b2s, (const bf16_t *)sf, (const bf16_t *)w3f, b3,
+                           (bf16_t *)out);
+        return hipSuccess;
+    }
     const int64_t span = cus * P2_MAX_ITERS * Cfg::POINTS_PER_WG;
     for (int64_t off = 0; off < n; off += span) {
         const int64_t m = std::min<int64_t>(span, n - off);
