@@ -150,9 +150,10 @@ COUNTER_KERNELS = {
     "k_slice_accumulate_pcw<": (1_000_000, 4 * 256 * 512, 512, PEAK_BF16_TFLOPS),
     "k_deslice_pc<": (1_000_000, 4 * 256 * 512, 1024, PEAK_BF16_TFLOPS),
     "k_mlp_residual_pc<": (1_000_000, 4 * 256 * 1024, 1536, PEAK_BF16_TFLOPS),
-    "k_bw_head<": (1_000_000, 4 * 128 * 512, 1024, 157.3),
-    "k_bw_dx<": (1_000_000, 10 * 128 * 512, 1536 + 4 * 512, 157.3),
-    "k_bw_dw2<": (1_000_000, 2 * 128 * 512, 512 + 4 * 512, 157.3),
+    # three-part operands: six bf16 products for each float32 one
+    "k_sum3<128, 64, (ts3::Sum3)1>": (1_000_000, 6 * 4 * 128 * 512, 1024, PEAK_BF16_TFLOPS),
+    "k_bw_dx3<": (1_000_000, 6 * 10 * 128 * 512, 1536 + 4 * 512, PEAK_BF16_TFLOPS),
+    "k_sum3<128, 64, (ts3::Sum3)2>": (1_000_000, 6 * 2 * 128 * 512, 512 + 4 * 512, PEAK_BF16_TFLOPS),
 }
 
 

@@ -69,8 +69,10 @@ typedef enum { TS3_ACCUM_FP32 = 0, TS3_ACCUM_FP64 = 1 } ts3_accum;
  *                the slice-weight and contraction products on bf16 matrix
  *                cores with float32 accumulation; TS3_FP32 keeps every operand
  *                to float32 precision, as sums of three bf16 parts on bf16
- *                matrix cores with float32 accumulation.  The runtime-shape
- *                kernels keep the slice weights so for either storage type.
+ *                matrix cores with float32 accumulation (a float32 input or
+ *                gradient that is infinite, or beyond bfloat16's largest value,
+ *                gives NaN).  The runtime-shape kernels keep the slice weights
+ *                so for either storage type.
  *  group_span  : Q, points per accumulation span (1 <= Q <= 2^30).  Pass 1
  *                reduces each span to partials of its consecutive parts and sums
  *                them in index order, so results do not depend on how the mesh

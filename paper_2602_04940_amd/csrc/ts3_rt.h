@@ -7,9 +7,8 @@
 // in float32 (x, W2', Z of float32 storage, and the slice weights of either
 // storage) enters as three bfloat16 parts (Parts), so no operand is rounded.  As
 // plain vector arithmetic these kernels took 12.8 + 2.2 ms for 30,000 float32
-// points at (C, H, M) = (256, 8, 64), bound by one LDS read per product, and now
-// 0.27 + 0.12 ms; 50,021 bf16 points at (192, 4, 48): 20.2 ms, now 0.17 ms for the
-// layer.
+// points at (C, H, M) = (256, 8, 64), bound by one LDS read per product, the layer now
+// 0.36 ms; 50,021 bf16 points at (192, 4, 48): 20.2 ms, now 0.15 ms.
 //
 // Operand layouts (16-bit parts, NP = 3 for float32 storage, 1 for bf16; written by
 // k_prep_w2_rt, k_prep_z_rt and k_attend, zero past C and past the last slice):
