@@ -59,6 +59,10 @@ template <int C, int M> struct Pass2SFCfg {
     static constexpr int NXLOAD = PT * CK;  // x fragments of a wave block: one per head
     static constexpr int NW3 = CK * CT;     // W3^T fragments (K steps outermost)
     static constexpr int W3_AHEAD = 8;      // W3^T fragments in flight
+    // step of the last product whose MFMAs the next block's x loads follow: the one that
+    // issues the last W3^T fragment, or the first where all of them are in flight before it
+    static constexpr int X_STEP = NW3 > W3_AHEAD ? NW3 - 1 - W3_AHEAD : 0;
+    static_assert(X_STEP >= 0 && X_STEP < NW3, "the next block's x is loaded in one of the steps");
     static_assert(M % 32 == 0 && C % 32 == 0, "slice and channel tiles pair into K32 steps");
     static_assert(H % 2 == 0, "two heads' u fill one K32 step of the Linear3 product");
     static_assert(NXLOAD == H, "one x fragment of the next block per head");
@@ -340,7 +344,7 @@ __global__ __launch_bounds__(512, 1) void k_deslice_sf(const bf16_t *__restrict_
                 for (int pt = 0; pt < PT; ++pt) mma(O[ct][pt], a[q % AHEAD], ub[kk][pt]);
                 __builtin_amdgcn_sched_barrier(0);
                 if constexpr (q + AHEAD < NW3) w3frag(q + AHEAD, a[q % AHEAD]);
-                if constexpr (q + AHEAD == NW3 - 1) {
+                if constexpr (q == Cfg::X_STEP) {
 #pragma unroll
                     for (int j = 0; j < Cfg::NXLOAD; ++j) load_xfrag(p0 + bstride, j, xb);
                 }

@@ -1,0 +1,57 @@
+"""Decoding more points than one block per workgroup, for every bf16 kernel of pass 2:
+rows of late blocks and of the ragged last one against the oracle, through deslice, forward
+with small and large chunks and the entry that allocates nothing, which must all give
+the same bits, and the same twice.
+
+65,537 points are one more than one block per workgroup of the 256-point kernels on 256
+compute units; 600,001 points give a workgroup up to ten blocks.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_helpers import assert_bf16_close, banner, to_host
+from ts3_synth import make_weights
+
+pytestmark = pytest.mark.gpu
+
+SIZES = (65_537, 100_003, 600_001)
+TILE = 65_536
+
+
+@pytest.mark.parametrize("C,H,M", [
+    (64, 4, 16), (64, 2, 32), (128, 8, 16), (128, 4, 64),  # a head's Z at a time
+    (64, 4, 32), (128, 8, 32), (128, 8, 64),               # slice-state form
+    (256, 8, 64),                                          # wide rows
+])
+def test_late_blocks_match_the_oracle_by_every_route(C, H, M):
+    import torch
+    from paper_2602_04940_amd import LayerWeights, PhysicsAttention
+    from paper_2602_04940_amd import _lib as L
+    from paper_2602_04940_amd.layer import layer_forward_noalloc
+    rng = np.random.default_rng(C + M)
+    big = max(SIZES)
+    xs = torch.randn((big, C), generator=torch.Generator("cuda").manual_seed(M), device="cuda").to(torch.bfloat16)
+    W = make_weights(C, H, M, C // H, seed=3, bias_seed=4)
+    lw = LayerWeights(W)
+    for n in SIZES:
+        banner(f"late blocks: C={C} H={H} M={M} bf16, {n} points")
+        x = xs[:n].contiguous()
+        noalloc = torch.empty_like(x)
+        layer_forward_noalloc(C, H, M, lw, x, TILE, TILE, noalloc, group_span=8192)
+        with PhysicsAttention(C, H, M, C // H, 0.5, "bf16", group_span=8192, max_points=n) as layer:
+            out = layer.forward(lw, x, tile=TILE, chunk=TILE).clone()
+            Z = layer.get(L.TS3_ZP).astype(np.float64)
+            whole = layer.deslice(lw, x)
+            again = layer.deslice(lw, x)
+            large = layer.forward(lw, x, tile=TILE, chunk=1_000_000)
+        torch.cuda.synchronize()
+        for what, got in (("deslice", whole), ("second deslice", again), ("chunks of 1M", large), ("no-alloc", noalloc)):
+            assert torch.equal(got, out), (n, what)
+        # the first and last rows of each 65,536, some between, and the ragged end
+        rows = np.unique(np.concatenate(
+            [np.arange(a, min(a + 16, n)) for a in range(0, n, 65_536)] + [np.arange(n - 300, n)] +
+            [rng.integers(a, min(a + 65_536, n), 64) for a in range(0, n, 65_536)]))
+        xr = to_host(x[torch.from_numpy(rows).cuda()])
+        assert_bf16_close(to_host(out[torch.from_numpy(rows).cuda()]),
+                          oracle.deslice(xr, W["W2"], W["b2"], Z, W["b3"], H, M, 2.0), f"{n} points", block=16)
