@@ -368,6 +368,10 @@ __global__ __launch_bounds__(512, 1) void k_deslice_sf(const bf16_t *__restrict_
                            (__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]};
             }
     }
+    // Waves with rows past the end have written the last row too: their stores are done
+    // before a wave that owns the row writes it again below.
+    wait_vmcnt<0>();
+    __syncthreads();
     // Rare: blocks whose exp2 sums left the safe window, redone from
     // global-memory operands with the max-shifted softmax, 16 points at a time.
     while (failed) {

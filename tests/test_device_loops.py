@@ -59,3 +59,16 @@ def test_slice_state_decoder_loads_the_next_blocks_rows(sf_assembly, C, M):
     a, b = block_loop(lines, C // 16)
     loads = sum("global_load_dwordx4" in l for l in lines[a:b])
     assert loads == (C // 32) * (C // 16) + C // 16
+
+
+@pytest.mark.parametrize("C,M", SF_SHAPES)
+def test_slice_state_decoder_waits_before_blocks_are_redone(sf_assembly, C, M):
+    """Waves past the end of a ragged block write the last row as computed by the unshifted
+    softmax; the wave that owns it may write it again only after them: a wait for the
+    stores and a barrier lie between the block loop and the products of the redone blocks."""
+    lines = sf_assembly[C, M]
+    _, b = block_loop(lines, C // 16)
+    redo = next(i for i in range(b, len(lines)) if "v_mfma" in lines[i])
+    barrier = [i for i in range(b, redo) if "s_barrier" in lines[i]]
+    assert barrier
+    assert any("vmcnt(0)" in l for l in lines[b:barrier[0]])

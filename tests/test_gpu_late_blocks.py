@@ -55,3 +55,41 @@ def test_late_blocks_match_the_oracle_by_every_route(C, H, M):
         xr = to_host(x[torch.from_numpy(rows).cuda()])
         assert_bf16_close(to_host(out[torch.from_numpy(rows).cuda()]),
                           oracle.deslice(xr, W["W2"], W["b2"], Z, W["b3"], H, M, 2.0), f"{n} points", block=16)
+
+
+@pytest.mark.parametrize("C,H,M", [(64, 4, 32), (128, 8, 32), (128, 8, 64), (128, 4, 64), (256, 8, 64)])
+@pytest.mark.parametrize("n", [30_001, 65_537 + 224])
+def test_last_row_outside_the_unshifted_softmax(C, H, M, n):
+    """A last row whose logits leave the unshifted softmax's range, in a block with up to
+    seven waves past the end (which work on that row as well), alone and with 40 rows
+    before it.  The temperature makes W2' = W2, which is bfloat16, so the logits are exact
+    to float32 and one-hot weights are as sharp here as in the oracle."""
+    import torch
+    from paper_2602_04940_amd import LayerWeights, PhysicsAttention
+    from paper_2602_04940_amd import _lib as L
+    from ts3_synth import round_bf16
+    banner(f"last row outside the window: C={C} H={H} M={M} bf16, {n} points")
+    tau = float(np.float32(1.4426950408889634))
+    W = make_weights(C, H, M, C // H, seed=3, bias_seed=4)
+    W["W2"] = round_bf16(W["W2"].astype(np.float64)).astype(np.float32)
+    lw = LayerWeights(W)
+    rng = np.random.default_rng(n)
+    Z, b3 = rng.standard_normal((H, M, C)), rng.standard_normal(C)
+    xs = torch.randn((n, C), generator=torch.Generator("cuda").manual_seed(M), device="cuda")
+    for far in (1, 41):
+        x = xs.clone()
+        x[-far:] *= 400.0
+        x = x.to(torch.bfloat16)
+        with PhysicsAttention(C, H, M, C // H, tau, "bf16", group_span=8192, max_points=n) as layer:
+            layer.forward(lw, x, tile=65_536)
+            cached = [layer.deslice(lw, x) for _ in range(2)]
+            state = layer.get(L.TS3_ZP).astype(np.float64)
+            layer.set_state(lw, Z, b3)
+            injected = [layer.deslice(lw, x) for _ in range(2)]
+        torch.cuda.synchronize()
+        xr = to_host(x[-300:])
+        for what, (a, b), zz, bb in (("cached", cached, state, W["b3"]),
+                                     ("injected", injected, Z.astype(np.float32), b3.astype(np.float32))):
+            assert torch.equal(a, b), (far, what)
+            assert_bf16_close(to_host(a[-300:]), oracle.deslice(xr, W["W2"], W["b2"], zz, bb, H, M, 1 / tau),
+                              f"{far} far rows, {what}", block=16)
