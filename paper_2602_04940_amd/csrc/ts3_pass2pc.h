@@ -22,8 +22,8 @@
 // x during the current block's last head.  One barrier per step.
 //
 // Softmax: exp2 of the raw logits while every row sum stays in [2^-100,
-// 2^100] (then it equals the shifted softmax to float32 rounding); a tile
-// with a row outside the window takes the max-shifted softmax, from the
+// 2^100] (then it equals the shifted softmax to float32 rounding); a 16-point
+// tile with a row outside the window takes the max-shifted softmax, from the
 // logits kept in registers.
 #pragma once
 #include "ts3_device.h"
@@ -128,7 +128,7 @@ __global__ __launch_bounds__(512, 1) void k_deslice_pc(const bf16_t *__restrict_
                 if (h == H - 1 && i + 1 < iters) load_x(i + 1, xn);
                 f32x4 E[MT][PT];
                 float inv[PT];
-                bool ok = true;
+                bool out_of_range[PT];
 #pragma unroll
                 for (int pt = 0; pt < PT; ++pt) {
                     float sum = 0.f;
@@ -140,12 +140,13 @@ __global__ __launch_bounds__(512, 1) void k_deslice_pc(const bf16_t *__restrict_
                             sum += E[mt][pt][r];
                         }
                     sum = xrow_sum(sum);
-                    ok = ok && softmax_sum_ok(sum);
+                    out_of_range[pt] = !softmax_sum_ok(sum);
                     inv[pt] = fast_rcp(sum);
                 }
-                if (__any(!ok)) {
+                // Decided for each 16-point tile, so a row's result does not depend on PT.
 #pragma unroll
-                    for (int pt = 0; pt < PT; ++pt) {
+                for (int pt = 0; pt < PT; ++pt)
+                    if (__any(out_of_range[pt])) {
                         float mx = L[0][pt][0];
 #pragma unroll
                         for (int mt = 0; mt < MT; ++mt)
@@ -162,7 +163,6 @@ __global__ __launch_bounds__(512, 1) void k_deslice_pc(const bf16_t *__restrict_
                             }
                         inv[pt] = fast_rcp(xrow_sum(sum));
                     }
-                }
                 // The decode's B fragments, in fragment order.
                 unsigned char *wt = hslots + (s & 1) * HTILE;
 #pragma unroll

@@ -36,3 +36,22 @@ def test_small_calls_give_the_rows_of_a_large_one(C, H, M):
             layer.deslice(lw, x[:n], out[:n])
             assert bool((out[n] == 7.0).all()), n
             assert torch.equal(out[:n], whole[:n]), n
+
+
+def test_wide_rows_do_not_depend_on_the_calls_size():
+    """C = 256: up to 64 points per compute unit run in blocks of 64, more in blocks of 128.
+    Rows that need the shifted softmax take their tile of 16 there in either, so calls
+    that start on a multiple of 16 agree to the bit, such rows included."""
+    import torch
+    from paper_2602_04940_amd import LayerWeights, PhysicsAttention
+    C, H, M = 256, 8, 64
+    banner("decoding wide rows in small and large calls")
+    rng = np.random.default_rng(12)
+    x64 = rng.standard_normal((BIG, C))
+    x64[rng.integers(0, BIG, 300)] *= 400.0
+    x = to_device(round_bf16(x64), "bf16")
+    lw = LayerWeights(make_weights(C, H, M, C // H, seed=3, bias_seed=4))
+    with PhysicsAttention(C, H, M, C // H, 0.5, "bf16", group_span=4096, max_points=BIG) as layer:
+        whole = layer.forward(lw, x, tile=4096, chunk=BIG).clone()
+        for a, b in ((0, 4_096), (16, 8_000), (20_000, 36_384), (39_984, BIG), (0, 16_384), (0, 16_400)):
+            assert torch.equal(layer.deslice(lw, x[a:b]), whole[a:b]), (a, b)
