@@ -1126,8 +1126,10 @@ ts3_status ts3_state_get_spans(const ts3_state *st, int64_t span0, int64_t nspan
         HIP_TRY(hipStreamSynchronize(hs));
         return TS3_OK;
     }
-    // a span is the sum of its parts, in order
-    const std::unique_ptr<float[]> part(new (std::nothrow) float[(size_t)(S * E)]);
+    // A span is the sum of its parts, in order.  The buffer holds the parts that exist (S counts
+    // those of a whole span, of which a mesh shorter than group_span has few).
+    const int64_t most = std::min<int64_t>(S, st->part_hi - span0 * S);
+    const std::unique_ptr<float[]> part(new (std::nothrow) float[(size_t)(most * E)]);
     if (!part) return fail(TS3_ERR_OUT_OF_MEMORY, "host allocation failed");
     for (int64_t i = 0; i < nspan; ++i) {
         const int64_t p0 = (span0 + i) * S, np = std::min<int64_t>(S, st->part_hi - p0);

@@ -81,3 +81,21 @@ def test_parts_match_the_oracle_and_do_not_depend_on_the_tiling(C, H, M, dtype):
     total = spans.astype(np.float64).sum(axis=0)
     assert np.abs(total[..., :-1] - st[key]).max() <= 1e-5 * np.abs(st[key]).max()
     assert np.abs(total[..., -1] - st["d"]).max() <= 1e-5 * st["d"].max()
+
+
+@pytest.mark.parametrize("N", [2_000, 9_001])
+def test_spans_of_a_mesh_much_shorter_than_group_span(N):
+    """One span of up to 2^30 points whose mesh has a few thousand: get_spans needs room for
+    the parts that exist, not for those of a whole span."""
+    from paper_2602_04940_amd import LayerWeights, PhysicsAttention
+    C, H, M = 128, 8, 64
+    banner(f"parts of one span of 2^30 points, {N} points")
+    x64 = np.random.default_rng(8).standard_normal((N, C)).astype(np.float32).astype(np.float64)
+    W = make_weights(C, H, M, C // H, seed=3, bias_seed=4)
+    with PhysicsAttention(C, H, M, C // H, 0.5, "fp32", group_span=1 << 30, max_points=N) as layer:
+        layer.forward(LayerWeights(W), to_device(x64, "fp32"), tile=1 << 30)
+        span = layer.get_spans(0, 1)[0]
+        st = state_of(layer)
+    # float32 sums of at most 64 parts in order, both of them
+    assert np.abs(span[..., :-1] - st["s_raw"]).max() <= 1e-5 * np.abs(st["s_raw"]).max()
+    assert np.abs(span[..., -1] - st["d"]).max() <= 1e-5 * st["d"].max()
