@@ -93,31 +93,46 @@ struct Kernels {
     bool rt = false;  // operands in the runtime-shape layouts (k_prep_w2_rt, k_prep_z_rt)
 };
 
+// Launches of at most MAX_WGS workgroups: a grid holds fewer than 2^32 threads, in
+// workgroups of up to 768 here.  Larger calls are split into ranges of parts (or of
+// points), which changes no result.  launch(p0, count, geo) runs parts p0 .. p0 + count.
+constexpr int64_t MAX_WGS = 1 << 22;
+template <typename F> void launch_parts(int64_t nparts, int64_t wgs_per_part, const SpanGeo &geo, F launch) {
+    const int64_t batch = std::max<int64_t>(1, MAX_WGS / wgs_per_part);
+    for (int64_t p0 = 0; p0 < nparts; p0 += batch) {
+        SpanGeo part = geo;
+        part.first += (int32_t)p0;
+        launch(p0, (int32_t)std::min(batch, nparts - p0), part);
+    }
+}
+
 template <typename T, int C, int M>
 hipError_t launch_pass1(const void *x, int64_t n, int64_t span0, SpanGeo geo, int32_t nspan, int32_t H, int32_t, int32_t,
                   const void *w2p, const float *b2s, float *partials, hipStream_t st) {
-    if constexpr (sizeof(T) == 4) {
-        hipLaunchKernelGGL((k_sum3<C, M, SUM3_X>), dim3(nspan * H), dim3(512), 0, st, (const float *)x, (const float *)x, n,
-                           span0, geo, nspan, H, (const bf16_t *)w2p, b2s, partials);
-    } else if constexpr (C == 256) {
-        // Wide rows: two heads per workgroup, two producer and two consumer
-        // waves per head (H is even for every wide shape check_desc accepts).
-        hipLaunchKernelGGL((k_slice_accumulate_pcw<C, M>), dim3(nspan * (H / 2)), dim3(512), 0, st,
-                           (const bf16_t *)x, n, span0, geo, nspan, H, (const bf16_t *)w2p, b2s, partials);
-    } else if constexpr (M >= 32 && C == 128) {
-        // Two heads per workgroup whenever H is even (independently of the
-        // span count, so that every tiling sums a span the same way); the one
-        // odd case, H = 1, takes the generic kernel.
-        if (H % 2 == 0)
-            hipLaunchKernelGGL((k_slice_accumulate_pc<C, M>), dim3(nspan * (H / 2)), dim3(512), 0, st,
-                               (const bf16_t *)x, n, span0, geo, nspan, H, (const bf16_t *)w2p, b2s, partials);
-        else
-            hipLaunchKernelGGL((k_slice_accumulate<T, C, M>), dim3(nspan * H), dim3(256), 0, st,
-                               (const T *)x, n, span0, geo, nspan, H, (const T *)w2p, b2s, partials);
-    } else {
-        hipLaunchKernelGGL((k_slice_accumulate<T, C, M>), dim3(nspan * H), dim3(256), 0, st,
-                           (const T *)x, n, span0, geo, nspan, H, (const T *)w2p, b2s, partials);
-    }
+    const bool pairs = sizeof(T) == 2 && (C == 256 || (C == 128 && M >= 32 && H % 2 == 0));
+    launch_parts(nspan, pairs ? H / 2 : H, geo, [&](int64_t p0, int32_t np, const SpanGeo &part) {
+        if constexpr (sizeof(T) == 4) {
+            hipLaunchKernelGGL((k_sum3<C, M, SUM3_X>), dim3(np * H), dim3(512), 0, st, (const float *)x, (const float *)x,
+                               n, span0 + p0, part, np, H, (const bf16_t *)w2p, b2s, partials);
+        } else if constexpr (C == 256) {
+            // Wide rows: two heads per workgroup, two producer and two consumer
+            // waves per head (H is even for every wide shape check_desc accepts).
+            hipLaunchKernelGGL((k_slice_accumulate_pcw<C, M>), dim3(np * (H / 2)), dim3(512), 0, st, (const bf16_t *)x,
+                               n, span0 + p0, part, np, H, (const bf16_t *)w2p, b2s, partials);
+        } else {
+            // Two heads per workgroup whenever H is even (independently of the
+            // span count, so that every tiling sums a span the same way); the one
+            // odd case, H = 1, takes the generic kernel.
+            if constexpr (M >= 32 && C == 128)
+                if (pairs) {
+                    hipLaunchKernelGGL((k_slice_accumulate_pc<C, M>), dim3(np * (H / 2)), dim3(512), 0, st,
+                                       (const bf16_t *)x, n, span0 + p0, part, np, H, (const bf16_t *)w2p, b2s, partials);
+                    return;
+                }
+            hipLaunchKernelGGL((k_slice_accumulate<T, C, M>), dim3(np * H), dim3(256), 0, st, (const T *)x, n,
+                               span0 + p0, part, np, H, (const T *)w2p, b2s, partials);
+        }
+    });
     return hipSuccess;
 }
 
@@ -210,15 +225,19 @@ hipError_t launch_pass2(const void *x, int64_t n, int32_t H, int32_t, int32_t, c
 template <int C, int M>
 void launch_bw_head(const float *x, const float *g, int64_t n, int64_t span0, SpanGeo geo, int32_t nspan,
                     int32_t H, const void *w2p, const float *b2s, float *partials, hipStream_t st) {
-    hipLaunchKernelGGL((k_sum3<C, M, SUM3_G>), dim3(nspan * H), dim3(512), 0, st, x, g, n, span0, geo, nspan, H,
-                       (const bf16_t *)w2p, b2s, partials);
+    launch_parts(nspan, H, geo, [&](int64_t p0, int32_t np, const SpanGeo &part) {
+        hipLaunchKernelGGL((k_sum3<C, M, SUM3_G>), dim3(np * H), dim3(512), 0, st, x, g, n, span0 + p0, part, np, H,
+                           (const bf16_t *)w2p, b2s, partials);
+    });
 }
 
 template <int C, int M>
 void launch_bw_dw2(const float *x, const float *dzs, int64_t n, int64_t span0, SpanGeo geo, int32_t nspan, int32_t H,
                    float *partials, hipStream_t st) {
-    hipLaunchKernelGGL((k_sum3<C, M, SUM3_STORED>), dim3(nspan * H), dim3(512), 0, st, dzs, x, n, span0, geo, nspan, H,
-                       (const bf16_t *)nullptr, (const float *)nullptr, partials);
+    launch_parts(nspan, H, geo, [&](int64_t p0, int32_t np, const SpanGeo &part) {
+        hipLaunchKernelGGL((k_sum3<C, M, SUM3_STORED>), dim3(np * H), dim3(512), 0, st, dzs, x, n, span0 + p0, part, np,
+                           H, (const bf16_t *)nullptr, (const float *)nullptr, partials);
+    });
 }
 
 template <int C, int M>
@@ -232,8 +251,11 @@ void launch_bw_dx(const float *x, const float *g, int64_t n, int32_t H, const vo
 template <int C, int M>
 void launch_pass1p(const void *x, int64_t n, int64_t span0, SpanGeo geo, int32_t nspan, int32_t H, const void *w2p,
                    const float *b2s, const void *w1p, float *partials, hipStream_t st) {
-    hipLaunchKernelGGL((k_slice_accumulate_pcp<C, M>), dim3(nspan * (H / 2)), dim3(PCP_THREADS), 0, st, (const bf16_t *)x,
-                       n, span0, geo, nspan, H, (const bf16_t *)w2p, b2s, (const bf16_t *)w1p, partials);
+    launch_parts(nspan, H / 2, geo, [&](int64_t p0, int32_t np, const SpanGeo &part) {
+        hipLaunchKernelGGL((k_slice_accumulate_pcp<C, M>), dim3(np * (H / 2)), dim3(PCP_THREADS), 0, st,
+                           (const bf16_t *)x, n, span0 + p0, part, np, H, (const bf16_t *)w2p, b2s, (const bf16_t *)w1p,
+                           partials);
+    });
 }
 
 template <int C, int M>
@@ -295,27 +317,20 @@ template <typename K> hipError_t grant_lds(K *kernel, int bytes) {
     return hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 
-// Launches of at most RT_MAX_WGS workgroups (larger calls are split into
-// part or point ranges, which changes no result).
-constexpr int64_t RT_MAX_WGS = 1 << 22;
-
 template <typename T>
 hipError_t launch_pass1_rt(const void *x, int64_t n, int64_t span0, SpanGeo geo, int32_t nspan, int32_t H, int32_t C,
                            int32_t M, const void *w2r, const float *b2s, float *partials, hipStream_t st) {
     const RtPass1 cfg = rt_pass1(RT_NP<T>, C, M);
     const int64_t per_span = (int64_t)H * ((C + cfg.CC - 1) / cfg.CC);
-    const int64_t batch = std::max<int64_t>(1, RT_MAX_WGS / per_span);
     hipError_t e = hipSuccess;
     rt_dispatch(M / 16, [&](auto mt) {
         constexpr auto kernel = &k_slice_accumulate_rt<T, decltype(mt)::value>;
         e = grant_lds(kernel, cfg.lds);
-        for (int64_t s0 = 0; e == hipSuccess && s0 < nspan; s0 += batch) {
-            const int64_t ns = std::min<int64_t>(batch, nspan - s0);
-            SpanGeo part = geo;
-            part.first += (int32_t)s0;
-            hipLaunchKernelGGL(kernel, dim3((unsigned)(ns * per_span)), dim3(512), (size_t)cfg.lds, st, (const T *)x, n,
-                               span0 + s0, part, (int32_t)ns, H, C, M, cfg.CC, cfg.PB, (const bf16_t *)w2r, b2s, partials);
-        }
+        if (e != hipSuccess) return;
+        launch_parts(nspan, per_span, geo, [&](int64_t p0, int32_t np, const SpanGeo &part) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)(np * per_span)), dim3(512), (size_t)cfg.lds, st, (const T *)x, n,
+                               span0 + p0, part, np, H, C, M, cfg.CC, cfg.PB, (const bf16_t *)w2r, b2s, partials);
+        });
     });
     return e;
 }
@@ -330,8 +345,8 @@ hipError_t launch_pass2_rt(const void *x, int64_t n, int32_t H, int32_t C, int32
         constexpr auto k4 = &k_deslice_rt<T, MT, 4>, k2 = &k_deslice_rt<T, MT, 2>;
         const auto kernel = cfg.PT == 4 ? k4 : k2;
         e = grant_lds(kernel, lds);
-        for (int64_t p0 = 0; e == hipSuccess && p0 < n; p0 += RT_MAX_WGS * P) {
-            const int64_t np = std::min<int64_t>(RT_MAX_WGS * P, n - p0);
+        for (int64_t p0 = 0; e == hipSuccess && p0 < n; p0 += MAX_WGS * P) {
+            const int64_t np = std::min<int64_t>(MAX_WGS * P, n - p0);
             hipLaunchKernelGGL(kernel, dim3((unsigned)((np + P - 1) / P)), dim3(512), (size_t)lds, st,
                                (const T *)x + p0 * C, np, H, C, M, RtGroup(cfg.GH, M), (const bf16_t *)w2r, b2s,
                                (const bf16_t *)zr, (T *)out + p0 * C);

@@ -9,7 +9,7 @@ import numpy as np
 import pytest
 
 import oracle
-from gpu_helpers import (assert_bf16_close, assert_state_close, banner, match_sums, normwise, state_of, sums_key,
+from gpu_helpers import (assert_bf16_close, assert_state_close, banner, match_sums, normwise, rel_l2, state_of, sums_key,
                          to_device, to_host)
 from ts3_synth import make_weights, round_bf16
 
@@ -99,3 +99,27 @@ def test_spans_of_a_mesh_much_shorter_than_group_span(N):
     # float32 sums of at most 64 parts in order, both of them
     assert np.abs(span[..., :-1] - st["s_raw"]).max() <= 1e-5 * np.abs(st["s_raw"]).max()
     assert np.abs(span[..., -1] - st["d"]).max() <= 1e-5 * st["d"].max()
+
+
+@pytest.mark.parametrize("C,H,M,dtype", [(64, 4, 16, "fp32"), (64, 8, 16, "bf16")])
+def test_spans_of_one_point_and_more_workgroups_than_a_launch_holds(C, H, M, dtype):
+    """2.2M spans of one point are 8.8M and 17.6M workgroups: more than 2^32 threads in one
+    launch, though each tile of 65,536 points holds far fewer."""
+    import torch
+    from paper_2602_04940_amd import LayerWeights, PhysicsAttention
+    N, tile = 2_200_000, 65_536
+    banner(f"{N} spans of one point: C={C} H={H} M={M} {dtype}")
+    x = torch.randn((N, C), generator=torch.Generator("cuda").manual_seed(1), device="cuda")
+    x = x.to(torch.bfloat16) if dtype == "bf16" else x
+    lw = LayerWeights(make_weights(C, H, M, C // H, seed=3, bias_seed=4))
+    outs, states = [], []
+    for Q in (1, 4096):
+        with PhysicsAttention(C, H, M, C // H, 0.5, dtype, group_span=Q, max_points=N, accum="fp64") as layer:
+            outs.append(to_host(layer.forward(lw, x, tile=tile, chunk=tile)[-5000:]))
+            states.append(state_of(layer))
+    # the same terms in other groups, float32 within a span: 4,096 terms against one
+    for k in ("s_raw", "d"):
+        e = normwise(states[0][k], states[1][k])
+        print(f"{k}: normwise {e:.2e}", flush=True)
+        assert e <= (2e-2 if dtype == "bf16" else 1e-4), (k, e)
+    assert rel_l2(outs[0], outs[1]) <= (2e-2 if dtype == "bf16" else 1e-4)
