@@ -298,7 +298,9 @@ typedef struct ts3_stack ts3_stack; /* opaque */
 /* A stack of n_blocks blocks of layer shape `desc` (bf16 storage) with hidden
  * width `hidden` = F.  Supported (C, F): (128, 512), (256, 1024); otherwise
  * TS3_ERR_UNSUPPORTED.  Allocates n_blocks layer states plus two activation
- * buffers of max_points * C bf16 and one block's feed-forward fragments. */
+ * buffers of max_points * C bf16 and one block's feed-forward fragments.  The
+ * states' spans are cut into parts within 1 GiB of partials for the whole stack
+ * (128 MiB per block), so a stack of more than eight blocks may cut them less. */
 ts3_status ts3_stack_create(const ts3_desc *desc, int32_t n_blocks, int32_t hidden, ts3_stack **out);
 ts3_status ts3_stack_free(ts3_stack *s);
 ts3_status ts3_stack_bytes(const ts3_stack *s, int64_t *bytes);

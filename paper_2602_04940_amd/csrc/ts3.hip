@@ -493,12 +493,13 @@ ts3_status check_desc(const ts3_desc *d) {
 // do not divide into parts evenly, and a few workgroups past a round cost a whole one.
 // Those 100,003 points in parts of 1,632 were 260 workgroups and took 48 us, a float32
 // training step of 60,001 points with 280 workgroups 895 us against 725 us with 248.
-// Never more than PART_BYTES of partials through the split, and a multiple of the points
+// Never more than `bytes` of partials through the split (PART_BYTES; for the blocks of a
+// stack their share of STACK_PART_BYTES), and a multiple of the points
 // that a workgroup's waves take per step.  Only desc enters the rule, so a state's sums
 // do not depend on the tiling.
 constexpr int64_t PART_POINTS = 2048, PART_WGS = 256, PART_ROUNDS = 8, PART_START = 128, PART_BYTES = int64_t(128) << 20;
 
-SpanGeo span_geo(const ts3_desc &d, const Kernels &k, bool proj, int64_t E) {
+SpanGeo span_geo(const ts3_desc &d, const Kernels &k, bool proj, int64_t E, int64_t bytes) {
     const bool pairs = d.H % 2 == 0 && d.io_dtype == TS3_BF16 && !k.rt && (d.C == 256 || (d.C == 128 && d.M >= 32));
     const int np = d.io_dtype == TS3_BF16 ? 1 : 3;
     const RtPass1 rt1 = k.rt ? rt_pass1(np, d.C, d.M) : RtPass1{d.C, 0, 0};
@@ -509,7 +510,7 @@ SpanGeo span_geo(const ts3_desc &d, const Kernels &k, bool proj, int64_t E) {
     const int64_t one_round = (N * wgs + PART_WGS - 1) / PART_WGS;
     const int64_t longest = std::max(PART_POINTS, one_round / PART_ROUNDS);
     const int64_t nspan = (N + Q - 1) / Q;
-    const int64_t most = PART_BYTES / (nspan * E * 4);
+    const int64_t most = bytes / (nspan * E * 4);
     const int64_t first = std::max<int64_t>(1, std::min(most, (q + longest - 1) / longest));
     // one_round >= q * wgs / PART_WGS, so at most PART_WGS lengths
     const int64_t last = std::max(first, std::min(most, (q + one_round - 1) / one_round));
@@ -624,7 +625,12 @@ ts3_status make_aux(ts3_state *st) {
 }
 }  // namespace
 
-ts3_status ts3_state_create(const ts3_desc *desc, ts3_state **out) {
+}  // extern "C"
+
+namespace {
+
+// A state whose spans are cut into parts of at most part_bytes of partials in all.
+ts3_status create_state(const ts3_desc *desc, int64_t part_bytes, ts3_state **out) {
     if (!out) return fail(TS3_ERR_INVALID_ARG, "out is NULL");
     *out = nullptr;
     ts3_status s = check_desc(desc);
@@ -639,7 +645,7 @@ ts3_status ts3_state_create(const ts3_desc *desc, ts3_state **out) {
     st->proj = st->k.pass1p && d.H * 16 == d.C;
     st->rowc = st->proj ? 16 : d.C;
     st->E = (int64_t)d.H * d.M * (st->rowc + 1);
-    st->geo = span_geo(d, st->k, st->proj, st->E);
+    st->geo = span_geo(d, st->k, st->proj, st->E, part_bytes);
     st->npart_max = std::max<int64_t>(1, st->geo.parts(d.max_points));
     st->nrun_max = (st->npart_max + FOLD - 1) / FOLD;
     const int64_t HM = (int64_t)d.H * d.M;
@@ -693,6 +699,12 @@ ts3_status ts3_state_create(const ts3_desc *desc, ts3_state **out) {
     *out = st;
     return TS3_OK;
 }
+
+}  // namespace
+
+extern "C" {
+
+ts3_status ts3_state_create(const ts3_desc *desc, ts3_state **out) { return create_state(desc, PART_BYTES, out); }
 
 ts3_status ts3_state_bytes(const ts3_state *st, int64_t *bytes) {
     if (!st || !bytes) return fail(TS3_ERR_INVALID_ARG, "NULL argument");
@@ -1311,7 +1323,7 @@ ts3_status ts3_layer_forward_noalloc(const ts3_desc *desc, const ts3_weights *w,
     Kernels ck;
     find_any_kernels(d.io_dtype, d.C, d.M, &ck);
     const bool cproj = ck.pass1p && d.H * 16 == d.C;
-    const SpanGeo geo = span_geo(cut, ck, cproj, (int64_t)d.H * d.M * ((cproj ? 16 : d.C) + 1));
+    const SpanGeo geo = span_geo(cut, ck, cproj, (int64_t)d.H * d.M * ((cproj ? 16 : d.C) + 1), PART_BYTES);
     // A state on the host stack whose device buffers are regions of the array;
     // it owns nothing and is never freed.
     ts3_state st;

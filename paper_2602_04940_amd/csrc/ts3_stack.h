@@ -105,6 +105,11 @@ ts3_status run_blocks(ts3_stack *s, const ts3_block_weights *blocks, bf16_t *x, 
     return TS3_OK;
 }
 
+// Partials that the blocks of one stack hold through the cutting of spans, in all: every
+// block keeps a state of its own, so PART_BYTES each would be 128 GiB for 1,024 blocks.  Up to eight
+// blocks are cut as single layers are.
+constexpr int64_t STACK_PART_BYTES = int64_t(1) << 30;
+
 }  // namespace
 
 extern "C" {
@@ -127,7 +132,7 @@ ts3_status ts3_stack_create(const ts3_desc *desc, int32_t n_blocks, int32_t hidd
     st->F = hidden;
     for (int l = 0; l < n_blocks; ++l) {
         ts3_state *ls = nullptr;
-        s = ts3_state_create(desc, &ls);
+        s = create_state(desc, std::min(PART_BYTES, STACK_PART_BYTES / n_blocks), &ls);
         if (s != TS3_OK) {
             ts3_stack_free(st);
             return s;

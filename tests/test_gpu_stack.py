@@ -156,3 +156,15 @@ def test_a_small_call_gives_the_rows_of_a_large_one(C, n):
     assert torch.equal(few, whole[:n])
     assert torch.equal(few_xn[:n], xn[:n]) and bool((few_xn[n] == 7.0).all())
     assert torch.equal(q_few, q[:n])
+
+
+def test_many_blocks_do_not_each_hold_partials_for_cut_spans():
+    """64 blocks over 1M points in spans of 31,250: beyond whole spans' partials, 1 GiB of
+    partials in all (and the blocks' state buffers and activations)."""
+    C, H, M, L, N, Q = 256, 8, 64, 64, 1_000_000, 31_250
+    banner(f"stack of {L} blocks: bytes")
+    whole = L * (N // Q) * H * M * (C + 1) * 4
+    with _stack(C, H, M, L, Q, N) as st:
+        beyond = st.bytes() - whole - 2 * N * C * 2
+    print(f"{beyond / 2**20:.0f} MiB beyond whole spans and activations", flush=True)
+    assert beyond <= (1 << 30) + L * 16 * H * M * C * 4  # Z, s_raw, fragments, one run of doubles, ...
