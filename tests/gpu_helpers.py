@@ -3,8 +3,18 @@ layer through the C ABI, and the error measures the acceptance bar uses."""
 import numpy as np
 
 
+# Float32 bars by output (normwise, on well-scaled inputs of up to some thousand points):
+# about four times the largest error measured over the shapes of the tests that use them.
+FP32_BARS = {"out": 8e-6, "dx": 8e-6, "dW2": 8e-6, "s_raw": 4e-6}
+FP32_BAR = 2.5e-6  # every other output
+
+
+def fp32_bar(name):
+    return FP32_BARS.get(name, FP32_BAR)
+
+
 def normwise(got, ref):
-    """max |got - ref| / max |ref|  (the fp32 bar, 1e-4)."""
+    """max |got - ref| / max |ref|  (the acceptance bar for float32 is 1e-4)."""
     ref = np.asarray(ref, dtype=np.float64)
     return float(np.abs(np.asarray(got, dtype=np.float64) - ref).max() / max(np.abs(ref).max(), 1e-300))
 

@@ -1,14 +1,15 @@
 """Float32 storage at the edges of its kernels: one point, one more and one less than a
 block, one head and several, every tile count, and both block sizes of pass 2.
 
-Operands enter the matrix cores as three bfloat16 parts with float32 sums, so the bar
-is that of the other float32 parity tests (normwise 1e-4; measured below 6e-6).
+Operands enter the matrix cores as three bfloat16 parts with float32 sums: the bars are a
+small multiple of the errors measured (gpu_helpers.FP32_BARS).  Whether a part of an
+operand is lost, which costs less than these bars, is test_float32_parts.py's question.
 """
 import numpy as np
 import pytest
 
 import oracle
-from gpu_helpers import banner, normwise, state_of, to_device, to_host
+from gpu_helpers import banner, fp32_bar, normwise, state_of, to_device, to_host
 from oracle import backward as BW
 from ts3_synth import make_weights
 
@@ -50,7 +51,7 @@ def test_forward_and_backward_against_the_oracle(C, H, M, N, Q):
     for n, (got, want) in pairs.items():
         e = normwise(got, want)
         print(f"{n}: normwise {e:.2e}", flush=True)
-        assert e <= 1e-4, (n, e)
+        assert e <= fp32_bar(n), (n, e)
 
 
 def test_both_block_sizes_of_pass_2_decode_a_point_the_same():

@@ -3,14 +3,14 @@ oracle, and the guarantees that must not depend on the cut.
 
 9,001 points in spans of 4,096 give parts of 64 to 192 points, the last span
 and its last part ragged.  A part's sum and the fold are float32 sums as before, so
-the bars are those of the other parity tests.
+the bars are those of the other tests.
 """
 import numpy as np
 import pytest
 
 import oracle
-from gpu_helpers import (assert_bf16_close, assert_state_close, banner, match_sums, normwise, rel_l2, state_of, sums_key,
-                         to_device, to_host)
+from gpu_helpers import (assert_bf16_close, assert_state_close, banner, fp32_bar, match_sums, normwise, rel_l2, state_of,
+                         sums_key, to_device, to_host)
 from ts3_synth import make_weights, round_bf16
 
 pytestmark = pytest.mark.gpu
@@ -72,11 +72,12 @@ def test_parts_match_the_oracle_and_do_not_depend_on_the_tiling(C, H, M, dtype):
         assert_state_close(late, late_ref, "state without the first span")
         assert_bf16_close(to_host(few), few_ref, "out of fewer points")
     else:
-        for what, got, want in (("out", to_host(out), ref_out), (key, st[key], ref[key]), ("d", st["d"], ref["d"]),
-                                ("late sums", late[key], late_ref[key]), ("few", to_host(few), few_ref)):
+        for what, bar, got, want in (("out", "out", to_host(out), ref_out), (key, key, st[key], ref[key]),
+                                     ("d", "d", st["d"], ref["d"]), ("late sums", key, late[key], late_ref[key]),
+                                     ("few", "out", to_host(few), few_ref)):
             e = normwise(got, want)
             print(f"{what}: normwise {e:.2e}", flush=True)
-            assert e <= 1e-4, (what, e)
+            assert e <= fp32_bar(bar), (what, e)
     # the spans that get_spans reports add up to the state (float32 sums of three terms)
     total = spans.astype(np.float64).sum(axis=0)
     assert np.abs(total[..., :-1] - st[key]).max() <= 1e-5 * np.abs(st[key]).max()
@@ -117,9 +118,11 @@ def test_spans_of_one_point_and_more_workgroups_than_a_launch_holds(C, H, M, dty
         with PhysicsAttention(C, H, M, C // H, 0.5, dtype, group_span=Q, max_points=N, accum="fp64") as layer:
             outs.append(to_host(layer.forward(lw, x, tile=tile, chunk=tile)[-5000:]))
             states.append(state_of(layer))
-    # the same terms in other groups, float32 within a span: 4,096 terms against one
+    # The same terms in other groups.  Sums of 4,096 positive-weighted terms in float32 against
+    # terms added in float64: within 4,096 half ulps at the worst, a few at random (measured
+    # 9e-8); the bar is 16 half ulps.
     for k in ("s_raw", "d"):
         e = normwise(states[0][k], states[1][k])
         print(f"{k}: normwise {e:.2e}", flush=True)
-        assert e <= (2e-2 if dtype == "bf16" else 1e-4), (k, e)
-    assert rel_l2(outs[0], outs[1]) <= (2e-2 if dtype == "bf16" else 1e-4)
+        assert e <= 2.0 ** -20, (k, e)
+    assert rel_l2(outs[0], outs[1]) <= (1e-2 if dtype == "bf16" else 2.0 ** -20)

@@ -3,14 +3,14 @@ their tiles, against the oracle: a channel count with half a K32 step, one to
 sixteen slice tiles, head groups with padding and a last group of fewer heads,
 channels in several chunks, blocks of 32 and 64 points, and ragged point counts.
 
-Float32 storage computes on exact three-part operands with float32 sums: the bar is
-that of the other float32 parity tests.  bf16 storage rounds x, W2' and Z as stored.
+Float32 storage computes on exact three-part operands with float32 sums: the bars are a
+small multiple of the errors measured (gpu_helpers.FP32_BARS).  bf16 storage rounds x, W2' and Z as stored.
 """
 import numpy as np
 import pytest
 
 import oracle
-from gpu_helpers import assert_bf16_close, assert_state_close, banner, normwise, rel_l2, state_of, to_device, to_host
+from gpu_helpers import assert_bf16_close, assert_state_close, banner, fp32_bar, normwise, rel_l2, state_of, to_device, to_host
 from ts3_synth import make_weights, round_bf16
 
 pytestmark = pytest.mark.gpu
@@ -59,7 +59,7 @@ def test_runtime_shapes_at_tile_edges(C, H, M, N, dtype):
                                 ("d", st["d"], ref["d"]), ("injected", to_host(inj), inj_ref)):
             e = normwise(got, want)
             print(f"{what}: normwise {e:.2e}", flush=True)
-            assert e <= 1e-4, (what, e)
+            assert e <= fp32_bar("out" if what == "injected" else what), (what, e)
 
 
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])

@@ -3,14 +3,14 @@ at the edges of what they accept, against the oracle: head widths that do not
 divide a workgroup, one wide head, a working set past 64 KiB of
 LDS, one and several runs of part sums, both fold precisions, and no biases.
 
-All sums are float32 (or float64 in the fold) of well-scaled terms: the bar is that
-of the other float32 parity tests.
+All sums are float32 (or float64 in the fold) of well-scaled terms: the bars are a small
+multiple of the errors measured (gpu_helpers.FP32_BARS).
 """
 import numpy as np
 import pytest
 
 import oracle
-from gpu_helpers import banner, normwise, state_of, to_device, to_host
+from gpu_helpers import banner, fp32_bar, normwise, state_of, to_device, to_host
 from ts3_synth import make_weights
 
 pytestmark = pytest.mark.gpu
@@ -40,7 +40,7 @@ def test_token_backward(C, H, M):
     for k in ("dx", "dW2", "db2", "dW1", "db1", "dWq", "dWk", "dWv", "dW3", "db3"):
         e = normwise(got[k], ref[k])
         print(f"{k}: normwise {e:.2e}", flush=True)
-        assert e <= 1e-4, (k, e)
+        assert e <= fp32_bar(k), (k, e)
 
 
 @pytest.mark.parametrize("C,H,M,N,Q,accum,biases", [
@@ -69,5 +69,5 @@ def test_slice_tokens_and_attention(C, H, M, N, Q, accum, biases):
     for k in ("s_raw", "d", "s", "s1", "Z"):
         e = normwise(st[k], ref[k])
         print(f"{k}: normwise {e:.2e}", flush=True)
-        assert e <= 1e-4, (k, e)
-    assert normwise(to_host(out), out_ref) <= 1e-4
+        assert e <= fp32_bar(k), (k, e)
+    assert normwise(to_host(out), out_ref) <= fp32_bar("out")
