@@ -153,7 +153,6 @@ int device_cu_count() {
     return c;
 }
 
-
 template <typename T, int C, int M>
 hipError_t launch_pass2(const void *x, int64_t n, int32_t H, int32_t, int32_t, const void *w2p, const float *b2s,
                         const void *zp, void *out, hipStream_t st) {
@@ -786,8 +785,7 @@ ts3_status ts3_slice_accumulate(ts3_state *st, const ts3_weights *w, const void 
 
 namespace {
 
-// Ordered fold of the first nspan part sums into main [H*M*C] and the
-// column C entries into col [H*M] (the forward's fold kernels).
+// s_raw, d and the slice tokens from `count` part sums, or runs of them, at src.
 template <typename TS, typename TA>
 void launch_tokens(ts3_state *st, const TS *src, int64_t count, const ts3_weights *w, hipStream_t hs) {
     const ts3_desc &d = st->desc;
@@ -821,6 +819,8 @@ template <typename T> ts3_status tokens_from_parts(ts3_state *st, int64_t nparts
     return tokens_from_runs(st, nrun, w, hs);
 }
 
+// Ordered fold of the first nspan part sums into main [H*M*rowc] and their last
+// (d-like) column into col [H*M]: the backward's sums.
 template <typename T>
 ts3_status fold_partials_t(ts3_state *st, int64_t nspan, int rowc, float *main, float *col, hipStream_t hs) {
     const int64_t E = (int64_t)st->desc.H * st->desc.M * (rowc + 1);

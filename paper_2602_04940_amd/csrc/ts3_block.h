@@ -17,15 +17,16 @@
 //                   tanh form in half precision, gelu2_f16) between them, the
 //                   residual, and optionally the next block's LN1.
 //
-// k_mlp_residual_pc: 32 PT (128, or fewer for a small call) points per workgroup.  The producer keeps LN2(y) of its points as B fragments (K = channels)
-// in registers; the hidden layer is walked in chunks staged in LDS:
+// k_mlp_residual_pc: 32 PT (128, or fewer for a small call) points per workgroup.  A
+// producer keeps LN2(y) of its group's points as B fragments (K = channels) in
+// registers; the hidden layer is walked in chunks staged in LDS:
 //   GEMM1  H^T[f][p] = W_a^T[f][:] . LN2(y)[p][:] + b_a[f]   (A = staged W_a^T)
 //   GELU   on packed halves; the 16 x 4 outputs of two hidden tiles are
 //          exactly a B fragment of the second product (K slot (g, t) <->
 //          hidden unit 32km + 16(t>>2) + 4g + (t&3)), handed to the consumer
 //          through LDS in that fragment order;
 //   GEMM2  out^T[c][p] += W_b^T[c][:] . h[p][:]   (consumer; A = staged W_b,
-//          f16 x f16) into the 32 x C output accumulator.
+//          f16 x f16) into the accumulator of 16 PT points x C/2 channels.
 // Output rows of W_b's fragments follow zchan(), so a lane ends up holding the
 // eight consecutive channels 32k + 8g .. +7 of its point: the same channels
 // it loads for the residual, which keeps the next LayerNorm in registers.

@@ -107,18 +107,6 @@ __device__ __forceinline__ void ones8(Frag<bf16_t> &f) {
     for (int t = 0; t < 8; ++t) f.v[t] = (__bf16)1.0f;
 }
 
-// Storage element <-> float.
-__device__ __forceinline__ float to_f32(float x) { return x; }
-__device__ __forceinline__ float to_f32(bf16_t x) { return __uint_as_float(uint32_t(x.bits) << 16); }
-__device__ __forceinline__ uint16_t raw16(bf16_t x) { return x.bits; }
-
-// Element t of a loaded fragment as stored bits/values (for LDS transposes).
-__device__ __forceinline__ uint16_t elem_bits(const Frag<bf16_t> &f, int t) {
-    // Read element t through the packed dwords (element 2k is the low half of dword k).
-    const u32x4 u = __builtin_bit_cast(u32x4, f.v);
-    return (uint16_t)((t & 1) ? (u[t >> 1] >> 16) : (u[t >> 1] & 0xffffu));
-}
-
 // Cross-lane reductions among the 16 lanes of a DPP row (all lanes get the result).
 template <int CTRL> __device__ __forceinline__ float dpp(float v) {
     return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), CTRL, 0xf, 0xf, false));
@@ -162,20 +150,6 @@ __device__ __forceinline__ bool softmax_sum_ok(float s) {
     return s >= 0x1p-100f && s <= 0x1p100f;
 }
 __device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
-
-// Scheduling hint for the region just emitted: alternate NMFMA matrix-core
-// instructions with VPER vector-ALU instructions, pulling one LDS read ahead
-// of every RPER MFMAs, so one wave keeps both units busy (in-order issue would
-// otherwise run the MFMA cluster and the VALU cluster back to back).
-template <int NMFMA, int VPER, int RPER>
-__device__ __forceinline__ void interleave_mfma_valu() {
-#pragma unroll
-    for (int i = 0; i < NMFMA; ++i) {
-        if (RPER > 0 && i % RPER == 0) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // DS read
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                  // MFMA
-        __builtin_amdgcn_sched_group_barrier(0x002, VPER, 0);                               // VALU
-    }
-}
 
 // Scheduling hint for a region holding a chain of NMFMA matrix-core
 // instructions fed by LDS reads, next to an independent vector-ALU chain: the

@@ -5,7 +5,6 @@
 
 namespace ts3 {
 
-__device__ __forceinline__ void store_elem(float *p, float v) { *p = v; }
 __device__ __forceinline__ void store_elem(bf16_t *p, float v) {
     *reinterpret_cast<__bf16 *>(p) = (__bf16)v;
 }
