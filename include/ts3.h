@@ -69,10 +69,13 @@ typedef enum { TS3_ACCUM_FP32 = 0, TS3_ACCUM_FP64 = 1 } ts3_accum;
  *                the slice-weight and contraction products on bf16 matrix
  *                cores with float32 accumulation; TS3_FP32 keeps every operand
  *                to float32 precision, as sums of three bf16 parts on bf16
- *                matrix cores with float32 accumulation (a float32 input or
- *                gradient that is infinite, or beyond bfloat16's largest value,
- *                gives NaN).  The runtime-shape kernels keep the slice weights
- *                so for either storage type.
+ *                matrix cores with float32 accumulation.  The parts have
+ *                bfloat16's range: a float32 input, weight or gradient that is
+ *                infinite, or beyond bfloat16's largest value (3.39e38), gives
+ *                NaN (not so b2, which is added as float32: -inf there closes a
+ *                slice), and one below 2^-102 in magnitude loses its lowest bits,
+ *                whose part underflows.  The runtime-shape kernels keep the slice
+ *                weights so for either storage type.
  *  group_span  : Q, points per accumulation span (1 <= Q <= 2^30).  Pass 1
  *                reduces each span to partials of its consecutive parts and sums
  *                them in index order, so results do not depend on how the mesh
@@ -86,7 +89,11 @@ typedef enum { TS3_ACCUM_FP32 = 0, TS3_ACCUM_FP64 = 1 } ts3_accum;
  *                either way.  Any other value is TS3_ERR_INVALID_ARG.
  *  max_points  : largest point index + 1 the state will accumulate; sizes the
  *                span partials (ceil(max_points / Q) * H * M * (C+1) floats, or
- *                up to 128 MiB where spans are cut into parts). */
+ *                up to 128 MiB where spans are cut into parts).  It also decides
+ *                how spans are cut, so size a state to the meshes it is used on:
+ *                one made for 100M points keeps spans whole, and a mesh of
+ *                100,000 points then runs pass 1 on as few workgroups as it has
+ *                spans and head pairs (about five times the time). */
 typedef struct {
     int32_t C, H, M, dh;
     float temperature;
@@ -189,8 +196,13 @@ ts3_status ts3_deslice(const ts3_state *st, const ts3_weights *w, const void *x_
 /* Whole layer on a resident mesh (Algorithm 1): reset, accumulate tiles of
  * `tile` points, finalize, attention, deslice chunks of `chunk` points.
  * tile must be a multiple of group_span; N <= max_points.  Allocates nothing.
- * A launch covers several tiles (or chunks), up to about 4M points, which
- * changes no result.
+ * A launch covers several tiles (or chunks), up to about 4M points.  That
+ * changes no sum of pass 1.  In pass 2 every point is decoded alone, and its
+ * row has the same bits wherever the chunks begin, with one exception: with
+ * bfloat16 storage, where a head's exp2 sum of some row leaves [2^-100, 2^100],
+ * the rows decoded in one tile with it (16 or 32 consecutive rows, counted from
+ * the start of the launch) take the max-shifted softmax too, which rounds
+ * differently in bfloat16.
  * Consecutive launches are enqueued alternately on `stream` and on
  * a second stream that the state owns, forked from `stream` by an event and
  * joined back into it before the call returns: work enqueued on `stream`

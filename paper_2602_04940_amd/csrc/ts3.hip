@@ -477,25 +477,32 @@ ts3_status check_desc(const ts3_desc *d) {
     return TS3_OK;
 }
 
-// The parts of a span (SpanGeo) for a state of max_points points.  A workgroup
-// sums one part for one head or head pair, so a mesh of few spans would leave
-// most compute units idle: at 100,003 points and spans of 32,768 (bf16, C =
-// 128, H = 8, M = 64) pass 1 ran 16 workgroups and took 343 us, with parts of
-// 1,728 points 232 workgroups and 30 us.  Parts are at most PART_POINTS long, so
-// that a mesh that arrives in tiles still spreads each tile, unless the mesh fills
-// PART_ROUNDS rounds of compute units with longer ones (1M points streamed in tiles of
-// 65,536 took 0.87 ms with 4,096 and 4 rounds, 0.62 ms with these; the same mesh in one
-// call 423 and 451 us, 470 us with whole spans of 15,625, one round of 256 workgroups;
-// at 16M points parts of 5,216 made the layer 1.8% slower than whole spans).  Of the
-// lengths below that, down to one round for the whole mesh, the one whose rounds, each a
-// part and a workgroup's start and end (about PART_START points), take the least: spans
-// do not divide into parts evenly, and a few workgroups past a round cost a whole one.
-// Those 100,003 points in parts of 1,632 were 260 workgroups and took 48 us, a float32
-// training step of 60,001 points with 280 workgroups 895 us against 725 us with 248.
+// The parts of a span (SpanGeo) for a state of max_points points. A workgroup sums one
+// part for one head or head pair, so a mesh of few spans would leave most compute units
+// idle: at 100,003 points and spans of 32,768 (bf16, C = 128, H = 8, M = 64) pass 1 ran 16
+// workgroups and took 343 us, with parts of 1,728 points 232 workgroups and 30 us.
+//
+// Parts are at most PART_POINTS long, so that a mesh that arrives in tiles still spreads
+// each tile, unless the mesh fills PART_ROUNDS rounds of compute units with longer ones:
+// 1M points streamed in tiles of 65,536 took 0.87 ms with 4,096 and 4 rounds, 0.62 ms with
+// these. A mesh that comes in one call, or in tiles that fill the chip with whole spans,
+// pays for it where those make up whole rounds: with spans of 15,625 (256 workgroups per
+// 1M points) the layer of 1M, 2M, 4M and 8M points takes 440, 846, 1634 and 3240 us, 399,
+// 796, 1602 and 3205 us with whole spans; with spans of 32,768, 447, 883, 1717 and 3459 us
+// against 554, 837, 1671 and 3338 us. The cut cannot know the tiles: it follows from desc
+// alone, so that a state's sums do not depend on the tiling.
+//
+// Of the lengths below that bound, down to one round for the whole mesh, the one whose
+// rounds, each a part and a workgroup's start and end (about PART_START points), take the
+// least: spans do not divide into parts evenly, and a few workgroups past a round cost a
+// whole one. Those 100,003 points in parts of 1,632 were 260 workgroups and took 48 us, a
+// float32 training step of 60,001 points with 280 workgroups 895 us against 725 us with
+// 248.
+//
 // Never more than `bytes` of partials through the split (PART_BYTES; for the blocks of a
-// stack their share of STACK_PART_BYTES), and a multiple of the points
-// that a workgroup's waves take per step.  Only desc enters the rule, so a state's sums
-// do not depend on the tiling.
+// stack their share of STACK_PART_BYTES): where that holds fewer parts than the bound on
+// their length asks for, the most that fit are taken and no other count is compared.
+// Lengths are a multiple of the points that a workgroup's waves take per step.
 constexpr int64_t PART_POINTS = 2048, PART_WGS = 256, PART_ROUNDS = 8, PART_START = 128, PART_BYTES = int64_t(128) << 20;
 
 SpanGeo span_geo(const ts3_desc &d, const Kernels &k, bool proj, int64_t E, int64_t bytes) {

@@ -10,11 +10,15 @@
 //            fragments in registers too), 4 consecutive channels per lane.
 // k_deslice_sf gives a wave 32 points and all heads and stages 128 KB of operands in LDS
 // first: 256 points and 14 us are its least step.  Here a block is 32 points and nothing
-// is staged, but a block is a chain across the barrier.  Calls in a row, k_deslice_sf and
-// this, in us: (C, M) = (128, 64) 5,003 points 14.3 and 8.6 (the host's time per call),
-// 16,384 points 15.1 and 10.8, 32,768 points 17.3 and 15.7, 100,003 points 27 and 36;
-// (128, 32) 16,384 points 12.1 and 9.5, 32,768 points 13.4 and 13.9; (64, 32) 5,003 points
-// 9.9 and 8.7, 100,003 points 10 and 12.
+// is staged, but a block is a chain across the barrier.  Launches in a row in a graph,
+// k_deslice_sf and this, in us:
+//   (C, M)     5,003 points   16,384        24,576         32,768         65,536 points
+//   (128, 64)  13.5 and 6.7   13.9 and 9.2  14.2 and 11.5  14.6 and 13.7  17.4 and 22.6
+//   (128, 32)  10.7 and 5.8   11.0 and 8.1  11.3 and 10.3  11.7 and 12.5  13.3 and 21.2
+//   (64, 32)    5.4 and 3.0    5.5 and 3.8   5.7 and 4.5    5.9 and 5.2    6.5 and 8.0
+// Three blocks per workgroup (24,576 points on 256 compute units) are the last count at
+// which this is the faster one for every shape.  Called one by one, no call takes less
+// than the host's 7.6 to 8.4 us.
 //
 // Blocks with an exp2 sum outside the window are noted in LDS by any of the waves and
 // redone at the end, as there.
@@ -23,7 +27,7 @@
 
 namespace ts3 {
 
-constexpr int SH_MAX_ITERS = 3;  // blocks per workgroup (at most the bits of `failed`)
+constexpr int SH_MAX_ITERS = 3;  // blocks per workgroup, see above (at most the bits of `failed`)
 
 // Operands as for k_deslice_sf.  Grid: at most ceil(n / 32) workgroups of 64 H threads,
 // each with at most SH_MAX_ITERS blocks.
