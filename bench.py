@@ -69,9 +69,10 @@ CAL_BYTES = 1 << 30  # calibration copy: 1 GiB read, 1 GiB written
 
 def pmc_driver(points: int, workloads=("layer",)):
     """Short workload for rocprofv3 --pmc runs.  "layer": two layer forwards over
-    `points` points of the 100M-point volume mesh's recipe (1M-point launches);
-    "stack": one block's feed-forward and both passes at C=256 on 1M car-surface
-    points; "backward": a float32 forward and backward on 1M volume points.
+    `points` points of the 100M-point volume mesh's recipe, tile by tile (1M-point
+    launches); "stack": two blocks at C=256 on 1M car-surface points; "backward": a
+    float32 forward and backward on 1M volume points; "runtime": two layers without
+    tuned kernels (C=192 bf16, C=256 float32) on 1M points each.
     Ends with one device-to-device copy of CAL_BYTES whose counter readings
     calibrate FETCH_SIZE / WRITE_SIZE."""
     import torch
@@ -86,9 +87,15 @@ def pmc_driver(points: int, workloads=("layer",)):
         out = torch.empty_like(x)
         lw = LayerWeights(make_weights(wl.C, wl.H, wl.M, wl.dh, seed=0))
         with PhysicsAttention(wl.C, wl.H, wl.M, wl.dh, wl.tau, "bf16", group_span=wl.group_span,
-                              max_points=points) as layer:
-            for _ in range(2):
-                layer.forward(lw, x, tile=wl.tile, chunk=wl.chunk, out=out)
+                              max_points=wl.N) as layer:  # whole spans, as on the whole mesh
+            for _ in range(2):  # as layer.forward, whose launches would take four tiles each
+                layer.reset()
+                for i in range(0, points, wl.tile):
+                    layer.accumulate(lw, x[i:i + wl.tile], i)
+                layer.finalize(lw)
+                layer.attention(lw)
+                for i in range(0, points, wl.chunk):
+                    layer.deslice(lw, x[i:i + wl.chunk], out[i:i + wl.chunk])
             torch.cuda.synchronize()
         del x, out
         log("pmc driver: layer done")
@@ -121,6 +128,19 @@ def pmc_driver(points: int, workloads=("layer",)):
             torch.cuda.synchronize()
         del x, g
         log("pmc driver: backward done")
+    if "runtime" in workloads:
+        n = 1_000_000
+        for C, H, M, dtype in ((192, 4, 48, "bf16"), (256, 8, 64, "fp32")):
+            gen = torch.Generator(device="cuda")
+            gen.manual_seed(C)
+            x = torch.randn((n, C), device="cuda", dtype=torch.float32, generator=gen)
+            x = x.to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+            lw = LayerWeights(make_weights(C, H, M, C // H, seed=0))
+            with PhysicsAttention(C, H, M, C // H, 0.5, dtype, group_span=15_625, max_points=n) as layer:
+                layer.forward(lw, x, tile=n, chunk=n)
+                torch.cuda.synchronize()
+            del x
+        log("pmc driver: runtime shapes done")
     src = torch.empty(CAL_BYTES, device="cuda", dtype=torch.uint8).fill_(1)
     dst = torch.empty_like(src)
     torch.cuda.synchronize()
@@ -139,7 +159,9 @@ def pmc_driver(points: int, workloads=("layer",)):
 # pass 2 executes 2*(C*H*M + 2*M*C + C*C): logits, w s' per head, the row
 # sums, and Linear3.  The backward's dZ kernel 4, its dx kernel 10 and its dW2
 # kernel 2 (x C*H*M), of which the backward as a whole needs 14.  The dx
-# kernel writes dz (H*M floats per point), which the dW2 kernel reads.
+# kernel writes dz (H*M floats per point), which the dW2 kernel reads.  Float32
+# products are six bf16 part products each; where only one operand has three parts
+# (the slice weights of bf16 rows in the runtime-shape kernels), three.
 SQ_COUNTERS = ("SQ_INSTS_MFMA SQ_VALU_MFMA_BUSY_CYCLES SQ_INSTS_VALU SQ_INSTS_VALU_TRANS_F32 "
                "SQ_INSTS_LDS SQ_LDS_BANK_CONFLICT SQ_LDS_IDX_ACTIVE SQ_BUSY_CYCLES GRBM_GUI_ACTIVE")
 COUNTER_KERNELS = {
@@ -150,10 +172,15 @@ COUNTER_KERNELS = {
     "k_slice_accumulate_pcw<": (1_000_000, 4 * 256 * 512, 512, PEAK_BF16_TFLOPS),
     "k_deslice_pc<": (1_000_000, 4 * 256 * 512, 1024, PEAK_BF16_TFLOPS),
     "k_mlp_residual_pc<": (1_000_000, 4 * 256 * 1024, 1536, PEAK_BF16_TFLOPS),
-    # three-part operands: six bf16 products for each float32 one
+    "k_sum3<128, 64, (ts3::Sum3)0>": (1_000_000, 6 * 4 * 128 * 512, 512, PEAK_BF16_TFLOPS),
+    "k_deslice3<": (1_000_000, 6 * 4 * 128 * 512, 1024, PEAK_BF16_TFLOPS),
     "k_sum3<128, 64, (ts3::Sum3)1>": (1_000_000, 6 * 4 * 128 * 512, 1024, PEAK_BF16_TFLOPS),
     "k_bw_dx3<": (1_000_000, 6 * 10 * 128 * 512, 1536 + 4 * 512, PEAK_BF16_TFLOPS),
     "k_sum3<128, 64, (ts3::Sum3)2>": (1_000_000, 6 * 2 * 128 * 512, 512 + 4 * 512, PEAK_BF16_TFLOPS),
+    "k_slice_accumulate_rt<ts3::bf16_t": (1_000_000, (1 + 3) * 2 * 192 * 192, 384, PEAK_BF16_TFLOPS),
+    "k_deslice_rt<ts3::bf16_t": (1_000_000, (1 + 3) * 2 * 192 * 192, 768, PEAK_BF16_TFLOPS),
+    "k_slice_accumulate_rt<float": (1_000_000, 6 * 4 * 256 * 512, 1024, PEAK_BF16_TFLOPS),
+    "k_deslice_rt<float": (1_000_000, 6 * 4 * 256 * 512, 2048, PEAK_BF16_TFLOPS),
 }
 
 
@@ -213,7 +240,7 @@ def summarize_counters(sq_dir: str, fetch_dir: str, write_dir: str, command: str
              "bank%: SQ_LDS_BANK_CONFLICT / (cycles x CUs);",
              "frac: executed matrix flop / duration / the dtype's dense peak; HBM: FETCH_SIZE + WRITE_SIZE, calibrated",
              ""]
-    hdr = (f"{'kernel':26s} {'disp':>4s} {'us':>8s} {'GHz':>5s} {'TF/s':>7s} {'frac':>6s} {'mfma%':>6s} "
+    hdr = (f"{'kernel':34s} {'disp':>4s} {'us':>8s} {'GHz':>5s} {'TF/s':>7s} {'frac':>6s} {'mfma%':>6s} "
            f"{'VALU/MFMA':>9s} {'TRANS/MFMA':>10s} {'LDS/MFMA':>8s} {'lds%':>5s} {'bank%':>6s} {'HBM MB':>8s} "
            f"{'algo MB':>8s} {'GB/s':>7s}")
     lines.append(hdr)
@@ -236,7 +263,7 @@ def summarize_counters(sq_dir: str, fetch_dir: str, write_dir: str, command: str
                "bank_conflict": vals["SQ_LDS_BANK_CONFLICT"][k] / (g * n_cu) if g else None,
                "hbm_mb": hbm / 1e6, "algo_mb": bytes_pt * pts / 1e6, "gbs": hbm / t / 1e9}
         out[k] = row
-        lines.append(f"{k.rstrip('<'):26s} {row['dispatches']:4d} {row['us']:8.1f} {row['clock_ghz']:5.2f} "
+        lines.append(f"{k.rstrip('<'):34s} {row['dispatches']:4d} {row['us']:8.1f} {row['clock_ghz']:5.2f} "
                      f"{tf:7.1f} {row['frac']:6.3f} {100 * row['mfma_busy']:6.1f} {row['valu_per_mfma']:9.2f} "
                      f"{row['trans_per_mfma']:10.2f} {row['lds_per_mfma']:8.2f} {100 * row['lds_busy']:5.1f} "
                      f"{100 * row['bank_conflict']:6.2f} "
@@ -384,7 +411,7 @@ def cpu_baseline_and_parity(x_dev, W, lw, wl, sample):
 
 
 METRIC_BW = "mesh points/s per Physics-Attention layer fwd+bwd @2M pts C=128 fp32; % roofline"
-PEAK_FP32_TFLOPS = 157.3    # MI355X dense float32 matrix peak
+PEAK_FP32_PARTS_TFLOPS = PEAK_BF16_TFLOPS / 6   # a float32 product is six bf16 part products
 
 
 def cpu_baseline_backward(x_dev, g_dev, W, wl, sample):
@@ -471,8 +498,8 @@ def bench_backward(args):
     # g.Z and x.ds_raw (4), x^T dz (2), dz W2^T (2), w ds_raw (2), each x C*H*M
     flop_bw = 14 * wl.C * wl.H * wl.M
     achieved = flop_bw * N / (t_bw * 1e-3) / 1e12
-    roofline = {"bound": "mfma", "achieved": round(achieved, 2), "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
-                "frac": round(achieved / PEAK_FP32_TFLOPS, 4), "traffic": None,
+    roofline = {"bound": "mfma", "achieved": round(achieved, 2), "peak": round(PEAK_FP32_PARTS_TFLOPS, 1), "unit": "TFLOP/s",
+                "frac": round(achieved / PEAK_FP32_PARTS_TFLOPS, 4), "traffic": None,
                 "kernel": "ts3_layer_backward (all launches)", "launch_ms": round(t_bw, 4), "launches": 1}
     result = {
         "metric": METRIC_BW, "value": N / (ms * 1e-3), "unit": "points/s", "n_gpus": 1,
@@ -634,7 +661,7 @@ def main():
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--pmc-driver", action="store_true", help="short workload for rocprofv3 --pmc runs")
     ap.add_argument("--pmc-workloads", default="layer",
-                    help="comma list of layer,stack,backward for --pmc-driver")
+                    help="comma list of layer,stack,backward,runtime for --pmc-driver")
     ap.add_argument("--summarize-counters", nargs=4, metavar=("SQ_DIR", "FETCH_DIR", "WRITE_DIR", "OUT"),
                     help="per-kernel counter summary from three rocprofv3 runs of --pmc-driver")
     ap.add_argument("--summarize-traffic", nargs=2, metavar=("FETCH_DIR", "WRITE_DIR"),
