@@ -9,9 +9,9 @@ import numpy as np
 import pytest
 
 import oracle
-from gpu_helpers import banner, fp32_bar, normwise, state_of, to_device, to_host
+from gpu_helpers import assert_bf16_close, banner, fp32_bar, normwise, state_of, to_device, to_host
 from oracle import backward as BW
-from ts3_synth import make_weights
+from ts3_synth import make_weights, round_bf16
 
 pytestmark = pytest.mark.gpu
 
@@ -83,3 +83,40 @@ def test_logits_far_apart_and_an_unreachable_slice():
     assert np.isfinite(out).all()
     assert (st["d"][:, :8] == 0).all() and (st["s_raw"][:, :8] == 0).all()
     assert normwise(st["d"], ref["d"]) <= 1e-4
+
+
+@pytest.mark.parametrize("C,H,M,dtype", [
+    (64, 4, 32, "fp32"), (128, 8, 64, "fp32"), (256, 8, 64, "fp32"), (48, 3, 32, "bf16"),
+    (64, 4, 16, "bf16"), (64, 4, 32, "bf16"), (128, 8, 64, "bf16"), (256, 8, 64, "bf16"),
+])
+def test_minus_infinity_in_b2_closes_a_slice(C, H, M, dtype):
+    """A closed slice has no weight, no sums and no gradient; the others are the oracle's."""
+    import torch
+    from paper_2602_04940_amd import LayerWeights, PhysicsAttention
+    banner(f"closed slices: C={C} H={H} M={M} {dtype}")
+    N, closed = 600, np.arange(H * M) % M % 5 == 1
+    rng = np.random.default_rng(4)
+    x64 = rng.standard_normal((N, C))
+    x64 = round_bf16(x64) if dtype == "bf16" else x64.astype(np.float32).astype(np.float64)
+    W = make_weights(C, H, M, C // H, seed=5, bias_seed=6)
+    W["b2"] = np.where(closed, -np.inf, W["b2"]).astype(np.float32)
+    W64 = {k: v.astype(np.float64) for k, v in W.items()}
+    lw, x = LayerWeights(W), to_device(x64, dtype)
+    ref = oracle.build_state(x64, W64, H, M, 2.0)
+    want = oracle.deslice(x64, W["W2"], W["b2"], ref["Z"], W["b3"], H, M, 2.0)
+    with PhysicsAttention(C, H, M, C // H, 0.5, dtype, group_span=256, max_points=N) as layer:
+        out = to_host(layer.forward(lw, x, tile=256))
+        st = state_of(layer)
+        if dtype == "fp32" and C <= 128:
+            g64 = rng.standard_normal((N, C)).astype(np.float32).astype(np.float64)
+            dx, grads = layer.backward(lw, x, to_device(g64, "fp32"), tile=256)
+            bref = BW.layer_backward(x64, W64, g64, H, M, 2.0)
+            assert normwise(to_host(dx), bref["dx"]) <= fp32_bar("dx")
+            for n, v in grads.items():
+                assert normwise(to_host(v), bref[n]) <= fp32_bar(n), n
+            assert bool((grads["dW2"][:, torch.from_numpy(closed)] == 0).all())
+    assert (st["d"].reshape(-1)[closed] == 0).all()
+    if dtype == "fp32":
+        assert normwise(out, want) <= fp32_bar("out")
+    else:
+        assert_bf16_close(out, want, "out")
